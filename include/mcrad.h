@@ -121,8 +121,9 @@ typedef struct {
  * Weight sums are raw packet-weight sums; multiply by `scale` (total source
  * measure / n_packets) for power.  launched + roulette_gain - roulette_loss
  * equals absorbed + escaped up to FP32 rounding.  generations: tiled
- * transport generations the run used before its tail went to the finisher
- * (0 for the whole-grid transport). */
+ * transport generations the run used before its tail was handed over (a run
+ * without generations: its walk-and-tally rounds; 0 for the whole-grid
+ * transport). */
 typedef struct {
     double launched, absorbed, escaped, roulette_gain, roulette_loss;
     double scale;
@@ -143,9 +144,12 @@ typedef struct {
  *  tile           tile side in pixels, 1 .. 256 (default, or a tile whose
  *                 tally does not fit: the largest square tile whose tally
  *                 fits the LDS of one workgroup per CU, 23 at N = 16)
- *  finish_packets once every packet is launched and at most this many remain
- *                 they finish without migration (default: the smaller of
- *                 2^16 and live_packets / 128)
+ *  finish_packets once every packet is launched and at most twice this many
+ *                 remain they finish without migration, in rounds of walk
+ *                 and tally (mc_run_noalloc: at most this many, in one
+ *                 kernel).  A run of few packets that the pool holds at once
+ *                 does so from its launch.  (default: the smaller of 2^16
+ *                 and live_packets / 128)
  *  grid_max_packets  a run whose tally fits one workgroup's LDS uses the
  *                 whole-grid kernel only up to this many packets, larger runs
  *                 the tiled transport (default 2^21)
@@ -154,7 +158,8 @@ typedef struct {
  *                 to the tile tally in parts, 0 .. 65536 (default 65536)
  *  tail_visits    once a job has turned quiet (quiet_percent), its packets
  *                 pause after this many more visits, 0 .. 2^30 (default 1)
- *  max_generations  tiled generations enqueued per call, 1 .. 65536
+ *  max_generations  tiled generations (rounds, in a run without generations)
+ *                 enqueued per call, 1 .. 65536
  *                 (default 0: 100, plus 30 per tile along the longest
  *                 grid side of any problem, plus 48 per pool of
  *                 live_packets the run's packets fill).  The host enqueues this many without

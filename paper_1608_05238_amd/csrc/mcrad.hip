@@ -22,8 +22,10 @@
 //      - tiled mode: square tiles of the grid, packets migrate between tiles
 //        in generations (launch and count, sort of record indices by tile,
 //        one workgroup job per tile batch, tile tally added to the FP64 map
-//        per job); a finisher kernel moves the last packets to their end
-//        without migration;
+//        per job);
+//      - walk and tally (few packets, and the last packets of a tiled run):
+//        packets move without migration or tally and write their segments as
+//        events, which a second kernel adds up tile by tile, in rounds;
 //  * every value a kernel needs that depends on device data (the sum and
 //    maximum of a source map, the fixed-point scale, the normalisation) is
 //    computed on the device, and the tiled generations are steered by a
@@ -44,6 +46,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "mcrad.h"
@@ -176,7 +179,7 @@ struct Packet {
     int ix, iz;
     float fx, fz;      // offset inside the pixel, pixel units
     float sx, sz;      // direction (sin t, cos t)
-    float isx, isz;    // reciprocals (inf for a zero component)
+    float isx, isz;    // reciprocals (not read for a zero component)
     float w, w0abs;
     float tau;         // optical depth left on the current free path
     float uh, ur;      // HG and roulette uniforms of the current block
@@ -273,9 +276,10 @@ __device__ __forceinline__ float profile(const ProbDev &S, const SrcDev &s, floa
 __device__ __forceinline__ void set_dir(Packet &p, float sx, float sz) {
     p.sx = sx;
     p.sz = sz;
-    // hardware reciprocal (1 ulp): enough for distances to pixel faces
-    p.isx = sx != 0.f ? __builtin_amdgcn_rcpf(sx) : INFINITY;
-    p.isz = sz != 0.f ? __builtin_amdgcn_rcpf(sz) : INFINITY;
+    // hardware reciprocal (1 ulp): enough for distances to pixel faces; that of
+    // a zero component (an infinity) is not read (step)
+    p.isx = __builtin_amdgcn_rcpf(sx);
+    p.isz = __builtin_amdgcn_rcpf(sz);
 }
 
 // Draw block k: free path (optical depth) and the uniforms used at its end.
@@ -394,17 +398,17 @@ __device__ bool launch(const ProbDev &P, uint64_t pid, Packet &p, float *h, Ledg
 // sum_k (-x)^k/(k+1)! in Horner form, truncated after x^7 (remainder below
 // x^8/9! ~ 4e-11 there); above, the library expm1.
 __device__ __forceinline__ float absorbed_per_depth(float x) {
-    if (x < 0.25f) {
-        float t = -1.f / 40320.f;
-        t = fmaf(t, x, 1.f / 5040.f);
-        t = fmaf(t, x, -1.f / 720.f);
-        t = fmaf(t, x, 1.f / 120.f);
-        t = fmaf(t, x, -1.f / 24.f);
-        t = fmaf(t, x, 1.f / 6.f);
-        t = fmaf(t, x, -0.5f);
-        return fmaf(t, x, 1.f);
-    }
-    return -expm1f(-x) * __builtin_amdgcn_rcpf(x);
+    float t = -1.f / 40320.f;
+    t = fmaf(t, x, 1.f / 5040.f);
+    t = fmaf(t, x, -1.f / 720.f);
+    t = fmaf(t, x, 1.f / 120.f);
+    t = fmaf(t, x, -1.f / 24.f);
+    t = fmaf(t, x, 1.f / 6.f);
+    t = fmaf(t, x, -0.5f);
+    t = fmaf(t, x, 1.f);
+    // one branch, around the rarer case only
+    if (__builtin_expect(!(x < 0.25f), 0)) t = -expm1f(-x) * __builtin_amdgcn_rcpf(x);
+    return t;
 }
 
 // One segment: run to the next pixel face or to the end of the free path,
@@ -466,24 +470,43 @@ __device__ __forceinline__ float sinpi_half(float x) {
 template <class PP, class LG>
 __device__ __forceinline__ bool scatter_roulette(const PP &P, Packet &p, const bool at, LG &L) {
     bool kill = false;
-    const bool low = at && (p.k >= kMaxInteractions || fabsf(p.w) < P.wth * p.w0abs);
-    if (__ballot(low)) {   // rare
-        if (low) {
-            if (p.k >= kMaxInteractions || (P.flags & MC_FLAG_LITERAL_TRUNCATION) || !(p.ur < P.inv_rm)) {
-                kill = true;
-                L.loss += p.w;
-            } else {
-                L.gain += (P.rm - 1.f) * p.w;
-                p.w *= P.rm;
-            }
+    // (no short circuit: that would be a branch)
+    const bool low = at & ((p.k >= kMaxInteractions) | (fabsf(p.w) < P.wth * p.w0abs));
+    if (__builtin_expect(low, 0)) {   // rare
+        if (p.k >= kMaxInteractions || (P.flags & MC_FLAG_LITERAL_TRUNCATION) || !(p.ur < P.inv_rm)) {
+            kill = true;
+            L.loss += p.w;
+        } else {
+            L.gain += (P.rm - 1.f) * p.w;
+            p.w *= P.rm;
         }
     }
     return kill;
 }
 
-// Then the 2D HG deflection (eq. scattering_angle) written without atan/tan:
-// with a = (1+g) cos(pi(u-1/2)), b = (1-g) sin(pi(u-1/2)), tan(dt/2) = b/a,
-// so cos dt = (a^2-b^2)/(a^2+b^2), sin dt = 2ab/(a^2+b^2); and the next
+// The 2D HG deflection (eq. scattering_angle) written without atan/tan: with
+// a = (1+g) cos(pi(u-1/2)), b = (1-g) sin(pi(u-1/2)), tan(dt/2) = b/a, so
+// cos dt = (a^2-b^2)/(a^2+b^2), sin dt = 2ab/(a^2+b^2).  In two parts, of
+// which the first needs the random number alone.
+__device__ __forceinline__ void hg_factors(float u, float &sp, float &cp) {
+    const float y = u - 0.5f;                // exact
+    sp = sinpi_half(y);                      // sin(pi (u - 1/2))
+    cp = sinpi_half(0.5f - fabsf(y));        // cos(pi (u - 1/2)); the argument min(u, 1 - u) is exact
+}
+
+__device__ __forceinline__ void hg_rotate(float g, float sp, float cp, float sx, float sz, float &nx_, float &nz_) {
+    // (fused as written, so that every kernel gets the same bits)
+    const float a = (1.f + g) * cp, b = (1.f - g) * sp, bb = b * b;
+    const float inv = __builtin_amdgcn_rcpf(fmaf(a, a, bb));
+    const float cd = fmaf(a, a, -bb) * inv, sd = 2.f * a * b * inv;
+    nx_ = fmaf(sx, cd, sz * sd);
+    nz_ = fmaf(sz, cd, -(sx * sd));
+    const float rn = __builtin_amdgcn_rsqf(fmaf(nx_, nx_, nz_ * nz_));   // argument ~1
+    nx_ *= rn;
+    nz_ *= rn;
+}
+
+// Then the deflection and the next
 // block of random numbers.  `go` marks the lanes that scatter and survived;
 // every lane runs the same instructions and only those lanes commit
 // (selects, so the Philox rounds and the deflection form one basic block the
@@ -491,21 +514,12 @@ __device__ __forceinline__ bool scatter_roulette(const PP &P, Packet &p, const b
 template <class PP, class LG>
 __device__ __forceinline__ void scatter_deflect(const PP &P, Packet &p, const bool go, const bool kill, const float g,
                                                 LG &L) {
-    const float y = p.uh - 0.5f;                 // exact
-    const float sp = sinpi_half(y);              // sin(pi (u - 1/2))
-    const float cp = sinpi_half(0.5f - fabsf(y));  // cos(pi (u - 1/2)); the argument min(u, 1 - u) is exact
-    const float a = (1.f + g) * cp, b = (1.f - g) * sp;
-    const float inv = __builtin_amdgcn_rcpf(a * a + b * b);
-    const float cd = (a * a - b * b) * inv, sd = 2.f * a * b * inv;
-    float nx_ = p.sx * cd + p.sz * sd;
-    float nz_ = p.sz * cd - p.sx * sd;
-    const float rn = __builtin_amdgcn_rsqf(nx_ * nx_ + nz_ * nz_);   // argument ~1
-    nx_ *= rn;
-    nz_ *= rn;
+    float sp, cp, nx_, nz_;
+    hg_factors(p.uh, sp, cp);
+    hg_rotate(g, sp, cp, p.sx, p.sz, nx_, nz_);
     const uint4 r = rng_block(P, p.pid, p.k + 1);
     const float tau = __builtin_amdgcn_logf(u01(r.x)) * -0.693147180559945309f;   // see new_leg
-    const float isx = nx_ != 0.f ? __builtin_amdgcn_rcpf(nx_) : INFINITY;
-    const float isz = nz_ != 0.f ? __builtin_amdgcn_rcpf(nz_) : INFINITY;
+    const float isx = __builtin_amdgcn_rcpf(nx_), isz = __builtin_amdgcn_rcpf(nz_);   // see set_dir
     p.sx = go ? nx_ : p.sx;
     p.sz = go ? nz_ : p.sz;
     p.isx = go ? isx : p.isx;
@@ -933,9 +947,42 @@ __device__ __forceinline__ void count_tile(const Gen &G, uint32_t *hist, bool lo
     }
 }
 
-// The scan of a generation, by the last workgroup of k_gen_count: exclusive
-// scan of the tile counts into cursors and a job list; bookkeeping of the
-// launches; the finisher decision; reset of the other pool's counters.
+// Counts the slots [0, n) by their tile, kCountPer per thread with every load
+// issued before the first is counted (an index past the end reads the last
+// slot, then counts as none), and adds the workgroup's histogram to the tile
+// counts.
+__device__ __forceinline__ void count_slots(const Gen &G, uint32_t *hist, bool local, const uint32_t *ct, uint32_t n) {
+    for (uint32_t b0 = blockIdx.x * kGenBlock * kCountPer; b0 < n; b0 += gridDim.x * kGenBlock * kCountPer) {
+        uint32_t t[kCountPer];
+#pragma unroll
+        for (int r = 0; r < kCountPer; ++r) t[r] = ct[min(b0 + r * kGenBlock + threadIdx.x, n - 1u)];
+#pragma unroll
+        for (int r = 0; r < kCountPer; ++r) {
+            const bool in = b0 + r * kGenBlock + threadIdx.x < n;
+            count_tile(G, hist, local, t[r], in && t[r] != kInvalidTile);
+        }
+    }
+    __syncthreads();
+    if (local)
+        for (int i = threadIdx.x; i < G.ntiles; i += kGenBlock)
+            if (hist[i]) atomicAdd(G.tile_count + i, hist[i]);
+}
+
+// True in the last workgroup of the grid to call it, which then sees
+// everything that the others wrote before.
+__device__ __forceinline__ bool last_workgroup(uint32_t *done) {
+    __shared__ int s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_last = atomicAdd(done, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!s_last) return false;
+    __threadfence();
+    return true;
+}
+
 // Inclusive scan of one count per thread over the kGenBlock threads of the
 // workgroup, and the workgroup's total: within each wave by shuffles, then
 // over the waves' totals (two barriers instead of two per doubling step).
@@ -960,15 +1007,15 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint3
     return v + pre;
 }
 
-__device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint32_t *a_prob, const uint32_t *a_new) {
-    GenCtl *C = G.ctl;
-    const int cur = g & 1;
+// Exclusive scan of G.tile_count into the tiles' sort cursors and the job
+// list (every thread of the workgroup calls it; tile_count is cleared).
+// Returns the number of jobs, 0 if the records or jobs do not fit.
+__device__ uint32_t scan_tiles(const Gen &G, uint32_t *buf, uint32_t &total, bool &fits) {
     const int t = threadIdx.x;
     const int per = (G.ntiles + kGenBlock - 1) / kGenBlock;
     const int a = t * per, b = min(G.ntiles, a + per);
     uint32_t nrec = 0;
     for (int i = a; i < b; ++i) nrec += G.tile_count[i];
-    uint32_t total = 0;
     const uint32_t rec_incl = block_scan(nrec, buf, total);
     // job size: job_size, or smaller when the generation's records would not
     // give every workgroup two jobs (never below job_min): a generation with
@@ -979,7 +1026,7 @@ __device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint3
     for (int i = a; i < b; ++i) njob += (G.tile_count[i] + js - 1) / js;
     uint32_t total_jobs = 0;
     const uint32_t job_incl = block_scan(njob, buf, total_jobs);
-    const bool fits = total <= G.live && total_jobs <= G.max_jobs;   // hold by construction
+    fits = total <= G.live && total_jobs <= G.max_jobs;   // hold by construction
     uint32_t roff = rec_incl - nrec, joff = job_incl - njob;
     for (int i = a; i < b; ++i) {
         const uint32_t c = G.tile_count[i];
@@ -990,6 +1037,19 @@ __device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint3
         roff += c;
         G.tile_count[i] = 0;
     }
+    return fits ? total_jobs : 0u;
+}
+
+// The scan of a generation, by the last workgroup of k_gen_count: cursors and
+// job list; bookkeeping of the launches; the finisher decision; reset of the
+// other pool's counters.
+__device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint32_t *a_prob, const uint32_t *a_new) {
+    GenCtl *C = G.ctl;
+    const int cur = g & 1;
+    const int t = threadIdx.x;
+    uint32_t total = 0;
+    bool fits = true;
+    const uint32_t total_jobs = scan_tiles(G, buf, total, fits);
     __syncthreads();
     if (t == 0) {
         uint64_t lt = C->launched_total;
@@ -1002,7 +1062,7 @@ __device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint3
         while (p < (uint32_t)G.nprob && G.launched[p] >= G.probs[p].todo) ++p;
         C->new_first_prob = p;
         C->n_rec = total;
-        C->n_jobs = fits ? total_jobs : 0u;
+        C->n_jobs = total_jobs;
         C->job_cursor = 0;
         if (!fits) C->overflow = 1u;
         // the packets left fit the finisher: this generation moves nothing
@@ -1029,7 +1089,7 @@ __global__ void __launch_bounds__(kGenBlock) k_gen_count(Gen G, int g) {
     __shared__ uint64_t a_base[kMaxAlloc];
     __shared__ uint32_t w_cnt[kGenBlock / 64];
     __shared__ uint32_t s_base;
-    __shared__ int s_np, s_last;
+    __shared__ int s_np;
     if (C->done) return;   // uniform: written by an earlier kernel
     const int cur = g & 1;
     const int lane = __lane_id(), wave = threadIdx.x >> 6;
@@ -1112,34 +1172,9 @@ __global__ void __launch_bounds__(kGenBlock) k_gen_count(Gen G, int g) {
         const ProbDev &q = G.probs[a_prob[lk]];
         ledger_flush_block(q.led, q.ledc, L);
     }
-    // the records carried over from the last generation, kCountPer per
-    // thread with every load issued before the first is counted (an index
-    // past the records reads the last one, then counts as no record)
-    const uint32_t nc = min(C->nc[cur], G.cap_c);
-    const uint32_t *ct = G.ptile[cur];
-    for (uint32_t b0 = blockIdx.x * kGenBlock * kCountPer; b0 < nc; b0 += gridDim.x * kGenBlock * kCountPer) {
-        uint32_t t[kCountPer];
-#pragma unroll
-        for (int r = 0; r < kCountPer; ++r) t[r] = ct[min(b0 + r * kGenBlock + threadIdx.x, nc - 1u)];
-#pragma unroll
-        for (int r = 0; r < kCountPer; ++r) {
-            const bool in = b0 + r * kGenBlock + threadIdx.x < nc;
-            count_tile(G, hist, local, t[r], in && t[r] != kInvalidTile);
-        }
-    }
-    __syncthreads();
-    if (local)
-        for (int i = threadIdx.x; i < G.ntiles; i += kGenBlock)
-            if (hist[i]) atomicAdd(G.tile_count + i, hist[i]);
-    // the last workgroup to finish sees every count and scans them
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        s_last = atomicAdd(&C->wg_done, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
+    // the records carried over from the last generation
+    count_slots(G, hist, local, G.ptile[cur], min(C->nc[cur], G.cap_c));
+    if (!last_workgroup(&C->wg_done)) return;
     gen_scan(G, g, hist, np, a_prob, a_new);
 }
 
@@ -1159,14 +1194,9 @@ __device__ __forceinline__ uint32_t gen_slot(const Gen &G, uint32_t u, uint32_t 
     return u < nc ? u : G.cap_c + (u - nc);
 }
 
-__global__ void __launch_bounds__(256) k_gen_scatter(Gen G, int g) {
-    extern __shared__ uint32_t cnt[];   // [ntiles] when ntiles <= kHistTiles (gen_hist_lds)
-    GenCtl *C = G.ctl;
-    if (C->done) return;
-    const int cur = g & 1;
-    const uint32_t nc = min(C->nc[cur], G.cap_c), nl = min(C->nl[cur], G.cap_l);
+// cnt: [ntiles] words of LDS when ntiles <= kHistTiles; pt: the slots' tiles
+__device__ __forceinline__ void sort_slots(const Gen &G, uint32_t *cnt, const uint32_t *pt, uint32_t nc, uint32_t nl) {
     const uint32_t n = nc + nl;
-    const uint32_t *pt = G.ptile[cur];
     const int lane = __lane_id();
     if (G.ntiles <= kHistTiles) {
         for (int i = threadIdx.x; i < G.ntiles; i += blockDim.x) cnt[i] = 0u;
@@ -1244,6 +1274,14 @@ __global__ void __launch_bounds__(256) k_gen_scatter(Gen G, int g) {
             }
         }
     }
+}
+
+__global__ void __launch_bounds__(256) k_gen_scatter(Gen G, int g) {
+    extern __shared__ uint32_t cnt[];
+    const GenCtl *C = G.ctl;
+    if (C->done) return;
+    const int cur = g & 1;
+    sort_slots(G, cnt, G.ptile[cur], min(C->nc[cur], G.cap_c), min(C->nl[cur], G.cap_l));
 }
 
 // ---- generation step 3: move the packets tile by tile
@@ -1465,6 +1503,710 @@ k_transport_tile(Gen G, int g) {
     if (cur_prob >= 0) ledger_flush_tile(G.probs[cur_prob].led, G.probs[cur_prob].ledc, L);   // uniform
 }
 
+// ------------------------------------------------------------------ walk and tally
+// A run of few packets, and the last packets of a large one, are bound by the
+// serial chain of the longest histories and by the cost of a generation, not
+// by issue: with at most a few packets per lane the tile kernel would need a
+// generation per tile crossing.  Here the two halves of a step are kernels of
+// their own, in rounds:
+//  * k_walk moves packets wherever they go, one per lane, without any tally:
+//    each segment is written as an event {T fx, sx, sz, pixel in tile | end of
+//    visit} to the lane's own stretch of a buffer in HBM.  Consecutive events
+//    in one tile form a run; runs are sorted by tile like records;
+//  * k_tally takes jobs of runs of one tile, sums their events per visit and
+//    adds the visits to the tile's LDS tally with the arithmetic of the tile
+//    kernel (deposit_harmonics, fixed_add_raw), one lane per run.
+// A round ends when the lanes have filled their stretches; packets alive then
+// go on in the next, with longer stretches the fewer they are.  A visit open
+// at that point hands its FP32 sums from one round's tally to the next
+// (carry), so every visit adds the same integers as in any other kernel.
+// Measured (start to end of mc_forward / mc_adjoint): 1e6 packets on a 256^2
+// disc 45.6 -> 23.2 ms, 5e5 adjoint packets at N = 32 on 149 x 101 34.1 -> 14.2
+// ms, against generations and a finisher that added each visit to HBM.  What
+// bounds it now: for few packets the ~170 instructions of a segment in a lone
+// wave (0.5 us); for many, issue (62% busy) and memory latency in k_walk, the
+// LDS atomics (75% active) in k_tally.
+constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
+constexpr uint32_t kRunSlice = 256;         // run slots a wave reserves at a time
+constexpr uint32_t kRunMax = 32;           // a longer run is cut at the end of a visit (tally lanes stay balanced)
+constexpr uint32_t kWalkLanes = 7u << 14;  // lanes that walk at once
+constexpr uint32_t kWalkAhead = 1u << 16;  // up to this many lanes prefetch both neighbours
+constexpr uint32_t kVisitEnd = 0x80000000u;
+// The handed-over packets are taken through one cursor per part, each on a
+// cache line of its own: a single cursor serialises the waves' atomics when
+// many packets end early.
+constexpr uint32_t kWalkParts = 16;
+constexpr int kRing = 16;                  // random blocks held ready per lane
+
+struct alignas(16) RunRec {
+    uint32_t first;     // first event, in units of 4
+    uint32_t len;       // events
+    uint32_t resume;    // carry slot of the visit the run continues, or kNoSlot
+    uint32_t suspend;   // carry slot of the visit it leaves open, or kNoSlot
+};
+
+// Device control block of the rounds (zeroed at set-up).
+struct WalkCtl {
+    uint32_t w_end;          // rounds from this one on do nothing
+    uint32_t n_p, pool, nc;  // packets handed over: slots in all, pool, slots in its carried region
+    uint32_t left;           // of them, not yet taken when the coming round starts
+    uint32_t lanes, cap;     // lanes and events per lane of the coming round
+    uint32_t n_jobs;
+    struct alignas(128) Line { uint32_t taken; };
+    Line part[kWalkParts];   // handed-over slots taken from each of kWalkParts equal parts
+    alignas(128) uint32_t wg_done;      // workgroups of k_run_count that finished
+    alignas(128) uint32_t job_cursor;
+    alignas(128) uint32_t n_state0;     // packets going on in even ...
+    alignas(128) uint32_t n_state1;     // ... and odd rounds
+    alignas(128) uint32_t n_run0;       // run slots reserved in even ...
+    alignas(128) uint32_t n_run1;       // ... and odd rounds
+    __device__ uint32_t &n_state(int par) { return par ? n_state1 : n_state0; }
+    __device__ uint32_t &n_run(int par) { return par ? n_run1 : n_run0; }
+};
+
+// Part j of the n_p handed-over slots.
+__device__ __forceinline__ uint32_t part_begin(uint32_t n_p, uint32_t j) {
+    return (uint32_t)((uint64_t)n_p * j / kWalkParts);
+}
+
+struct Walk {
+    Gen runs;                     // the sort's view of the runs (ptile[0], sidx, jobs, counts)
+    const ProbDev *probs;
+    const GenCtl *gctl;
+    const PacketRec *pool[2];     // packets handed over by the generations
+    const uint32_t *ptile[2];
+    uint32_t pool_cap_c, pool_cap_l;
+    PacketRec *state[2];          // packets going on, by parity of the round that takes them [lanes_max]
+    float *carry[2];              // sums of their open visits [lanes_max][K]
+    float4 *ev;                   // events [ev_cap]
+    RunRec *run;
+    uint32_t lanes_max, run_cap;
+    uint64_t ev_cap;
+    WalkCtl *ctl;
+};
+
+// Lanes and events per lane of the next round: every packet left, up to
+// lanes_max at a time; the whole buffer shared out in fours.
+__device__ __forceinline__ void walk_share(const Walk &W, WalkCtl *C, uint32_t n_state, uint32_t left) {
+    const uint32_t lanes = (uint32_t)min<uint64_t>(W.lanes_max, (uint64_t)n_state + left);
+    C->lanes = lanes;
+    C->cap = (uint32_t)min<uint64_t>(1u << 20, W.ev_cap / max(lanes, 1u)) & ~3u;
+}
+
+// Hands the generations' packets to the rounds: those the finisher threshold
+// left, or the leavers of the last generation enqueued.
+__global__ void k_walk_init(Walk W, int g_last) {
+    WalkCtl *C = W.ctl;
+    const GenCtl *X = W.gctl;
+    uint32_t pool = X->fin_pool, nc = X->fin_nc, nl = X->fin_nl;
+    if (!X->done) {
+        pool = (uint32_t)(g_last & 1);
+        nc = min(X->nc[pool], W.pool_cap_c);
+        nl = 0;
+    }
+    C->pool = pool;
+    C->nc = nc;
+    C->n_p = nc + nl;
+    C->w_end = nc + nl ? 0xFFFFFFFFu : 0u;
+    C->left = nc + nl;
+    walk_share(W, C, 0, nc + nl);
+}
+
+// Ledger of lanes that may hold different problems (prob < 0: nothing held):
+// the lanes of each problem in turn are summed over the wave and one lane
+// adds the sums to that problem's ledger.
+__device__ __forceinline__ void ledger_flush_lanes(const ProbDev *probs, int prob, const LedgerRegs &L) {
+    const int lane = __lane_id();
+    int pend = prob;
+    for (;;) {
+        const unsigned long long m = __ballot(pend >= 0);
+        if (!m) break;
+        const int leader = __ffsll((long long)m) - 1;
+        const int p0 = __shfl(pend, leader);
+        const bool mine = pend == p0;
+        double v[5] = {L.launched, L.absorbed, L.escaped, L.gain, L.loss};
+        unsigned long long c[4] = {L.packets, L.segments, L.visits, L.scatters};
+#pragma unroll
+        for (int i = 0; i < 5; ++i) v[i] = mine ? v[i] : 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = mine ? c[i] : 0ull;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+            for (int i = 0; i < 5; ++i) v[i] += __shfl_xor(v[i], off);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] += __shfl_xor(c[i], off);
+        }
+        if (lane == leader) {
+            const ProbDev &S = probs[p0];
+            for (int i = 0; i < 5; ++i)
+                if (v[i] != 0.0) atomicAdd(S.led + i, v[i]);
+            for (int i = 0; i < 4; ++i)
+                if (c[i]) atomicAdd(S.ledc + i, c[i]);
+        }
+        if (mine) pend = -1;
+    }
+}
+
+// What a walking lane needs of its packet's problem.
+struct WalkProb {
+    Hot H;
+    const float4 *med;
+    float fx;
+    int ntx, tile_base;
+};
+
+__device__ __forceinline__ WalkProb walk_prob(const ProbDev &S) {
+    return WalkProb{hot_of(S), S.med, S.fx, S.ntx, S.tile_base};
+}
+
+// The ledger of a lane whose packet's problem changes (rare: a batch).
+__device__ __forceinline__ void ledger_flush_lane(const ProbDev &O, const LedgerRegs &L) {
+    const double v[5] = {L.launched, L.absorbed, L.escaped, L.gain, L.loss};
+    const unsigned long long c[4] = {L.packets, L.segments, L.visits, L.scatters};
+    for (int i = 0; i < 5; ++i)
+        if (v[i] != 0.0) atomicAdd(O.led + i, v[i]);
+    for (int i = 0; i < 4; ++i)
+        if (c[i]) atomicAdd(O.ledc + i, c[i]);
+}
+
+// Lanes of the mask below this one.
+__device__ __forceinline__ uint32_t rank_in(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Adds n to a counter once for the wave and returns its old value, the same
+// in every lane (every lane of the wave calls it).
+__device__ __forceinline__ uint32_t wave_claim(uint32_t *counter, uint32_t n) {
+    uint32_t b = 0;
+    if (__lane_id() == 0) b = atomicAdd(counter, n);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+}
+
+// A workgroup is two waves, one packet per lane of the first: that wave moves
+// the packets, the second keeps a ring of their next random blocks in LDS,
+// with what depends on the random numbers alone (free path, roulette draw,
+// factors of the deflection) worked out.  With few packets a pass costs the
+// latency of its instructions, and this takes half of them off the chain;
+// with many, a block is computed once per scatter instead of once per segment.
+// Workgroups this small spread over the CUs one by one, so that a few thousand
+// packets use every SIMD.  Each pass of the inner loop is one segment; runs,
+// refills and the space left are looked after every fourth.
+// ONE: a single problem, whose parameters are the same in every lane.
+template <bool ONE>
+__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k_walk(Walk W, int r) {
+    // entry k % kRing: roulette draw, cos and sin factors of block k, optical depth of block k + 1
+    __shared__ float4 ring[kRing][64];
+    // what the first wave posts, by parity of the post
+    __shared__ uint32_t s_k[2][64], s_new[2][64], s_prob[2][64];
+    __shared__ uint64_t s_pid[2][64];
+    __shared__ uint32_t s_stop[2];
+    // four events per lane on their way to memory; lane l's event u of a batch
+    // is at (4 l + (l / 4) % 4) ^ u, which spreads both sides over the banks
+    __shared__ float4 s_ev[256];
+    WalkCtl *C = W.ctl;
+    if ((uint32_t)r >= C->w_end) return;
+    const uint32_t lanes = C->lanes;
+    if (blockIdx.x * 64u >= lanes) return;
+    const int lane = __lane_id();
+
+    if (threadIdx.x >= 64u) {
+        uint64_t seed = W.probs[0].seed, pid = 0;
+        uint32_t tag = W.probs[0].tag;
+        uint32_t have = 0;   // blocks up to this one are in the ring
+        // One barrier a post: blocks asked for at one post are computed while
+        // the first wave moves its packets, and are there after the next.
+        for (uint32_t side = 0;; side ^= 1u) {
+            __syncthreads();
+            if (s_stop[side]) break;
+            const uint32_t k = s_k[side][lane];
+            const bool live = k != kNoSlot;
+            if (s_new[side][lane]) {
+                have = k - 1u;
+                pid = s_pid[side][lane];
+                if constexpr (!ONE) {
+                    seed = W.probs[s_prob[side][lane]].seed;
+                    tag = W.probs[s_prob[side][lane]].tag;
+                }
+            }
+            // Until the next post the first wave uses blocks up to k + 4 and the
+            // entries from k on; after it, with k at most 4 larger, blocks up
+            // to k + 8.  A lane with space takes part in every block computed
+            // (its ring fills up), so most do.
+            while (__ballot(live && (int)(have - k) < 8)) {
+                if (live && (int)(have - k) < kRing - 1) {
+                    ++have;
+                    const uint4 b = philox4x32_10(make_uint4(have, tag, (uint32_t)pid, (uint32_t)(pid >> 32)),
+                                                  (uint32_t)seed, (uint32_t)(seed >> 32));
+                    const float tau = __builtin_amdgcn_logf(u01(b.x)) * -0.693147180559945309f;   // see new_leg
+                    float sp, cp;
+                    hg_factors(u01(b.y), sp, cp);
+                    ring[(have - 1u) % kRing][lane].w = tau;
+                    float4 &e = ring[have % kRing][lane];
+                    e.x = u01(b.z);
+                    e.y = cp;
+                    e.z = sp;
+                }
+            }
+        }
+        return;
+    }
+
+    const int par = r & 1;
+    const uint32_t gid = blockIdx.x * 64u + threadIdx.x;
+    const uint32_t cap = C->cap, n_state = C->n_state(par), n_p = C->n_p, nc = C->nc;
+    const PacketRec *pool = W.pool[C->pool];
+    const uint32_t *ptile = W.ptile[C->pool];
+    const int tw = W.runs.tw, th = W.runs.th;
+    const uint64_t ev0 = (uint64_t)gid * cap;   // a multiple of 4
+    const uint32_t s_ev0 = 4u * lane + ((lane >> 2) & 3u);
+    // few packets: the medium of both pixels the packet may enter next is
+    // loaded a segment ahead
+    const bool ahead = lanes <= kWalkAhead;
+
+    // what a lane does (bit 0 beside: its last event left a visit open)
+    enum : uint32_t {
+        kMove = 0,     // moves its packet
+        kLeft = 2,     // its packet left the tile
+        kDead = 4,     // its packet was terminated
+        kEmpty = 8,    // has no packet
+        kPark = 16,    // holds a packet that goes on in the next round
+        kIdle = 32,    // has no packet and takes none
+        kWait = 64,    // has a packet whose random blocks have been asked for
+    };
+    WalkProb Q = walk_prob(W.probs[0]);
+    int prob = ONE ? 0 : -1;
+    LedgerRegs L;
+    Packet p;                  // ix, iz: pixel within the tile
+    idle_packet(p, 0, 0);
+    Hot B = Q.H;               // as Q.H, with the extent of the tile's part in the grid
+    float4 mm = make_float4(0.f, 0.f, 0.f, 0.f), mx = mm, mz = mm;   // medium here, and of the neighbours ahead
+    int tx0 = 0, tz0 = 0;
+    uint32_t tile = 0, k0 = 0, resume = kNoSlot;
+    uint32_t n = 0, run0 = 0;  // events written; the first of the current run
+    uint32_t lim = 0;          // event count at which the run or the space has to be looked after
+    uint32_t fl = gid < lanes ? kEmpty : kIdle;
+    bool more = C->left != 0;  // handed-over packets may be left (wave-uniform)
+    uint32_t part = blockIdx.x % kWalkParts, tries = 0;
+    uint32_t rbase = 0, rused = kRunSlice;
+
+    // gives the runs of the lanes with `close` set a slot and writes them
+    auto put_runs = [&](bool close, uint32_t suspend) {
+        const unsigned long long m = __ballot(close);
+        if (!m) return;
+        const uint32_t c = (uint32_t)__popcll(m);
+        if (rused + c > kRunSlice) {
+            for (uint32_t i = rused + lane; i < kRunSlice; i += 64)
+                if (rbase + i < W.run_cap) W.runs.ptile[0][rbase + i] = kInvalidTile;
+            rbase = wave_claim(&C->n_run(par), kRunSlice);
+            rused = 0;
+        }
+        if (close) {
+            const uint32_t slot = rbase + rused + rank_in(m);
+            if (slot < W.run_cap) {   // always: a run holds at least four events' space
+                *reinterpret_cast<uint4 *>(W.run + slot) =
+                    make_uint4((uint32_t)((ev0 + run0) >> 2), n - run0, resume, suspend);
+                W.runs.ptile[0][slot] = tile;
+            } else {
+                atomicOr(const_cast<uint32_t *>(&W.gctl->overflow), 1u);
+            }
+            L.segments += n - run0;
+        }
+        rused += c;
+    };
+    // the pixel's index in the medium table, and its loads
+    auto pixel = [&] { return (tz0 + p.iz) * Q.H.nx + tx0 + p.ix; };
+    auto load_ahead = [&](int i) {
+        mx = load_medium(Q.med, i + (p.sx > 0.f ? 1 : -1));
+        mz = load_medium(Q.med, i + (p.sz > 0.f ? Q.H.nx : -Q.H.nx));
+    };
+    auto enter_tile = [&] {
+        B.nx = min(tw, Q.H.nx - tx0);
+        B.nz = min(th, Q.H.nz - tz0);
+        const int i = pixel();
+        mm = load_medium(Q.med, i);
+        if (ahead) load_ahead(i);
+    };
+    // the lane takes a packet (goes_on: from the last round, maybe in the
+    // middle of a visit) and asks for its random blocks
+    auto take = [&](const PacketRec *rec, bool goes_on) {
+        const int np = (int)rec_load(rec, p);
+        if (!ONE && np != prob) {
+            if (prob >= 0) {
+                L.visits = L.segments - L.scatters;
+                ledger_flush_lane(W.probs[prob], L);
+            }
+            L = LedgerRegs();
+            prob = np;
+            Q = walk_prob(W.probs[np]);
+            B = Q.H;
+        }
+        const int tx = p.ix / tw, tz = p.iz / th;
+        tx0 = tx * tw;
+        tz0 = tz * th;
+        p.ix -= tx0;
+        p.iz -= tz0;
+        tile = (uint32_t)(Q.tile_base + tz * Q.ntx + tx);
+        enter_tile();
+        k0 = p.k;
+        const uint32_t in_visit = goes_on && rec->tile != 0u ? 1u : 0u;
+        resume = in_visit ? gid : kNoSlot;
+        fl = kWait | in_visit;
+    };
+    // one segment
+    auto pass = [&](auto ahead_c, uint32_t u) {
+        constexpr bool kAhead = decltype(ahead_c)::value;
+        const float4 rnd = ring[p.k % kRing][lane];   // for a scatter at the segment's end
+        const uint32_t lp = (uint32_t)(__mul24(p.iz, tw) + p.ix);
+        const int oix = p.ix, oiz = p.iz;
+        float T = 0.f, dw = 0.f;
+        const float g = mm.w, sx = p.sx, sz = p.sz;   // direction of the segment, before any scatter
+        const int e = step(B, p, mm, T, dw);          // EV_ESCAPE: the packet leaves the tile
+        const bool at = e == EV_SCATTER;
+        // the medium of the pixel the next step starts in (padding, if outside
+        // the grid), on its way while the rest is computed
+        if constexpr (!kAhead)
+            if (!at) mm = load_medium(Q.med, pixel());
+        p.ur = rnd.x;
+        const bool killed = scatter_roulette(Q.H, p, at, L);
+        const bool vend = killed || !at;
+        s_ev[s_ev0 ^ u] = make_float4(T * Q.fx, sx, sz, __uint_as_float(lp | (vend ? kVisitEnd : 0u)));
+        ++n;
+        L.absorbed += (double)dw;
+        if (!vend) {
+            float nx_, nz_;
+            hg_rotate(g, rnd.z, rnd.y, p.sx, p.sz, nx_, nz_);
+            set_dir(p, nx_, nz_);
+            ++p.k;
+            p.tau = rnd.w;
+        }
+        fl = (vend ? 0u : 1u) | (e == EV_ESCAPE ? kLeft : 0u) | (killed ? kDead : 0u);
+        if constexpr (kAhead) {
+            // taken as late as can be: the loads have had a whole pass
+            const bool cx = p.ix != oix, cz = p.iz != oiz;
+            mm.x = cx ? mx.x : (cz ? mz.x : mm.x);
+            mm.y = cx ? mx.y : (cz ? mz.y : mm.y);
+            mm.z = cx ? mx.z : (cz ? mz.z : mm.z);
+            mm.w = cx ? mx.w : (cz ? mz.w : mm.w);
+            if (cx && cz) mm = load_medium(Q.med, pixel());   // a corner: rare
+            load_ahead(e == EV_ESCAPE ? 0 : pixel());
+        }
+    };
+
+    if (gid < n_state) take(W.state[par] + gid, true);
+    uint32_t post = 0;
+    for (;;) {
+        uint32_t fresh = post == 0u && fl >= kWait ? 1u : 0u;   // the packet is new to the second wave
+        // most times nothing but the passes needs looking after
+        if (post == 0u || __ballot((fl >= kLeft && fl < kPark) || fl >= kWait || (fl < kLeft && n >= lim))) {
+            if (fl & kLeft) {
+                const int gx = tx0 + p.ix, gz = tz0 + p.iz;
+                if ((unsigned)gx >= (unsigned)Q.H.nx || (unsigned)gz >= (unsigned)Q.H.nz) {
+                    L.escaped += p.w;
+                    fl = kDead;
+                }
+            }
+            // runs that ended: the packet left the tile or is gone, or the run is long
+            const bool close = n != run0 && ((fl & (kLeft | kDead)) != 0u || (fl == kMove && n - run0 >= kRunMax));
+            put_runs(close, kNoSlot);
+            if (close) {
+                n = (n + 3u) & ~3u;
+                run0 = n;
+                resume = kNoSlot;
+                if (fl & kDead) {
+                    L.scatters += p.k - k0;
+                    fl = kEmpty;
+                } else if (fl & kLeft) {
+                    const int ox = p.ix < 0 ? -1 : (p.ix >= tw ? 1 : 0), oz = p.iz < 0 ? -1 : (p.iz >= th ? 1 : 0);
+                    tile = (uint32_t)((int)tile + oz * Q.ntx + ox);
+                    tx0 += ox * tw;
+                    tz0 += oz * th;
+                    p.ix -= ox * tw;
+                    p.iz -= oz * th;
+                    enter_tile();
+                    fl = kMove;
+                }
+            }
+            const bool space = n + 4u <= cap;
+            if (fl >= kWait && !fresh) fl = kMove | (fl & 1u);   // the blocks asked for at the last post are there
+            if (fl < kLeft && !space) fl |= kPark;
+            // free lanes with space take the next packet
+            if (fl == kEmpty && !(more && space)) fl = kIdle;
+            const unsigned long long m = __ballot(fl == kEmpty);
+            if (m) {
+                const uint32_t c = (uint32_t)__popcll(m);
+                const uint32_t b = wave_claim(&C->part[part].taken, c);
+                const uint32_t p0 = part_begin(n_p, part), size = part_begin(n_p, part + 1) - p0;
+                const uint32_t i = b + rank_in(m);
+                if (fl == kEmpty && b < size && i < size) {
+                    const uint32_t idx = p0 + i, slot = idx < nc ? idx : W.pool_cap_c + (idx - nc);
+                    if (ptile[slot] != kInvalidTile) {
+                        take(pool + slot, false);
+                        fresh = 1u;
+                    }
+                }
+                if (b >= size || b + c >= size) {
+                    part = (part + 1) % kWalkParts;
+                    more = ++tries < kWalkParts;
+                }
+            }
+            lim = min(cap - 3u, run0 + kRunMax);
+        }
+        const uint32_t side = post++ & 1u;
+        s_k[side][lane] = fl < kLeft || fl >= kWait ? p.k : kNoSlot;
+        s_new[side][lane] = fresh;
+        if (fresh) {
+            s_pid[side][lane] = p.pid;
+            s_prob[side][lane] = (uint32_t)prob;
+        }
+        const bool stop = !__ballot(fl < kLeft || fl >= kWait || fl == kEmpty);
+        if (lane == 0) s_stop[side] = stop ? 1u : 0u;
+        __syncthreads();
+        if (stop) break;
+        const unsigned long long moved = __ballot(fl < kLeft);
+        const uint32_t n4 = n;   // a multiple of 4 in lanes that move
+        if (ahead) {
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u)
+                if (fl < kLeft) pass(std::true_type{}, u);
+        } else {
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u)
+                if (fl < kLeft) pass(std::false_type{}, u);
+        }
+        // the batch's events, four lanes to a lane's 64 bytes: written one by
+        // one, each event of 16 bytes is a request of its own to the L2
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+            if (((moved >> (16u * j)) & 0xFFFFull) == 0ull) continue;
+            const uint32_t src = 16u * j + ((uint32_t)lane >> 2), u = (uint32_t)lane & 3u;
+            const float4 v = s_ev[(4u * src + ((src >> 2) & 3u)) ^ u];
+            const uint32_t at = (blockIdx.x * 64u + src) * cap + __shfl(n4, (int)src) + u;
+            if ((moved >> src) & 1ull) W.ev[at] = v;
+        }
+    }
+    // packets alive go on in the next round
+    const bool going = (fl & kPark) != 0u;
+    const unsigned long long m = __ballot(going);
+    if (m) {
+        const uint32_t slot = wave_claim(&C->n_state(par ^ 1), (uint32_t)__popcll(m)) + rank_in(m);
+        if (going) {
+            L.scatters += p.k - k0;
+            const uint4 b = rng_block(Q.H, p.pid, p.k);   // the record holds the draws of its block
+            p.uh = u01(b.y);
+            p.ur = u01(b.z);
+            Packet q = p;
+            q.ix += tx0;
+            q.iz += tz0;
+            rec_store(W.state[par ^ 1] + slot, q, fl & 1u, (uint32_t)(ONE ? 0 : prob));
+        }
+        put_runs(going && n != run0, (fl & 1u) ? slot : kNoSlot);
+    }
+    for (uint32_t i = rused + lane; i < kRunSlice; i += 64)
+        if (rbase + i < W.run_cap) W.runs.ptile[0][rbase + i] = kInvalidTile;
+    L.visits = L.segments - L.scatters;
+    ledger_flush_lanes(W.probs, prob, L);
+}
+
+// Counts the round's runs by tile; the last workgroup scans the counts into
+// cursors and jobs and shares out the next round.
+__global__ void __launch_bounds__(kGenBlock) k_run_count(Walk W, int r) {
+    extern __shared__ uint32_t hist[];
+    WalkCtl *C = W.ctl;
+    const Gen &G = W.runs;
+    if ((uint32_t)r >= C->w_end) return;
+    const int par = r & 1;
+    const bool local = G.ntiles <= kHistTiles;
+    if (local)
+        for (int i = threadIdx.x; i < G.ntiles; i += kGenBlock) hist[i] = 0u;
+    __syncthreads();
+    count_slots(G, hist, local, G.ptile[0], min(C->n_run(par), W.run_cap));
+    if (!last_workgroup(&C->wg_done)) return;
+    uint32_t total = 0;
+    bool fits = true;
+    const uint32_t jobs = scan_tiles(G, hist, total, fits);
+    if (threadIdx.x == 0) {
+        C->n_jobs = jobs;
+        C->job_cursor = 0;
+        C->wg_done = 0;
+        C->n_state(par) = 0;     // taken by this round; the next one but one fills it
+        C->n_run(par ^ 1) = 0;
+        const uint32_t going = C->n_state(par ^ 1);
+        uint32_t left = 0;
+        for (uint32_t j = 0; j < kWalkParts; ++j) {
+            const uint32_t size = part_begin(C->n_p, j + 1) - part_begin(C->n_p, j);
+            left += size - min(size, C->part[j].taken);
+        }
+        C->left = left;
+        if (!going && !left) C->w_end = (uint32_t)r + 1u;
+        else walk_share(W, C, going, left);
+        if (!fits) atomicOr(const_cast<uint32_t *>(&W.gctl->overflow), 1u);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_run_sort(Walk W, int r) {
+    extern __shared__ uint32_t cnt[];
+    WalkCtl *C = W.ctl;
+    if ((uint32_t)r >= C->w_end) return;
+    sort_slots(W.runs, cnt, W.runs.ptile[0], min(C->n_run(r & 1), W.run_cap), 0u);
+}
+
+// The tally of a round.  A lane reads its run's events in chunks of four (64
+// bytes), the next chunk in flight while one is summed; the record of its next
+// run is loaded a chunk ahead and its slot claimed a chunk before that.
+template <int NH>
+__global__ void __launch_bounds__(tile_block(NH)) __attribute__((amdgpu_waves_per_eu(NH <= 16 ? 4 : 2)))
+k_tally(Walk W, int r) {
+    constexpr int K = 2 * NH + 1;
+    extern __shared__ unsigned long long fxt[];   // [tw*th][K] fixed-point sums
+    const Gen &G = W.runs;
+    const int ntp = G.tw * G.th;
+    uint32_t *sadds = reinterpret_cast<uint32_t *>(fxt + (size_t)ntp * K);   // fixed_add_raw adds per pixel
+    __shared__ uint32_t s_job[5];
+    __shared__ uint32_t s_next;
+    __shared__ float s_mag;
+    WalkCtl *C = W.ctl;
+    if ((uint32_t)r >= C->w_end) return;
+    const int par = r & 1;
+    const int lane = __lane_id();
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const uint32_t j = atomicAdd(&C->job_cursor, 1u);
+            const bool ok = j < C->n_jobs;
+            const uint4 jb = ok ? G.jobs[j] : make_uint4(0u, 0u, 0u, 0u);
+            s_job[0] = ok ? 1u : 0u;
+            s_job[1] = jb.x;
+            s_job[2] = jb.y;
+            s_job[3] = jb.z;
+            s_job[4] = jb.w;
+            s_next = 0;
+            s_mag = 0.f;
+        }
+        __syncthreads();
+        if (!s_job[0]) break;
+        const uint32_t tile = s_job[1], pos0 = s_job[2], cnt = s_job[3], prob = s_job[4];
+        const ProbDev &pd = W.probs[prob];
+        const float flush_at = pd.flush_at;
+        for (int i = threadIdx.x; i < ntp * K; i += blockDim.x) fxt[i] = 0ull;
+        for (int i = threadIdx.x; i < ntp; i += blockDim.x) sadds[i] = 0u;
+        __syncthreads();
+
+        float mag = 0.f;
+        float acc[K], keep = 0.f;
+#pragma unroll
+        for (int j = 0; j < K; ++j) acc[j] = 0.f;
+        float4 e0, e1, e2, e3;                     // chunk in flight
+        e0 = e1 = e2 = e3 = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t em = 0, eres = kNoSlot, esus = kNoSlot;   // its events; carry slots it starts from / ends in
+        const float4 *fp = nullptr;                // next chunk to fetch
+        uint32_t left = 0, fres = kNoSlot, fsus = kNoSlot;
+        uint4 rec = make_uint4(0u, 0u, 0u, 0u);
+        bool has_rec = false, more = true;
+        uint32_t slot = kNoSlot;
+        for (;;) {
+            const float4 c0 = e0, c1 = e1, c2 = e2, c3 = e3;
+            const uint32_t m = em, res = eres, sus = esus;
+            em = 0;
+            if (left == 0 && has_rec) {            // the next run
+                fp = W.ev + (size_t)rec.x * 4u;
+                left = rec.y;
+                fres = rec.z;
+                fsus = rec.w;
+                has_rec = false;
+            }
+            if (left) {
+                e0 = fp[0];
+                e1 = fp[1];
+                e2 = fp[2];
+                e3 = fp[3];
+                fp += 4;
+                em = min(left, 4u);
+                left -= em;
+                eres = fres;
+                esus = left ? kNoSlot : fsus;
+                fres = kNoSlot;
+            }
+            if (!has_rec && slot != kNoSlot) {
+                if (slot < W.run_cap) {            // always true; guards the load
+                    rec = *reinterpret_cast<const uint4 *>(W.run + slot);
+                    has_rec = true;
+                }
+                slot = kNoSlot;
+            }
+            if (more) {
+                const unsigned long long want = __ballot(slot == kNoSlot);
+                if (want) {
+                    const uint32_t nw = (uint32_t)__popcll(want);
+                    const int leader = __ffsll((long long)want) - 1;
+                    uint32_t base = 0;
+                    if (lane == leader) base = atomicAdd(&s_next, nw);
+                    base = __shfl(base, leader);
+                    if (base + nw >= cnt) more = false;
+                    if (slot == kNoSlot) {
+                        const uint32_t my = base + (uint32_t)__popcll(want & lt_mask);
+                        if (my < cnt) slot = G.sidx[pos0 + my];
+                    }
+                }
+            }
+            if (!__ballot(m != 0u)) {
+                if (!more && !__ballot(em != 0u || has_rec || slot != kNoSlot)) break;
+                continue;
+            }
+            if (res != kNoSlot && m) {             // rare: the first run of a packet that goes on
+                const float *q = W.carry[par] + (size_t)res * K;
+#pragma unroll
+                for (int j = 0; j < K; ++j) acc[j] = q[j];
+                keep = 1.f;
+                // waited for here: else every use of the sums below, in every
+                // pass, would wait for the chunk in flight
+                __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+            }
+            auto add = [&](const float4 &e) {
+                deposit_harmonics<NH>(e.x, e.y, e.z, keep, acc);
+                const uint32_t w = __float_as_uint(e.w);
+                const bool flush = (w & kVisitEnd) != 0u || fabsf(acc[0]) > flush_at;
+                if (flush) {
+                    const uint32_t lp = w & ~kVisitEnd;
+                    unsigned long long *t = fxt + __umul24(lp, (uint32_t)K);
+#pragma unroll
+                    for (int j = 0; j < K; ++j) fixed_add_raw(t + j, acc[j]);
+                    atomicAdd(sadds + lp, 1u);
+                    mag += fabsf(acc[0]);
+                }
+                keep = flush ? 0.f : 1.f;
+            };
+            if (m > 0u) add(c0);
+            if (m > 1u) add(c1);
+            if (m > 2u) add(c2);
+            if (m > 3u) add(c3);
+            if (sus != kNoSlot && m) {             // rare: the visit goes on in the next round
+                float *q = W.carry[par ^ 1] + (size_t)sus * K;
+#pragma unroll
+                for (int j = 0; j < K; ++j) q[j] = keep != 0.f ? acc[j] : 0.f;
+                keep = 0.f;
+            }
+        }
+        float wm = mag;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) wm += __shfl_xor(wm, o);
+        if (lane == 0) atomicAdd(&s_mag, wm);
+        __syncthreads();
+        if (threadIdx.x == 0 && !(s_mag < 0x1p62f)) atomicAdd(pd.ledc + 4, 1ull);   // see k_normalise
+        const int ntx = pd.ntx, local = (int)tile - pd.tile_base, nx = pd.nx, nz = pd.nz;
+        const int tx0 = (local % ntx) * G.tw, tz0 = (local / ntx) * G.th;
+        double *const t64 = pd.t64;
+        const double fx_inv = pd.fx_inv;   // read once: see k_transport_tile
+        for (int i = threadIdx.x; i < ntp * K; i += blockDim.x) {
+            const int lp = i / K, c = i - lp * K;
+            const double v = (double)fixed_value(fxt[i], sadds[lp]) * fx_inv;
+            const int gx = tx0 + lp % G.tw, gz = tz0 + lp / G.tw;
+            if (v != 0.0 && gx < nx && gz < nz) tally_add(t64 + (size_t)(gz * nx + gx) * K + c, v);
+        }
+        __syncthreads();
+    }
+}
+
 // ------------------------------------------------------------------ tail finisher
 // When few packets remain, the generations would be dominated by the
 // longest-lived packets.  The finisher moves each remaining packet to its end
@@ -1500,42 +2242,6 @@ __device__ __forceinline__ void finish_flush_stage(const float *stage, const uns
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Ledger of lanes that may hold different problems (prob < 0: nothing held):
-// the lanes of each problem in turn are summed over the wave and one lane
-// adds the sums to that problem's ledger.
-__device__ __forceinline__ void ledger_flush_lanes(const Gen &G, int prob, const LedgerRegs &L) {
-    const int lane = __lane_id();
-    int pend = prob;
-    for (;;) {
-        const unsigned long long m = __ballot(pend >= 0);
-        if (!m) break;
-        const int leader = __ffsll((long long)m) - 1;
-        const int p0 = __shfl(pend, leader);
-        const bool mine = pend == p0;
-        double v[5] = {L.launched, L.absorbed, L.escaped, L.gain, L.loss};
-        unsigned long long c[4] = {L.packets, L.segments, L.visits, L.scatters};
-#pragma unroll
-        for (int i = 0; i < 5; ++i) v[i] = mine ? v[i] : 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = mine ? c[i] : 0ull;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-            for (int i = 0; i < 5; ++i) v[i] += __shfl_xor(v[i], off);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) c[i] += __shfl_xor(c[i], off);
-        }
-        if (lane == leader) {
-            const ProbDev &S = G.probs[p0];
-            for (int i = 0; i < 5; ++i)
-                if (v[i] != 0.0) atomicAdd(S.led + i, v[i]);
-            for (int i = 0; i < 4; ++i)
-                if (c[i]) atomicAdd(S.ledc + i, c[i]);
-        }
-        if (mine) pend = -1;
-    }
-}
-
 // Few packets per lane and long histories make this kernel latency-bound, so
 // its loop keeps global memory off the dependent chain where it can: the
 // medium of the pixel a packet enters is loaded one iteration ahead of its
@@ -1544,7 +2250,7 @@ __device__ __forceinline__ void ledger_flush_lanes(const Gen &G, int prob, const
 // buffer, not once per visit).  Lanes branch (a lone packet in a wave pays
 // only for what it does).
 template <int NH>
-__global__ void __launch_bounds__(kBlockFinish) k_finish(Gen G, int g_last, int prob_only) {
+__global__ void __launch_bounds__(kBlockFinish) k_finish(Gen G, Walk W, int g_last, int rounds, int prob_only) {
     constexpr int K = 2 * NH + 1;
     extern __shared__ float stage_all[];
     GenCtl *C = G.ctl;
@@ -1559,9 +2265,16 @@ __global__ void __launch_bounds__(kBlockFinish) k_finish(Gen G, int g_last, int 
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
     // the work: records of a pool (prob_only < 0) or the unlaunched packets of one problem
     uint32_t pool = 0, nc = 0, nl = 0;
+    uint32_t n_state = 0;   // packets the rounds left on their way
     uint64_t n_work = 0, pid_first = 0;
     unsigned long long *cursor = G.fin_cur + (prob_only < 0 ? 0 : 1 + prob_only);
-    if (prob_only < 0) {
+    if (prob_only < 0 && W.ctl) {
+        if (W.ctl->w_end <= (uint32_t)rounds) return;   // the rounds moved everything
+        pool = W.ctl->pool;
+        nc = W.ctl->nc;
+        n_state = W.ctl->n_state(rounds & 1);
+        n_work = (uint64_t)n_state + W.ctl->left;
+    } else if (prob_only < 0) {
         if (C->done) {
             pool = C->fin_pool;
             nc = C->fin_nc;
@@ -1610,8 +2323,28 @@ __global__ void __launch_bounds__(kBlockFinish) k_finish(Gen G, int g_last, int 
                     Packet q;
                     q.alive = false;
                     if (my < n_work) {
-                        if (prob_only < 0) {
-                            const uint32_t slot = my < nc ? (uint32_t)my : G.cap_c + (uint32_t)(my - nc);
+                        if (prob_only < 0 && my < n_state) {
+                            const PacketRec *rec = W.state[rounds & 1] + my;
+                            np_ = (int)rec_load(rec, q);
+                            if (rec->tile != 0u) {   // its visit is open: the sums so far
+                                const float *sums = W.carry[rounds & 1] + (size_t)my * K;
+                                for (int j = 0; j < K; ++j) acc[j] = sums[j];
+                                keep = 1.f;
+                            }
+                        } else if (prob_only < 0) {
+                            uint64_t i = my - n_state;
+                            if (W.ctl) {   // of the slots that the rounds left in each part
+                                for (uint32_t j = 0; j < kWalkParts; ++j) {
+                                    const uint32_t b = part_begin(W.ctl->n_p, j), size = part_begin(W.ctl->n_p, j + 1) - b;
+                                    const uint32_t taken = min(size, W.ctl->part[j].taken);
+                                    if (i < size - taken) {
+                                        i += b + taken;
+                                        break;
+                                    }
+                                    i -= size - taken;
+                                }
+                            }
+                            const uint32_t slot = i < nc ? (uint32_t)i : G.cap_c + (uint32_t)(i - nc);
                             if (G.ptile[pool][slot] != kInvalidTile) np_ = (int)rec_load(G.pool[pool] + slot, q);
                         } else {
                             np_ = prob_only;
@@ -1620,13 +2353,7 @@ __global__ void __launch_bounds__(kBlockFinish) k_finish(Gen G, int g_last, int 
                     if (np_ >= 0) {
                         if (np_ != lprob) {   // a lane changes problem: its ledger goes out first (rare)
                             if (lprob >= 0) {
-                                const ProbDev &O = G.probs[lprob];
-                                double v[5] = {L.launched, L.absorbed, L.escaped, L.gain, L.loss};
-                                unsigned long long c[4] = {L.packets, L.segments, L.visits, L.scatters};
-                                for (int i = 0; i < 5; ++i)
-                                    if (v[i] != 0.0) atomicAdd(O.led + i, v[i]);
-                                for (int i = 0; i < 4; ++i)
-                                    if (c[i]) atomicAdd(O.ledc + i, c[i]);
+                                ledger_flush_lane(G.probs[lprob], L);
                                 L = LedgerRegs();
                             }
                             lprob = np_;
@@ -1696,7 +2423,7 @@ __global__ void __launch_bounds__(kBlockFinish) k_finish(Gen G, int g_last, int 
         if (ev != EV_NONE) keep = flush ? 0.f : 1.f;
     }
     if (used) finish_flush_stage(stage, stage_dst, stage_scale, used, K);
-    ledger_flush_lanes(G, lprob, L);
+    ledger_flush_lanes(G.probs, lprob, L);
 }
 
 // ------------------------------------------------------------------ discrete-ordinates tally
@@ -1942,7 +2669,8 @@ __global__ void k_normalise(const ProbDev *pd, int N, const GenCtl *ctl, double 
     }
 }
 
-__global__ void k_ledger_out(const ProbDev *pd, const GenCtl *ctl, uint32_t generations, mc_ledger *out) {
+__global__ void k_ledger_out(const ProbDev *pd, const GenCtl *ctl, const WalkCtl *rounds, uint32_t generations,
+                             mc_ledger *out) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const double *led = pd->led;
     const unsigned long long *ledc = pd->ledc;
@@ -1956,7 +2684,7 @@ __global__ void k_ledger_out(const ProbDev *pd, const GenCtl *ctl, uint32_t gene
     out->segments = ledc[1];
     out->visits = ledc[2];
     out->scatters = ledc[3];
-    out->generations = ctl ? (ctl->done ? ctl->gen_done : generations) : 0;
+    out->generations = rounds ? min(rounds->w_end, generations) : (ctl ? (ctl->done ? ctl->gen_done : generations) : 0);
 }
 
 // Residual (Sec. 2, Sec. 6) with a deterministic single-block reduction of eps.
@@ -2053,16 +2781,18 @@ __global__ void k_philox_fill(uint64_t seed, uint32_t tag, uint64_t pid0, uint64
 using GridFn = void (*)(GridArgs);
 using TileFn = void (*)(Gen, int);
 using TraceFn = void (*)(const ProbDev *, const uint64_t *, int, mc_event *, size_t, unsigned long long *);
-using FinishFn = void (*)(Gen, int, int);
+using FinishFn = void (*)(Gen, Walk, int, int, int);
+using TallyFn = void (*)(Walk, int);
 
 template <int NH>
 struct Table {
-    static void fill(GridFn *grid, TileFn *tile, TraceFn *tr, FinishFn *fin) {
+    static void fill(GridFn *grid, TileFn *tile, TraceFn *tr, FinishFn *fin, TallyFn *tal) {
         grid[NH] = k_transport_grid<NH>;
         tile[NH] = k_transport_tile<NH>;
         tr[NH] = k_trace<NH>;
         fin[NH] = k_finish<NH>;
-        if constexpr (NH > 0) Table<NH - 1>::fill(grid, tile, tr, fin);
+        tal[NH] = k_tally<NH>;
+        if constexpr (NH > 0) Table<NH - 1>::fill(grid, tile, tr, fin, tal);
     }
 };
 
@@ -2072,7 +2802,8 @@ struct Kernels {
     TileFn tile[MC_NHARM_MAX + 1];
     TraceFn tr[MC_NHARM_MAX + 1];
     FinishFn fin[MC_NHARM_MAX + 1];
-    Kernels() { Table<MC_NHARM_MAX>::fill(grid, tile, tr, fin); }
+    TallyFn tal[MC_NHARM_MAX + 1];
+    Kernels() { Table<MC_NHARM_MAX>::fill(grid, tile, tr, fin, tal); }
 };
 
 const Kernels &kernels() {
@@ -2118,11 +2849,23 @@ constexpr int kTileSlotsMax = kTileWavesMax / (tile_block(MC_NHARM_MAX) / 64);  
 constexpr uint32_t kJobMin = 1024;             // smallest job of a generation with few packets (see gen_scan)
 constexpr uint32_t kQuietPercent = 50;         // see the quiet rule of k_transport_tile
 
+// Walk and tally (see k_walk).
+// Runs up to this many packets (those of volume sources count twice) walk from
+// their launch: on 256^2 discs 1e6 forward packets take 24 ms against 29 ms in
+// generations, 3e6 50.6 against 51.9, 1e6 adjoint packets 57.7 against 61.5,
+// 2e6 103 against 95.
+constexpr uint64_t kDirectMax = 3ull << 20;
+constexpr uint64_t kWalkEvents = 1ull << 27;         // events a round may write
+constexpr uint64_t kWalkEventsPerLane = 1ull << 14;  // or this many per lane if that is less
+constexpr uint32_t kWalkRounds = 4;                  // rounds enqueued: these, and as many as events are expected
+constexpr uint64_t kWalkRoundEvents = 6144;          // per packet
+constexpr uint32_t kRunJobMin = 256;                  // smallest tally job of a round with few runs
+
 // The tuning a call runs with: the caller's fields, defaults where zero.
 struct TileTuning {
     uint64_t live = kLiveMax;
     uint32_t job = kJobSize, maxvis = kMaxVisitsPerStay, tailvis = kTailVisits;
-    uint64_t finish = 0;   // 0: min(2^17, live / 128)
+    uint64_t finish = 0;   // 0: min(2^16, live / 128)
     int tile = 0;          // 0: largest square tile whose tally fits one workgroup's LDS
     uint64_t grid_max = kGridMaxPackets;
     double flush_track = kFlushTrackMax;
@@ -2130,6 +2873,7 @@ struct TileTuning {
     uint32_t job_min = kJobMin;
     uint32_t quiet = kQuietPercent;
     uint32_t slice = kSlice;   // not a caller knob: the no-alloc entry point narrows it to save scratch
+    uint64_t ev_max = kWalkEvents;   // nor this: events a round may write (0: no rounds)
 };
 
 bool tuning_from(const mc_options *o, TileTuning &v) {
@@ -2255,6 +2999,12 @@ struct BatchLayout {
     size_t tile_lds = 0;
     uint64_t live = 0, cap_c = 0, cap_l = 0, max_jobs = 0, total_packets = 0;
     uint32_t job = 0;   // packets per job: the tuning's, halved for small pools
+    bool direct = false;        // every packet walks from its launch: no generations
+    uint64_t finish = 0;        // finisher threshold
+    uint32_t rounds = 0;        // walk-and-tally rounds enqueued; 0: the finisher alone
+    uint64_t lanes = 0, ev_cap = 0, run_cap = 0, run_jobs = 0;
+    size_t wctl = 0, rcount = 0, rcursor = 0, rjobs = 0, ev = 0, run = 0, rtile = 0, rsidx = 0, state[2] = {0, 0},
+           carry[2] = {0, 0};
     std::vector<size_t> med, cdf, t64, led, ledc;
     std::vector<int> ntx, ntz, tile_base;
     size_t probs = 0, tile_prob = 0, ctl = 0, launched = 0, fin_cur = 0, tcount = 0, tcursor = 0, jobs = 0,
@@ -2276,8 +3026,11 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
     size_t off = 0;
     for (int i = 0; i < n; ++i) {
         const size_t npix = (size_t)pb[i].m->nx * pb[i].m->nz;
-        B.med.push_back(off);
-        off = align_up(off + npix * sizeof(float4));
+        // a row and a pixel of padding on either side: a walking packet's
+        // prefetch of its neighbours needs no bounds check (k_walk)
+        const size_t pad = (size_t)pb[i].m->nx + 1;
+        B.med.push_back(off + pad * sizeof(float4));
+        off = align_up(off + (npix + 2 * pad) * sizeof(float4));
         B.cdf.push_back(off);
         if (pb[i].src[0].kind == MC_SRC_MAP) off = align_up(off + (npix + 1) * sizeof(double));   // CDF, max |q|
         B.t64.push_back(off);
@@ -2293,10 +3046,21 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
         B.total_packets += pb[i].run->n_packets;
     }
     B.live = std::min<uint64_t>(B.total_packets, B.tt.live);
+    B.finish = B.tt.finish ? B.tt.finish : std::min<uint64_t>(kFinishMax, B.tt.live / 128);
+    const bool walk = B.tt.ev_max != 0;
+    // the rounds take over earlier than the finisher alone would: measured on
+    // 128^2 to 256^2 discs at 1e5 to 4e6 packets, 2^17 left is the best
+    // hand-over for them (10-25% faster than 2^16 and 2^14)
+    if (walk) B.finish = std::min<uint64_t>(2 * B.finish, kLiveMax);
+    uint64_t weight = 0;   // packets, those of volume sources twice: their paths are about that much longer
+    for (int i = 0; i < n; ++i)
+        weight += pb[i].run->n_packets * (pb[i].src[0].kind == MC_SRC_MAP || pb[i].src[0].kind == MC_SRC_POINT ? 2 : 1);
+    B.direct = walk && n <= kMaxAlloc && weight <= kDirectMax && B.total_packets <= B.tt.live;
     // carried region: every packet a generation moves may leave, plus the
     // padding of the wave slices still open when it ends; launch region: at
     // most `live` new packets per generation
-    B.cap_c = B.live + (uint64_t)B.tt.slice * kTileWavesMax + 64ull * 64;
+    // (a direct run has only launches)
+    B.cap_c = B.direct ? 64 : B.live + (uint64_t)B.tt.slice * kTileWavesMax + 64ull * 64;
     B.cap_l = B.live;
     // a pool below 2^23 live packets spreads over too few jobs of the tuned
     // size to fill the device: half-size jobs (measured on 1e6- and 4e6-packet
@@ -2311,6 +3075,16 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
         B.tt.max_gen = (uint32_t)std::min<uint64_t>(
             65536, kGenBase + kGenPerTile * side + kGenPerPool * ((B.total_packets + B.live - 1) / B.live));
     }
+    if (walk) {
+        B.lanes = (std::min<uint64_t>(B.direct ? B.total_packets : std::min(B.finish, B.live), kWalkLanes) + 63) & ~63ull;
+        B.ev_cap = std::min<uint64_t>(B.tt.ev_max, B.lanes * kWalkEventsPerLane);
+        // a run takes four events or more; up to 63 of a slice's slots stay empty
+        B.run_cap = B.ev_cap / 4 * kRunSlice / (kRunSlice - 63) + kRunSlice * (B.lanes / 64 + 1);
+        B.run_jobs = (uint64_t)B.ntiles + std::max<uint64_t>(B.run_cap / kJobSize, 2ull * kTileSlotsMax) + 2;
+        // every round but the last ones fills the buffer
+        B.rounds = kWalkRounds + (uint32_t)((B.direct ? B.total_packets : B.finish) * kWalkRoundEvents / B.ev_cap);
+        if (B.direct && tt.max_gen) B.rounds = tt.max_gen;
+    }
     B.probs = off;
     off = align_up(off + (size_t)n * sizeof(ProbDev));
     B.tile_prob = off;
@@ -2324,17 +3098,46 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
     off = align_up(off + (size_t)(n + 1) * sizeof(unsigned long long));
     B.tcount = off;
     off = align_up(off + (size_t)B.ntiles * sizeof(uint32_t));
+    B.wctl = off;
+    if (walk) off = align_up(off + sizeof(WalkCtl));
+    B.rcount = off;
+    if (walk) off = align_up(off + (size_t)B.ntiles * sizeof(uint32_t));
     B.tcursor = off;
     off = align_up(off + (size_t)B.ntiles * kCursorStride * sizeof(uint32_t));
     B.jobs = off;
     off = align_up(off + B.max_jobs * sizeof(uint4));
     B.sidx = off;
-    off = align_up(off + B.live * sizeof(uint32_t));
+    if (!B.direct) off = align_up(off + B.live * sizeof(uint32_t));
     for (int p = 0; p < 2; ++p) {
+        if (p && B.direct) {   // never written
+            B.pool[1] = B.pool[0];
+            B.ptile[1] = B.ptile[0];
+            break;
+        }
         B.pool[p] = off;
         off = align_up(off + (B.cap_c + B.cap_l) * sizeof(PacketRec));
         B.ptile[p] = off;
         off = align_up(off + (B.cap_c + B.cap_l) * sizeof(uint32_t));
+    }
+    if (walk) {
+        B.rcursor = off;
+        off = align_up(off + (size_t)B.ntiles * kCursorStride * sizeof(uint32_t));
+        B.rjobs = off;
+        off = align_up(off + B.run_jobs * sizeof(uint4));
+        B.ev = off;
+        off = align_up(off + B.ev_cap * sizeof(float4));
+        B.run = off;
+        off = align_up(off + B.run_cap * sizeof(RunRec));
+        B.rtile = off;
+        off = align_up(off + B.run_cap * sizeof(uint32_t));
+        B.rsidx = off;
+        off = align_up(off + B.run_cap * sizeof(uint32_t));
+        for (int p = 0; p < 2; ++p) {
+            B.state[p] = off;
+            off = align_up(off + B.lanes * sizeof(PacketRec));
+            B.carry[p] = off;
+            off = align_up(off + B.lanes * B.K * sizeof(float));
+        }
     }
     B.total = off;
     return B;
@@ -2518,6 +3321,36 @@ mc_status run_grid(const ProbDev *pd, const Layout &L, const mc_run *run, mc_tim
     return MC_OK;
 }
 
+// Enqueues the rounds of walk and tally.
+mc_status enqueue_rounds(const Walk &W, const BatchLayout &B, int N, int n_gen, mc_timer *timer, unsigned cgrid,
+                         unsigned sgrid, size_t count_lds, size_t scatter_lds, hipStream_t s) {
+    hipLaunchKernelGGL(k_walk_init, dim3(1), dim3(1), 0, s, W, n_gen);
+    const TallyFn fn = kernels().tal[N];
+    const size_t lds = (size_t)B.t * B.t * (B.K * sizeof(double) + sizeof(uint32_t));
+    mc_status st;
+    if ((st = set_lds_limit(reinterpret_cast<const void *>(fn), lds)) != MC_OK ||
+        (st = set_lds_limit(reinterpret_cast<const void *>(k_run_count), count_lds)) != MC_OK ||
+        (st = set_lds_limit(reinterpret_cast<const void *>(k_run_sort), scatter_lds)) != MC_OK)
+        return st;
+    for (uint32_t r = 0; r < B.rounds; ++r) {
+        LaunchTimer tw(timer);
+        if ((st = tw.begin(s)) != MC_OK) return st;
+        if (W.runs.nprob == 1)
+            hipLaunchKernelGGL(k_walk<true>, dim3((unsigned)(B.lanes / 64)), dim3(128), 0, s, W, (int)r);
+        else
+            hipLaunchKernelGGL(k_walk<false>, dim3((unsigned)(B.lanes / 64)), dim3(128), 0, s, W, (int)r);
+        if ((st = tw.end(s)) != MC_OK) return st;
+        hipLaunchKernelGGL(k_run_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, W, (int)r);
+        hipLaunchKernelGGL(k_run_sort, dim3(sgrid), dim3(256), scatter_lds, s, W, (int)r);
+        LaunchTimer tt(timer);
+        if ((st = tt.begin(s)) != MC_OK) return st;
+        hipLaunchKernelGGL(fn, dim3(W.runs.slots), dim3(tile_block(N)), lds, s, W, (int)r);
+        if ((st = tt.end(s)) != MC_OK) return st;
+        if (hipGetLastError() != hipSuccess) return MC_ERR_DEVICE;
+    }
+    return MC_OK;
+}
+
 // Tiled mode: every problem of the batch in one packet pool.  The host
 // enqueues the set-up, max_generations generations (each: launch and count,
 // sort, transport -- steered by the device control block, see GenCtl), the
@@ -2573,7 +3406,7 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     G.quiet_pct = B.tt.quiet;
     G.max_visits = B.tt.maxvis;
     G.tail_visits = B.tt.tailvis;
-    G.finish_at = (uint32_t)(B.tt.finish ? B.tt.finish : std::min<uint64_t>(kFinishMax, B.tt.live / 128));
+    G.finish_at = (uint32_t)(B.direct ? B.live : B.finish);
     G.slice = B.tt.slice;
     G.probs = probs_d;
     G.tile_prob = tile_prob;
@@ -2605,7 +3438,10 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     const size_t scatter_lds = local_hist ? sizeof(uint32_t) * B.ntiles : 0;
     if ((st = set_lds_limit(reinterpret_cast<const void *>(k_gen_count), count_lds)) != MC_OK) return st;
     if ((st = set_lds_limit(reinterpret_cast<const void *>(k_gen_scatter), scatter_lds)) != MC_OK) return st;
-    for (uint32_t g = 0; g < B.tt.max_gen; ++g) {
+    const uint32_t n_gen = B.direct ? 0u : B.tt.max_gen;
+    // a direct run's only generation launches every packet and finds the threshold met
+    if (B.direct) hipLaunchKernelGGL(k_gen_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, G, 0);
+    for (uint32_t g = 0; g < n_gen; ++g) {
         hipLaunchKernelGGL(k_gen_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, G, (int)g);
         hipLaunchKernelGGL(k_gen_scatter, dim3(sgrid), dim3(256), scatter_lds, s, G, (int)g);
         LaunchTimer tm(timer);
@@ -2614,6 +3450,37 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
         if ((st = tm.end(s)) != MC_OK) return st;
         if (hipGetLastError() != hipSuccess) return MC_ERR_DEVICE;
     }
+    Walk W{};
+    if (B.rounds) {
+        W.runs = G;
+        W.runs.live = (uint32_t)B.run_cap;
+        W.runs.cap_c = (uint32_t)B.run_cap;
+        W.runs.cap_l = 0;
+        W.runs.job_size = kJobSize;
+        W.runs.job_min = kRunJobMin;
+        W.runs.ptile[0] = W.runs.ptile[1] = reinterpret_cast<uint32_t *>(base + B.rtile);
+        W.runs.sidx = reinterpret_cast<uint32_t *>(base + B.rsidx);
+        W.runs.tile_count = reinterpret_cast<uint32_t *>(base + B.rcount);
+        W.runs.tile_cursor = reinterpret_cast<uint32_t *>(base + B.rcursor);
+        W.runs.jobs = reinterpret_cast<uint4 *>(base + B.rjobs);
+        W.runs.max_jobs = (uint32_t)B.run_jobs;
+        W.probs = probs_d;
+        W.gctl = ctl;
+        for (int p = 0; p < 2; ++p) {
+            W.pool[p] = G.pool[p];
+            W.ptile[p] = G.ptile[p];
+            W.state[p] = reinterpret_cast<PacketRec *>(base + B.state[p]);
+            W.carry[p] = reinterpret_cast<float *>(base + B.carry[p]);
+        }
+        W.pool_cap_c = G.cap_c;
+        W.ev = reinterpret_cast<float4 *>(base + B.ev);
+        W.run = reinterpret_cast<RunRec *>(base + B.run);
+        W.lanes_max = (uint32_t)B.lanes;
+        W.run_cap = (uint32_t)B.run_cap;
+        W.ev_cap = B.ev_cap;
+        W.ctl = reinterpret_cast<WalkCtl *>(base + B.wctl);
+        if ((st = enqueue_rounds(W, B, N, (int)n_gen, timer, cgrid, sgrid, count_lds, scatter_lds, s)) != MC_OK) return st;
+    }
     // the finisher: the records left, then any packets the generations did not launch
     const FinishFn ff = kernels().fin[N];
     const size_t flds = (size_t)kBlockFinish * (2 * N + 1) * sizeof(float) +
@@ -2621,16 +3488,16 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     if ((st = set_lds_limit(reinterpret_cast<const void *>(ff), flds)) != MC_OK) return st;
     const int focc = occupancy_blocks(reinterpret_cast<const void *>(ff), kBlockFinish, flds);
     const unsigned fgrid = (unsigned)std::max<uint64_t>(
-        1, std::min<uint64_t>((G.finish_at + kBlockFinish - 1) / kBlockFinish + 1, (uint64_t)cus * focc));
+        1, std::min<uint64_t>(((uint64_t)G.finish_at + kBlockFinish - 1) / kBlockFinish + 1, (uint64_t)cus * focc));
     {
         LaunchTimer tf(timer);
         if ((st = tf.begin(s)) != MC_OK) return st;
-        hipLaunchKernelGGL(ff, dim3(fgrid), dim3(kBlockFinish), flds, s, G, (int)B.tt.max_gen, -1);
+        hipLaunchKernelGGL(ff, dim3(fgrid), dim3(kBlockFinish), flds, s, G, W, (int)n_gen, (int)B.rounds, -1);
         if ((st = tf.end(s)) != MC_OK) return st;
     }
     const unsigned fgrid_all = (unsigned)std::max(1, cus * focc);
-    for (int i = 0; i < n; ++i)
-        hipLaunchKernelGGL(ff, dim3(fgrid_all), dim3(kBlockFinish), flds, s, G, (int)B.tt.max_gen, i);
+    for (int i = 0; i < n && !B.direct; ++i)
+        hipLaunchKernelGGL(ff, dim3(fgrid_all), dim3(kBlockFinish), flds, s, G, W, (int)n_gen, (int)B.rounds, i);
     // normalisation and ledgers
     for (int i = 0; i < n; ++i) {
         const int npix = pb[i].m->nx * pb[i].m->nz;
@@ -2638,7 +3505,7 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
                            (const GenCtl *)ctl, pb[i].coeffs);
         if (pb[i].ledger)
             hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)(probs_d + i), (const GenCtl *)ctl,
-                               B.tt.max_gen, pb[i].ledger);
+                               (const WalkCtl *)(B.direct ? W.ctl : nullptr), B.direct ? B.rounds : n_gen, pb[i].ledger);
     }
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
@@ -2675,7 +3542,8 @@ mc_status run_mc(const mc_medium *m, const mc_source *src, int n_src, const mc_r
     hipLaunchKernelGGL(k_normalise, dim3((npix + 255) / 256), dim3(256), 0, s, (const ProbDev *)pd, N,
                        (const GenCtl *)nullptr, coeffs);
     if (ledger)
-        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, (const GenCtl *)nullptr, 0u, ledger);
+        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, (const GenCtl *)nullptr,
+                           (const WalkCtl *)nullptr, 0u, ledger);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 
@@ -2744,7 +3612,8 @@ mc_status run_binned(const mc_medium *m, const mc_source *src, int n_src, const 
     hipLaunchKernelGGL(k_binned_normalise, dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, s, (const ProbDev *)pd,
                        n_bins, 2.0 * M_PI / n_bins, (const double *)raw, out);
     if (ledger)
-        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, (const GenCtl *)nullptr, 0u, ledger);
+        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, (const GenCtl *)nullptr,
+                           (const WalkCtl *)nullptr, 0u, ledger);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 
@@ -2787,6 +3656,7 @@ void *scratch_ptr() {
 bool noalloc_tuning(const mc_medium *m, const mc_source *src, int n_src, const mc_run *run, int adjoint,
                     const mc_options *opts, TileTuning &tt) {
     tt.slice = kScratchSlice;
+    tt.ev_max = 0;
     if (!is_tiled(m, run, tt)) return layout(m, src, run).total <= kScratchBytes;
     const BatchProblem one{m, src, n_src, run, adjoint, nullptr, nullptr};
     auto fits = [&](uint64_t live) {
