@@ -462,7 +462,7 @@ def batch_workload(args) -> dict:
 def pencil32(args) -> dict:
     """Forward MC on the 32x32 pencil-beam medium (0.5 mm pixels, mua 0.05,
     mus 5, g 0.8) at args.packets packets, N = 8 and N = 16 (at 1e8 packets
-    both take the tiled transport; the whole-grid kernel serves small runs)."""
+    both take the tiled transport; small runs walk from their launch)."""
     import torch
     import phantoms as P
     from paper_1608_05238_amd import rmc
@@ -478,9 +478,8 @@ def pencil32(args) -> dict:
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
         L = rmc.ledger_dict(led)
-        whole = 32 * 32 * (2 * N + 1) * 8 <= 144 * 1024 and n <= rmc.default_tuning()["grid_max_packets"]
         res[f"N{N}"] = {"packets_per_s": n / dt, "ms": dt * 1e3, "visits_per_packet": L["visits"] / n,
-                        "mode": "whole-grid LDS tally" if whole else "tiled"}
+                        "mode": "walk and tally" if n <= 3 << 20 else "tiled"}
         log(f"pencil32 N={N}: {n / dt:.3e} packets/s")
     out = {"metric": "packets/s fwd MC, 32x32 pencil beam", "value": res["N8"]["packets_per_s"],
            "unit": "packets/s", "higher_is_better": True, "n_gpus": 1, "dtype": "f32", "data": "synthetic",

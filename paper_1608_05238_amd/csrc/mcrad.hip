@@ -46,7 +46,6 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
-#include <type_traits>
 #include <vector>
 
 #include "mcrad.h"
@@ -84,7 +83,7 @@ struct SrcDev {
 };
 
 // One problem (a forward or adjoint run) in device memory.  The host fills
-// what it knows and hands the struct to k_prob_setup by value; that kernel
+// what it knows and hands the struct to k_setup by value; that kernel
 // adds what depends on device data (the sum and maximum of a MAP source, the
 // fixed-point scale, the normalisation) and stores it.  Every transport
 // kernel reads its packets' problem from here.
@@ -802,6 +801,7 @@ struct Gen {
     uint32_t job_size, max_visits, tail_visits, finish_at;
     uint32_t job_min;             // smallest job a generation with few packets splits its tiles into
     uint32_t slots;               // workgroups of the tile kernel
+    uint32_t direct;              // the packets walk from their launch: no records are counted or sorted
     uint32_t quiet_pct;           // a job turns quiet when this percent of its lanes' worth of stays is left
     uint32_t slice;               // slots a wave reserves at a time in a carried region (64 .. 256)
     const ProbDev *probs;
@@ -820,6 +820,7 @@ struct Gen {
 
 // The total of packets to launch: problems whose source has no power (or is
 // unusable) launch none, which only the device descriptors know.
+// (A single problem's is read from its descriptor, see gen_scan.)
 __global__ void k_ctl_init(Gen G) {
     uint64_t t = 0;
     for (int p = 0; p < G.nprob; ++p) t += G.probs[p].todo;
@@ -930,10 +931,13 @@ constexpr int kCountPer = 8;       // carried records per thread and pass of the
 
 // Counts one record of tile t (LDS histogram, or the global count directly).
 __device__ __forceinline__ void count_tile(const Gen &G, uint32_t *hist, bool local, uint32_t t, bool valid) {
-    if (local) {
+    // with few tiles, lane by lane the adds to one counter would queue up:
+    // one per tile and wave, as for the global counts
+    if (local && G.ntiles > 8) {
         if (valid) atomicAdd(hist + t, 1u);
         return;
     }
+    uint32_t *count = local ? hist : G.tile_count;
     const int lane = __lane_id();
     bool pend = valid;
     for (;;) {
@@ -942,7 +946,7 @@ __device__ __forceinline__ void count_tile(const Gen &G, uint32_t *hist, bool lo
         const int leader = __ffsll((long long)m) - 1;
         const uint32_t t0 = __shfl(t, leader);
         const unsigned long long same = __ballot(pend && t == t0);
-        if (lane == leader) atomicAdd(G.tile_count + t0, (uint32_t)__popcll(same));
+        if (lane == leader) atomicAdd(count + t0, (uint32_t)__popcll(same));
         if (pend && t == t0) pend = false;
     }
 }
@@ -1028,12 +1032,36 @@ __device__ uint32_t scan_tiles(const Gen &G, uint32_t *buf, uint32_t &total, boo
     const uint32_t job_incl = block_scan(njob, buf, total_jobs);
     fits = total <= G.live && total_jobs <= G.max_jobs;   // hold by construction
     uint32_t roff = rec_incl - nrec, joff = job_incl - njob;
+    if (G.ntiles <= kGenBlock) {   // one tile a thread: the jobs are written by all (few tiles have many each)
+        uint32_t *first_job = buf + kGenBlock, *first_rec = buf + 2 * kGenBlock, *count = buf + 3 * kGenBlock;
+        const uint32_t c = t < G.ntiles ? G.tile_count[t] : 0u;
+        first_job[t] = joff;
+        first_rec[t] = roff;
+        count[t] = c;
+        if (t < G.ntiles) {
+            G.tile_cursor[(size_t)t * kCursorStride] = roff;
+            G.tile_count[t] = 0;
+        }
+        __syncthreads();
+        for (uint32_t j = t; fits && j < total_jobs; j += kGenBlock) {
+            int lo = 0, hi = kGenBlock - 1;   // the last tile whose first job is at most j
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (first_job[mid] <= j) lo = mid; else hi = mid - 1;
+            }
+            while (count[lo] == 0u) --lo;     // threads past the last tile, tiles without records
+            const uint32_t s0 = (j - first_job[lo]) * js;
+            G.jobs[j] = make_uint4((uint32_t)lo, first_rec[lo] + s0, min(js, count[lo] - s0), G.tile_prob[lo]);
+        }
+        return fits ? total_jobs : 0u;
+    }
     for (int i = a; i < b; ++i) {
         const uint32_t c = G.tile_count[i];
+        const uint32_t prob = G.tile_prob[i];   // once: a reload after each store would wait for it
         G.tile_cursor[(size_t)i * kCursorStride] = roff;
         if (fits)
             for (uint32_t s0 = 0; s0 < c; s0 += js)
-                G.jobs[joff++] = make_uint4((uint32_t)i, roff + s0, min(js, c - s0), G.tile_prob[i]);
+                G.jobs[joff++] = make_uint4((uint32_t)i, roff + s0, min(js, c - s0), prob);
         roff += c;
         G.tile_count[i] = 0;
     }
@@ -1066,7 +1094,7 @@ __device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint3
         C->job_cursor = 0;
         if (!fits) C->overflow = 1u;
         // the packets left fit the finisher: this generation moves nothing
-        if (lt >= C->todo_total && total <= G.finish_at) {
+        if (lt >= (G.nprob == 1 ? G.probs[0].todo : C->todo_total) && total <= G.finish_at) {
             C->done = 1u;
             C->fin_pool = (uint32_t)cur;
             C->fin_nc = min(C->nc[cur], G.cap_c);
@@ -1084,7 +1112,7 @@ __device__ void gen_scan(const Gen &G, int g, uint32_t *buf, int np, const uint3
 
 __global__ void __launch_bounds__(kGenBlock) k_gen_count(Gen G, int g) {
     GenCtl *C = G.ctl;
-    extern __shared__ uint32_t hist[];   // max(ntiles, 2 kGenBlock) counts (gen_hist_lds), or the scan's buffer
+    extern __shared__ uint32_t hist[];   // max(ntiles, 4 kGenBlock) counts, or the scan's buffer
     __shared__ uint32_t a_prob[kMaxAlloc], a_new[kMaxAlloc], a_pre[kMaxAlloc + 1];
     __shared__ uint64_t a_base[kMaxAlloc];
     __shared__ uint32_t w_cnt[kGenBlock / 64];
@@ -1094,7 +1122,7 @@ __global__ void __launch_bounds__(kGenBlock) k_gen_count(Gen G, int g) {
     const int cur = g & 1;
     const int lane = __lane_id(), wave = threadIdx.x >> 6;
     const bool local = G.ntiles <= kHistTiles;
-    if (local)
+    if (local && !G.direct)
         for (int i = threadIdx.x; i < G.ntiles; i += kGenBlock) hist[i] = 0u;
     if (threadIdx.x == 0) {
         // new packets fill the pool up to `live`, problem after problem; each
@@ -1165,13 +1193,14 @@ __global__ void __launch_bounds__(kGenBlock) k_gen_count(Gen G, int g) {
                 tile = kInvalidTile;
             }
         }
-        count_tile(G, hist, local, tile, tile != kInvalidTile);
+        if (!G.direct) count_tile(G, hist, local, tile, tile != kInvalidTile);
         __syncthreads();   // w_cnt and s_base are reused
     }
     if (lk >= 0) {
         const ProbDev &q = G.probs[a_prob[lk]];
         ledger_flush_block(q.led, q.ledc, L);
     }
+    if (G.direct) return;   // k_walk_init takes it from here
     // the records carried over from the last generation
     count_slots(G, hist, local, G.ptile[cur], min(C->nc[cur], G.cap_c));
     if (!last_workgroup(&C->wg_done)) return;
@@ -1530,7 +1559,8 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 constexpr uint32_t kRunSlice = 256;         // run slots a wave reserves at a time
 constexpr uint32_t kRunMax = 32;           // a longer run is cut at the end of a visit (tally lanes stay balanced)
 constexpr uint32_t kWalkLanes = 7u << 14;  // lanes that walk at once
-constexpr uint32_t kWalkAhead = 1u << 16;  // up to this many lanes prefetch both neighbours
+constexpr uint32_t kWalkSpread = 1u << 10;  // waves that walk few packets
+constexpr uint32_t kWalkAhead = 64u * kWalkSpread;   // few packets: at most this many
 constexpr uint32_t kVisitEnd = 0x80000000u;
 // The handed-over packets are taken through one cursor per part, each on a
 // cache line of its own: a single cursor serialises the waves' atomics when
@@ -1599,7 +1629,11 @@ __global__ void k_walk_init(Walk W, int g_last) {
     WalkCtl *C = W.ctl;
     const GenCtl *X = W.gctl;
     uint32_t pool = X->fin_pool, nc = X->fin_nc, nl = X->fin_nl;
-    if (!X->done) {
+    if (W.runs.direct) {
+        pool = 0;
+        nc = 0;
+        nl = min(X->nl[0], W.pool_cap_l);
+    } else if (!X->done) {
         pool = (uint32_t)(g_last & 1);
         nc = min(X->nc[pool], W.pool_cap_c);
         nl = 0;
@@ -1693,7 +1727,11 @@ __device__ __forceinline__ uint32_t wave_claim(uint32_t *counter, uint32_t n) {
 // packets use every SIMD.  Each pass of the inner loop is one segment; runs,
 // refills and the space left are looked after every fourth.
 // ONE: a single problem, whose parameters are the same in every lane.
-template <bool ONE>
+// AHEAD: the round has few packets (kWalkAhead): they are spread over as many
+// waves as there are SIMDs, with free lanes in each (a wave waits for whatever
+// one of its lanes has to look after), and the medium of both pixels a packet
+// may enter next is loaded a segment ahead.
+template <bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k_walk(Walk W, int r) {
     // entry k % kRing: roulette draw, cos and sin factors of block k, optical depth of block k + 1
     __shared__ float4 ring[kRing][64];
@@ -1707,7 +1745,9 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
     WalkCtl *C = W.ctl;
     if ((uint32_t)r >= C->w_end) return;
     const uint32_t lanes = C->lanes;
-    if (blockIdx.x * 64u >= lanes) return;
+    if ((lanes <= kWalkAhead) != AHEAD) return;
+    const uint32_t per = AHEAD ? min(64u, (lanes + kWalkSpread - 1u) / kWalkSpread) : 64u;   // lanes a wave uses
+    if (blockIdx.x * per >= lanes) return;
     const int lane = __lane_id();
 
     if (threadIdx.x >= 64u) {
@@ -1753,16 +1793,14 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
     }
 
     const int par = r & 1;
-    const uint32_t gid = blockIdx.x * 64u + threadIdx.x;
+    const uint32_t gid = blockIdx.x * per + threadIdx.x;
+    const bool used = threadIdx.x < per && gid < lanes;
     const uint32_t cap = C->cap, n_state = C->n_state(par), n_p = C->n_p, nc = C->nc;
     const PacketRec *pool = W.pool[C->pool];
     const uint32_t *ptile = W.ptile[C->pool];
     const int tw = W.runs.tw, th = W.runs.th;
     const uint64_t ev0 = (uint64_t)gid * cap;   // a multiple of 4
     const uint32_t s_ev0 = 4u * lane + ((lane >> 2) & 3u);
-    // few packets: the medium of both pixels the packet may enter next is
-    // loaded a segment ahead
-    const bool ahead = lanes <= kWalkAhead;
 
     // what a lane does (bit 0 beside: its last event left a visit open)
     enum : uint32_t {
@@ -1779,13 +1817,13 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
     LedgerRegs L;
     Packet p;                  // ix, iz: pixel within the tile
     idle_packet(p, 0, 0);
-    Hot B = Q.H;               // as Q.H, with the extent of the tile's part in the grid
+    int wx = 0, wz = 0;        // extent of the tile's part in the grid
     float4 mm = make_float4(0.f, 0.f, 0.f, 0.f), mx = mm, mz = mm;   // medium here, and of the neighbours ahead
     int tx0 = 0, tz0 = 0;
     uint32_t tile = 0, k0 = 0, resume = kNoSlot;
     uint32_t n = 0, run0 = 0;  // events written; the first of the current run
     uint32_t lim = 0;          // event count at which the run or the space has to be looked after
-    uint32_t fl = gid < lanes ? kEmpty : kIdle;
+    uint32_t fl = used ? kEmpty : kIdle;
     bool more = C->left != 0;  // handed-over packets may be left (wave-uniform)
     uint32_t part = blockIdx.x % kWalkParts, tries = 0;
     uint32_t rbase = 0, rused = kRunSlice;
@@ -1814,18 +1852,29 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         }
         rused += c;
     };
-    // the pixel's index in the medium table, and its loads
-    auto pixel = [&] { return (tz0 + p.iz) * Q.H.nx + tx0 + p.ix; };
+    // Along x, a packet's face is at gx (1 or 0; 2, which it never reaches, for
+    // no motion) and the pixel behind it dx away; the same along z.
+    float gx = 2.f, gz = 2.f;
+    int dx = 0, dz = 0;
+    int gb = 0;                // the tile's first pixel in the medium table
+    auto turn = [&] {
+        gx = p.sx > 0.f ? 1.f : (p.sx < 0.f ? 0.f : 2.f);
+        gz = p.sz > 0.f ? 1.f : (p.sz < 0.f ? 0.f : 2.f);
+        dx = p.sx > 0.f ? 1 : -1;
+        dz = p.sz > 0.f ? 1 : -1;
+    };
+    auto pixel = [&] { return gb + p.iz * Q.H.nx + p.ix; };
     auto load_ahead = [&](int i) {
-        mx = load_medium(Q.med, i + (p.sx > 0.f ? 1 : -1));
-        mz = load_medium(Q.med, i + (p.sz > 0.f ? Q.H.nx : -Q.H.nx));
+        mx = load_medium(Q.med, i + dx);
+        mz = load_medium(Q.med, dz > 0 ? i + Q.H.nx : i - Q.H.nx);
     };
     auto enter_tile = [&] {
-        B.nx = min(tw, Q.H.nx - tx0);
-        B.nz = min(th, Q.H.nz - tz0);
+        wx = min(tw, Q.H.nx - tx0);
+        wz = min(th, Q.H.nz - tz0);
+        gb = tz0 * Q.H.nx + tx0;
         const int i = pixel();
         mm = load_medium(Q.med, i);
-        if (ahead) load_ahead(i);
+        if constexpr (AHEAD) load_ahead(i);
     };
     // the lane takes a packet (goes_on: from the last round, maybe in the
     // middle of a visit) and asks for its random blocks
@@ -1839,7 +1888,6 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
             L = LedgerRegs();
             prob = np;
             Q = walk_prob(W.probs[np]);
-            B = Q.H;
         }
         const int tx = p.ix / tw, tz = p.iz / th;
         tx0 = tx * tw;
@@ -1847,53 +1895,82 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         p.ix -= tx0;
         p.iz -= tz0;
         tile = (uint32_t)(Q.tile_base + tz * Q.ntx + tx);
+        turn();
         enter_tile();
         k0 = p.k;
         const uint32_t in_visit = goes_on && rec->tile != 0u ? 1u : 0u;
         resume = in_visit ? gid : kNoSlot;
         fl = kWait | in_visit;
     };
-    // one segment
-    auto pass = [&](auto ahead_c, uint32_t u) {
-        constexpr bool kAhead = decltype(ahead_c)::value;
+    // One segment: the arithmetic of step(), scatter_roulette() and
+    // scatter_deflect(), operation by operation, with what depends on the
+    // direction alone kept from the scatter and no test for a zero component.
+    auto pass = [&](uint32_t u) {
+#pragma clang fp contract(off)
         const float4 rnd = ring[p.k % kRing][lane];   // for a scatter at the segment's end
-        const uint32_t lp = (uint32_t)(__mul24(p.iz, tw) + p.ix);
-        const int oix = p.ix, oiz = p.iz;
-        float T = 0.f, dw = 0.f;
-        const float g = mm.w, sx = p.sx, sz = p.sz;   // direction of the segment, before any scatter
-        const int e = step(B, p, mm, T, dw);          // EV_ESCAPE: the packet leaves the tile
-        const bool at = e == EV_SCATTER;
+        uint32_t ev = (uint32_t)(__mul24(p.iz, tw) + p.ix);
+        const float sx = p.sx, sz = p.sz, g = mm.w;   // direction of the segment, before any scatter
+        const float dfx = fabsf(gx - p.fx) * fabsf(p.isx), dfz = fabsf(gz - p.fz) * fabsf(p.isz);
+        const float d = fminf(dfx, dfz);
+        const float od = mm.y * d;
+        const bool at = od > p.tau;
+        const float l = at ? p.tau * mm.z : d;
+        const float x = mm.x * l;
+        const float wf = p.w * absorbed_per_depth(x);
+        const float dw = wf * x, T = wf * l;
+        p.w = fmaf(-x, wf, p.w);
+        const bool cx = !at & (dfx <= dfz), cz = !at & (dfz <= dfx);   // faces crossed (both at a corner)
+        const float nfx = fminf(fmaxf(fmaf(sx, l, p.fx), 0.f), 1.f);
+        const float nfz = fminf(fmaxf(fmaf(sz, l, p.fz), 0.f), 1.f);
+        p.tau = p.tau - od;                           // a scatter replaces it
+        p.ix += cx ? dx : 0;
+        p.iz += cz ? dz : 0;
+        p.fx = cx ? 1.f - gx : nfx;
+        p.fz = cz ? 1.f - gz : nfz;
+        const bool out = ((unsigned)p.ix >= (unsigned)wx) | ((unsigned)p.iz >= (unsigned)wz);
         // the medium of the pixel the next step starts in (padding, if outside
         // the grid), on its way while the rest is computed
-        if constexpr (!kAhead)
+        if constexpr (!AHEAD)
             if (!at) mm = load_medium(Q.med, pixel());
-        p.ur = rnd.x;
-        const bool killed = scatter_roulette(Q.H, p, at, L);
-        const bool vend = killed || !at;
-        s_ev[s_ev0 ^ u] = make_float4(T * Q.fx, sx, sz, __uint_as_float(lp | (vend ? kVisitEnd : 0u)));
+        fl = at ? 1u : (out ? kLeft : 0u);
+        ev |= at ? 0u : kVisitEnd;
+        bool go = at;
+        const bool low = at & ((p.k >= kMaxInteractions) | (fabsf(p.w) < Q.H.wth * p.w0abs));
+        if (__builtin_expect(low, 0)) {               // rare
+            if (p.k >= kMaxInteractions || (Q.H.flags & MC_FLAG_LITERAL_TRUNCATION) || !(rnd.x < Q.H.inv_rm)) {
+                L.loss += p.w;
+                fl = kDead;
+                ev |= kVisitEnd;
+                go = false;
+            } else {
+                L.gain += (Q.H.rm - 1.f) * p.w;
+                p.w *= Q.H.rm;
+            }
+        }
+        s_ev[s_ev0 ^ u] = make_float4(T * Q.fx, sx, sz, __uint_as_float(ev));
         ++n;
         L.absorbed += (double)dw;
-        if (!vend) {
+        if (go) {
             float nx_, nz_;
-            hg_rotate(g, rnd.z, rnd.y, p.sx, p.sz, nx_, nz_);
+            hg_rotate(g, rnd.z, rnd.y, sx, sz, nx_, nz_);
             set_dir(p, nx_, nz_);
+            turn();
             ++p.k;
             p.tau = rnd.w;
         }
-        fl = (vend ? 0u : 1u) | (e == EV_ESCAPE ? kLeft : 0u) | (killed ? kDead : 0u);
-        if constexpr (kAhead) {
+        if constexpr (AHEAD) {
             // taken as late as can be: the loads have had a whole pass
-            const bool cx = p.ix != oix, cz = p.iz != oiz;
             mm.x = cx ? mx.x : (cz ? mz.x : mm.x);
             mm.y = cx ? mx.y : (cz ? mz.y : mm.y);
             mm.z = cx ? mx.z : (cz ? mz.z : mm.z);
             mm.w = cx ? mx.w : (cz ? mz.w : mm.w);
-            if (cx && cz) mm = load_medium(Q.med, pixel());   // a corner: rare
-            load_ahead(e == EV_ESCAPE ? 0 : pixel());
+            const int i = out ? 0 : pixel();
+            if (__builtin_expect(cx & cz, 0)) mm = load_medium(Q.med, i);   // a corner
+            load_ahead(i);
         }
     };
 
-    if (gid < n_state) take(W.state[par] + gid, true);
+    if (used && gid < n_state) take(W.state[par] + gid, true);
     uint32_t post = 0;
     for (;;) {
         uint32_t fresh = post == 0u && fl >= kWait ? 1u : 0u;   // the packet is new to the second wave
@@ -1965,15 +2042,9 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         if (stop) break;
         const unsigned long long moved = __ballot(fl < kLeft);
         const uint32_t n4 = n;   // a multiple of 4 in lanes that move
-        if (ahead) {
 #pragma unroll
-            for (uint32_t u = 0; u < 4u; ++u)
-                if (fl < kLeft) pass(std::true_type{}, u);
-        } else {
-#pragma unroll
-            for (uint32_t u = 0; u < 4u; ++u)
-                if (fl < kLeft) pass(std::false_type{}, u);
-        }
+        for (uint32_t u = 0; u < 4u; ++u)
+            if (fl < kLeft) pass(u);
         // the batch's events, four lanes to a lane's 64 bytes: written one by
         // one, each event of 16 bytes is a request of its own to the L2
 #pragma unroll
@@ -1981,7 +2052,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
             if (((moved >> (16u * j)) & 0xFFFFull) == 0ull) continue;
             const uint32_t src = 16u * j + ((uint32_t)lane >> 2), u = (uint32_t)lane & 3u;
             const float4 v = s_ev[(4u * src + ((src >> 2) & 3u)) ^ u];
-            const uint32_t at = (blockIdx.x * 64u + src) * cap + __shfl(n4, (int)src) + u;
+            const uint32_t at = (blockIdx.x * per + src) * cap + __shfl(n4, (int)src) + u;
             if ((moved >> src) & 1ull) W.ev[at] = v;
         }
     }
@@ -2025,6 +2096,13 @@ __global__ void __launch_bounds__(kGenBlock) k_run_count(Walk W, int r) {
     uint32_t total = 0;
     bool fits = true;
     const uint32_t jobs = scan_tiles(G, hist, total, fits);
+    uint32_t left = 0;   // summed over the parts by the first wave
+    if (threadIdx.x < kWalkParts) {
+        const uint32_t size = part_begin(C->n_p, threadIdx.x + 1) - part_begin(C->n_p, threadIdx.x);
+        left = size - min(size, C->part[threadIdx.x].taken);
+    }
+#pragma unroll
+    for (int o = 1; o < (int)kWalkParts; o <<= 1) left += __shfl_xor(left, o);
     if (threadIdx.x == 0) {
         C->n_jobs = jobs;
         C->job_cursor = 0;
@@ -2032,11 +2110,6 @@ __global__ void __launch_bounds__(kGenBlock) k_run_count(Walk W, int r) {
         C->n_state(par) = 0;     // taken by this round; the next one but one fills it
         C->n_run(par ^ 1) = 0;
         const uint32_t going = C->n_state(par ^ 1);
-        uint32_t left = 0;
-        for (uint32_t j = 0; j < kWalkParts; ++j) {
-            const uint32_t size = part_begin(C->n_p, j + 1) - part_begin(C->n_p, j);
-            left += size - min(size, C->part[j].taken);
-        }
         C->left = left;
         if (!going && !left) C->w_end = (uint32_t)r + 1u;
         else walk_share(W, C, going, left);
@@ -2561,16 +2634,6 @@ __global__ void k_trace(const ProbDev *pd, const uint64_t *pids, int n_pids, mc_
 }
 
 // ------------------------------------------------------------------ setup / post kernels
-// Medium table of the transport: {mua dx, mus dx, 1/(mus dx), g} per pixel,
-// one 16-byte load per step (the scatter reads g from the same load).
-__global__ void k_setup_medium(int npix, float dx, const float *mua, const float *mus, const float *g,
-                               float4 *med) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= npix) return;
-    const float a = mua[i] * dx, s = mus[i] * dx;
-    med[i] = make_float4(a, s, s > 0.f ? 1.f / s : 0.f, g[i]);
-}
-
 __global__ void k_fill_zero(uint32_t *p, size_t n) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0u;
@@ -2617,12 +2680,8 @@ __global__ void __launch_bounds__(1024) k_map_cdf(int n, const double *map, doub
 // max |q| / mean |q| is known, launches nothing and normalises to NaN.
 // Fixed-point scale fx = 2^(32 - e) with 2^e above the weight bound, so a
 // segment adds at most sqrt 2 * 2^32 in scaled units; a visit is flushed in
-// parts at flush_track * 2^32 <= 2^48, inside fixed_add's 2^51.  Every thread
-// also fills the problem's entries of the tile-to-problem table.
-__global__ void k_prob_setup(ProbDev h, ProbDev *out, uint32_t *tile_prob, uint32_t index) {
-    for (int k = threadIdx.x; k < h.ntiles; k += blockDim.x)
-        if (tile_prob) tile_prob[h.tile_base + k] = index;
-    if (threadIdx.x != 0) return;
+// parts at flush_track * 2^32 <= 2^48, inside fixed_add's 2^51.
+__device__ void prob_setup(ProbDev &h, ProbDev *out) {
     bool usable = true;
     double wb = h.wbound;
     if (h.map) {
@@ -2649,29 +2708,28 @@ __global__ void k_prob_setup(ProbDev h, ProbDev *out, uint32_t *tile_prob, uint3
     *out = h;
 }
 
-// Normalise (Sec. 6: divide by the packet count; times the source measure and
-// the track-length-to-fluence factor 1/(dx Np) in pixel units) and transpose
-// [npix][K] -> [K][npix]; the adjoint output reads the mirrored direction,
-// (-1)^n on orders n >= 1.  A job whose fixed-point tile tally may have
-// wrapped (ledc[4]) or an overflowed queue turns the whole output into NaN.
-__global__ void k_normalise(const ProbDev *pd, int N, const GenCtl *ctl, double *out) {
-    const int npix = pd->npix;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= npix) return;
-    const int K = 2 * N + 1;
-    const bool bad = pd->ledc[4] != 0 || (ctl && ctl->overflow);
-    const double scale = pd->scale / (double)pd->dx;
-    const double *t64 = pd->t64;
-    for (int c = 0; c < K; ++c) {
-        const int n = c <= N ? c : c - N;
-        const double f = (pd->adjoint && (n & 1)) ? -scale : scale;
-        out[(size_t)c * npix + i] = bad ? __builtin_nan("") : t64[(size_t)i * K + c] * f;
+// Set-up of one problem: the medium table of the transport, {mua dx, mus dx,
+// 1/(mus dx), g} per pixel (one 16-byte load per step; the scatter reads g from
+// the same load), the problem's entries of the tile-to-problem table, its
+// descriptor, and nz words at `zero` cleared.  One launch: each costs a small
+// run more than the work.
+__global__ void __launch_bounds__(256) k_setup(ProbDev h, ProbDev *out, uint32_t *tile_prob, uint32_t index,
+                                               const float *mua, const float *mus, const float *g, uint32_t *zero,
+                                               size_t nz) {
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = t; i < nz; i += step) zero[i] = 0u;
+    float4 *med = const_cast<float4 *>(h.med);
+    for (size_t i = t; i < (size_t)h.npix; i += step) {
+        const float a = mua[i] * h.dx, m = mus[i] * h.dx;
+        med[i] = make_float4(a, m, m > 0.f ? 1.f / m : 0.f, g[i]);
     }
+    if (tile_prob)
+        for (size_t k = t; k < (size_t)h.ntiles; k += step) tile_prob[h.tile_base + k] = index;
+    if (t == 0) prob_setup(h, out);
 }
 
-__global__ void k_ledger_out(const ProbDev *pd, const GenCtl *ctl, const WalkCtl *rounds, uint32_t generations,
-                             mc_ledger *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ void ledger_out(const ProbDev *pd, const GenCtl *ctl, const WalkCtl *rounds, uint32_t generations,
+                           mc_ledger *out) {
     const double *led = pd->led;
     const unsigned long long *ledc = pd->ledc;
     out->launched = led[0];
@@ -2685,6 +2743,32 @@ __global__ void k_ledger_out(const ProbDev *pd, const GenCtl *ctl, const WalkCtl
     out->visits = ledc[2];
     out->scatters = ledc[3];
     out->generations = rounds ? min(rounds->w_end, generations) : (ctl ? (ctl->done ? ctl->gen_done : generations) : 0);
+}
+
+__global__ void k_ledger_out(const ProbDev *pd, mc_ledger *out) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) ledger_out(pd, nullptr, nullptr, 0u, out);
+}
+
+// Normalise (Sec. 6: divide by the packet count; times the source measure and
+// the track-length-to-fluence factor 1/(dx Np) in pixel units) and transpose
+// [npix][K] -> [K][npix]; the adjoint output reads the mirrored direction,
+// (-1)^n on orders n >= 1.  A job whose fixed-point tile tally may have
+// wrapped (ledc[4]) or an overflowed queue turns the whole output into NaN.
+__global__ void k_normalise(const ProbDev *pd, int N, const GenCtl *ctl, const WalkCtl *rounds, uint32_t generations,
+                            double *out, mc_ledger *ledger) {
+    if (ledger && blockIdx.x == 0 && threadIdx.x == 0) ledger_out(pd, ctl, rounds, generations, ledger);
+    const int npix = pd->npix;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= npix) return;
+    const int K = 2 * N + 1;
+    const bool bad = pd->ledc[4] != 0 || (ctl && ctl->overflow);
+    const double scale = pd->scale / (double)pd->dx;
+    const double *t64 = pd->t64;
+    for (int c = 0; c < K; ++c) {
+        const int n = c <= N ? c : c - N;
+        const double f = (pd->adjoint && (n & 1)) ? -scale : scale;
+        out[(size_t)c * npix + i] = bad ? __builtin_nan("") : t64[(size_t)i * K + c] * f;
+    }
 }
 
 // Residual (Sec. 2, Sec. 6) with a deterministic single-block reduction of eps.
@@ -2857,7 +2941,7 @@ constexpr uint32_t kQuietPercent = 50;         // see the quiet rule of k_transp
 constexpr uint64_t kDirectMax = 3ull << 20;
 constexpr uint64_t kWalkEvents = 1ull << 27;         // events a round may write
 constexpr uint64_t kWalkEventsPerLane = 1ull << 14;  // or this many per lane if that is less
-constexpr uint32_t kWalkRounds = 4;                  // rounds enqueued: these, and as many as events are expected
+constexpr uint32_t kWalkRounds = 2;                  // rounds enqueued: these, and as many as events are expected
 constexpr uint64_t kWalkRoundEvents = 6144;          // per packet
 constexpr uint32_t kRunJobMin = 256;                  // smallest tally job of a round with few runs
 
@@ -2939,11 +3023,15 @@ size_t tile_lds_bytes(int tw, int th, int K) {
     return tal + (size_t)tw * th * (sizeof(float4) + sizeof(uint32_t));
 }
 
-// Tiled transport unless the whole tally (8 bytes per value) fits one
-// workgroup's LDS and the run is small (the tiled mode's per-generation
-// overhead is ~10 ms; measured on a 32x32 pencil beam, the tiled mode
-// overtakes the whole-grid kernel near 2e6 packets and is 5x faster at 1e8).
+// The whole-grid transport serves runs that have no event buffer for walk and
+// tally (mc_run_noalloc), if the whole tally (8 bytes per value) fits one
+// workgroup's LDS and the run is small (generations alone cost ~10 ms a run;
+// measured on a 32x32 pencil beam, they overtake the whole-grid kernel near
+// 2e6 packets and are 5x faster at 1e8).  With the buffer, walking is faster
+// at every size: 32x32, N = 8: 1e3 packets 0.95 against 1.68 ms, 1e5 1.5
+// against 2.1, 2e6 7.7 against 18.6.
 bool is_tiled(const mc_medium *m, const mc_run *run, const TileTuning &tt) {
+    if (tt.ev_max) return true;
     if ((size_t)m->nx * m->nz * (2 * run->n_harm + 1) * sizeof(double) > kLdsGridMax) return true;
     return run->n_packets > tt.grid_max;
 }
@@ -3007,7 +3095,7 @@ struct BatchLayout {
            carry[2] = {0, 0};
     std::vector<size_t> med, cdf, t64, led, ledc;
     std::vector<int> ntx, ntz, tile_base;
-    size_t probs = 0, tile_prob = 0, ctl = 0, launched = 0, fin_cur = 0, tcount = 0, tcursor = 0, jobs = 0,
+    size_t probs = 0, tile_prob = 0, zero = 0, ctl = 0, launched = 0, fin_cur = 0, tcount = 0, tcursor = 0, jobs = 0,
            sidx = 0, pool[2] = {0, 0}, ptile[2] = {0, 0}, total = 0;
 };
 
@@ -3033,12 +3121,6 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
         off = align_up(off + (npix + 2 * pad) * sizeof(float4));
         B.cdf.push_back(off);
         if (pb[i].src[0].kind == MC_SRC_MAP) off = align_up(off + (npix + 1) * sizeof(double));   // CDF, max |q|
-        B.t64.push_back(off);
-        off = align_up(off + npix * B.K * sizeof(double));
-        B.led.push_back(off);
-        off = align_up(off + 8 * sizeof(double));
-        B.ledc.push_back(off);
-        off = align_up(off + 8 * sizeof(unsigned long long));
         B.ntx.push_back((pb[i].m->nx + B.t - 1) / B.t);
         B.ntz.push_back((pb[i].m->nz + B.t - 1) / B.t);
         B.tile_base.push_back(B.ntiles);
@@ -3076,8 +3158,9 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
             65536, kGenBase + kGenPerTile * side + kGenPerPool * ((B.total_packets + B.live - 1) / B.live));
     }
     if (walk) {
-        B.lanes = (std::min<uint64_t>(B.direct ? B.total_packets : std::min(B.finish, B.live), kWalkLanes) + 63) & ~63ull;
-        B.ev_cap = std::min<uint64_t>(B.tt.ev_max, B.lanes * kWalkEventsPerLane);
+        const uint64_t most = std::min<uint64_t>(B.direct ? B.total_packets : std::min(B.finish, B.live), kWalkLanes);
+        B.lanes = (most + 63) & ~63ull;
+        B.ev_cap = std::min<uint64_t>(B.tt.ev_max, most * kWalkEventsPerLane);
         // a run takes four events or more; up to 63 of a slice's slots stay empty
         B.run_cap = B.ev_cap / 4 * kRunSlice / (kRunSlice - 63) + kRunSlice * (B.lanes / 64 + 1);
         B.run_jobs = (uint64_t)B.ntiles + std::max<uint64_t>(B.run_cap / kJobSize, 2ull * kTileSlotsMax) + 2;
@@ -3089,7 +3172,17 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
     off = align_up(off + (size_t)n * sizeof(ProbDev));
     B.tile_prob = off;
     off = align_up(off + (size_t)B.ntiles * sizeof(uint32_t));
-    // everything from ctl to the end of the cursors is zeroed at set-up
+    // everything from zero to the cursors starts at zero: tallies and ledgers,
+    // then the control blocks and counts
+    B.zero = off;
+    for (int i = 0; i < n; ++i) {
+        B.t64.push_back(off);
+        off = align_up(off + (size_t)pb[i].m->nx * pb[i].m->nz * B.K * sizeof(double));
+        B.led.push_back(off);
+        off = align_up(off + 8 * sizeof(double));
+        B.ledc.push_back(off);
+        off = align_up(off + 8 * sizeof(unsigned long long));
+    }
     B.ctl = off;
     off = align_up(off + sizeof(GenCtl));
     B.launched = off;
@@ -3148,7 +3241,7 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
 // |c0| + 2 sum (|c_n| + |s_n|) (1 without a profile, and for pencils and
 // lines); a roulette survivor gains at most the factor m W_th.  The
 // equal-count map launch multiplies by q_i / mean |q|, bounded on the device
-// once max |q| is known (k_prob_setup).
+// once max |q| is known (prob_setup).
 double weight_bound(const mc_source *src, int n_src, const mc_run *run) {
     double wb = 0.0;
     for (int s = 0; s < n_src; ++s) {
@@ -3204,7 +3297,7 @@ mc_status validate(const mc_medium *m, const mc_source *src, int n_src, const mc
     return MC_OK;
 }
 
-// The host's part of a problem descriptor (k_prob_setup adds the rest).
+// The host's part of a problem descriptor (prob_setup adds the rest).
 void fill_problem(ProbDev &P, const mc_medium *m, const mc_source *src, int n_src, const mc_run *run, int adjoint,
                   double flush_track) {
     std::memset(&P, 0, sizeof(P));
@@ -3285,14 +3378,16 @@ mc_status set_lds_limit(const void *fn, size_t lds) {
                                                                                                     : MC_ERR_DEVICE;
 }
 
-// Medium table, CDF of a MAP source, then the problem descriptor.
+// CDF of a MAP source, then the medium table and the problem descriptor;
+// `zero`: memory to clear beside (whole 32-bit words).
 mc_status setup_problem(const ProbDev &host, ProbDev *pd_d, uint32_t *tile_prob, uint32_t index, const float *mua,
-                        const float *mus, const float *g, hipStream_t s) {
-    hipLaunchKernelGGL(k_setup_medium, dim3((host.npix + 255) / 256), dim3(256), 0, s, host.npix, host.dx, mua, mus, g,
-                       const_cast<float4 *>(host.med));
+                        const float *mus, const float *g, hipStream_t s, void *zero = nullptr, size_t zero_bytes = 0) {
     if (host.map)
         hipLaunchKernelGGL(k_map_cdf, dim3(1), dim3(1024), 0, s, host.npix, host.map, const_cast<double *>(host.cdf));
-    hipLaunchKernelGGL(k_prob_setup, dim3(1), dim3(256), 0, s, host, pd_d, tile_prob, index);
+    const size_t work = std::max<size_t>(host.npix, zero_bytes / 4);
+    const unsigned grid = (unsigned)std::min<size_t>((work + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_setup, dim3(grid), dim3(256), 0, s, host, pd_d, tile_prob, index, mua, mus, g,
+                       (uint32_t *)zero, zero_bytes / 4);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 
@@ -3335,10 +3430,12 @@ mc_status enqueue_rounds(const Walk &W, const BatchLayout &B, int N, int n_gen, 
     for (uint32_t r = 0; r < B.rounds; ++r) {
         LaunchTimer tw(timer);
         if ((st = tw.begin(s)) != MC_OK) return st;
-        if (W.runs.nprob == 1)
-            hipLaunchKernelGGL(k_walk<true>, dim3((unsigned)(B.lanes / 64)), dim3(128), 0, s, W, (int)r);
-        else
-            hipLaunchKernelGGL(k_walk<false>, dim3((unsigned)(B.lanes / 64)), dim3(128), 0, s, W, (int)r);
+        const bool one = W.runs.nprob == 1;
+        if (B.lanes > kWalkAhead)
+            hipLaunchKernelGGL((one ? k_walk<true, false> : k_walk<false, false>), dim3((unsigned)(B.lanes / 64)),
+                               dim3(128), 0, s, W, (int)r);
+        hipLaunchKernelGGL((one ? k_walk<true, true> : k_walk<false, true>),
+                           dim3((unsigned)std::min<uint64_t>(B.lanes, kWalkSpread)), dim3(128), 0, s, W, (int)r);
         if ((st = tw.end(s)) != MC_OK) return st;
         hipLaunchKernelGGL(k_run_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, W, (int)r);
         hipLaunchKernelGGL(k_run_sort, dim3(sgrid), dim3(256), scatter_lds, s, W, (int)r);
@@ -3371,14 +3468,8 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     ProbDev *probs_d = reinterpret_cast<ProbDev *>(base + B.probs);
     uint32_t *tile_prob = reinterpret_cast<uint32_t *>(base + B.tile_prob);
     GenCtl *ctl = reinterpret_cast<GenCtl *>(base + B.ctl);
-    // counters, cursors and tile counts start at zero; the control block knows the total to launch
-    if ((st = launch_zero(base + B.ctl, B.tcursor - B.ctl, s)) != MC_OK) return st;
     for (int i = 0; i < n; ++i) {
         const mc_medium *m = pb[i].m;
-        const int npix = m->nx * m->nz;
-        if ((st = launch_zero(base + B.t64[i], (size_t)npix * B.K * sizeof(double), s)) != MC_OK) return st;
-        if ((st = launch_zero(base + B.led[i], B.ledc[i] + 8 * sizeof(unsigned long long) - B.led[i], s)) != MC_OK)
-            return st;
         ProbDev P;
         fill_problem(P, m, pb[i].src, pb[i].n_src, pb[i].run, pb[i].adjoint, tt.flush_track);
         P.ntx = B.ntx[i];
@@ -3389,7 +3480,9 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
         P.t64 = reinterpret_cast<double *>(base + B.t64[i]);
         P.led = reinterpret_cast<double *>(base + B.led[i]);
         P.ledc = reinterpret_cast<unsigned long long *>(base + B.ledc[i]);
-        if ((st = setup_problem(P, probs_d + i, tile_prob, (uint32_t)i, m->mua_d, m->mus_d, m->g_d, s)) != MC_OK)
+        // the first set-up launch also clears what must start at zero
+        if ((st = setup_problem(P, probs_d + i, tile_prob, (uint32_t)i, m->mua_d, m->mus_d, m->g_d, s,
+                                i ? nullptr : base + B.zero, i ? 0 : B.tcursor - B.zero)) != MC_OK)
             return st;
     }
     // total packets to launch (problems whose map has no power launch none:
@@ -3406,7 +3499,8 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     G.quiet_pct = B.tt.quiet;
     G.max_visits = B.tt.maxvis;
     G.tail_visits = B.tt.tailvis;
-    G.finish_at = (uint32_t)(B.direct ? B.live : B.finish);
+    G.finish_at = (uint32_t)B.finish;
+    G.direct = B.direct;
     G.slice = B.tt.slice;
     G.probs = probs_d;
     G.tile_prob = tile_prob;
@@ -3422,7 +3516,7 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     G.ctl = ctl;
     G.launched = reinterpret_cast<uint64_t *>(base + B.launched);
     G.fin_cur = reinterpret_cast<unsigned long long *>(base + B.fin_cur);
-    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(1), 0, s, G);
+    if (n > 1) hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(1), 0, s, G);
 
     const TileFn fn = kernels().tile[N];
     if ((st = set_lds_limit(reinterpret_cast<const void *>(fn), B.tile_lds)) != MC_OK) return st;
@@ -3434,13 +3528,16 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     const unsigned sgrid = (unsigned)std::max(1, 4 * cus);
     // the generation kernels' tile histograms (and the scan's buffer) in dynamic LDS
     const bool local_hist = B.ntiles <= kHistTiles;
-    const size_t count_lds = sizeof(uint32_t) * std::max<size_t>(local_hist ? B.ntiles : 0, 2 * kGenBlock);
+    const size_t count_lds = sizeof(uint32_t) * std::max<size_t>(local_hist ? B.ntiles : 0, 4 * kGenBlock);
     const size_t scatter_lds = local_hist ? sizeof(uint32_t) * B.ntiles : 0;
     if ((st = set_lds_limit(reinterpret_cast<const void *>(k_gen_count), count_lds)) != MC_OK) return st;
     if ((st = set_lds_limit(reinterpret_cast<const void *>(k_gen_scatter), scatter_lds)) != MC_OK) return st;
     const uint32_t n_gen = B.direct ? 0u : B.tt.max_gen;
-    // a direct run's only generation launches every packet and finds the threshold met
-    if (B.direct) hipLaunchKernelGGL(k_gen_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, G, 0);
+    // a direct run's only generation launches every packet
+    if (B.direct) {
+        const uint64_t want = (B.total_packets + kGenBlock - 1) / kGenBlock + (uint64_t)n;
+        hipLaunchKernelGGL(k_gen_count, dim3((unsigned)std::min<uint64_t>(cgrid, want)), dim3(kGenBlock), count_lds, s, G, 0);
+    }
     for (uint32_t g = 0; g < n_gen; ++g) {
         hipLaunchKernelGGL(k_gen_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, G, (int)g);
         hipLaunchKernelGGL(k_gen_scatter, dim3(sgrid), dim3(256), scatter_lds, s, G, (int)g);
@@ -3473,6 +3570,7 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
             W.carry[p] = reinterpret_cast<float *>(base + B.carry[p]);
         }
         W.pool_cap_c = G.cap_c;
+        W.pool_cap_l = G.cap_l;
         W.ev = reinterpret_cast<float4 *>(base + B.ev);
         W.run = reinterpret_cast<RunRec *>(base + B.run);
         W.lanes_max = (uint32_t)B.lanes;
@@ -3501,11 +3599,9 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     // normalisation and ledgers
     for (int i = 0; i < n; ++i) {
         const int npix = pb[i].m->nx * pb[i].m->nz;
-        hipLaunchKernelGGL(k_normalise, dim3((npix + 255) / 256), dim3(256), 0, s, probs_d + i, N,
-                           (const GenCtl *)ctl, pb[i].coeffs);
-        if (pb[i].ledger)
-            hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)(probs_d + i), (const GenCtl *)ctl,
-                               (const WalkCtl *)(B.direct ? W.ctl : nullptr), B.direct ? B.rounds : n_gen, pb[i].ledger);
+        hipLaunchKernelGGL(k_normalise, dim3((npix + 255) / 256), dim3(256), 0, s, probs_d + i, N, (const GenCtl *)ctl,
+                           (const WalkCtl *)(B.direct ? W.ctl : nullptr), B.direct ? B.rounds : n_gen, pb[i].coeffs,
+                           pb[i].ledger);
     }
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
@@ -3540,10 +3636,7 @@ mc_status run_mc(const mc_medium *m, const mc_source *src, int n_src, const mc_r
     const size_t lds = (size_t)npix * (2 * N + 1) * sizeof(double);
     if ((st = run_grid(pd, L, run, timer, base, lds, s)) != MC_OK) return st;
     hipLaunchKernelGGL(k_normalise, dim3((npix + 255) / 256), dim3(256), 0, s, (const ProbDev *)pd, N,
-                       (const GenCtl *)nullptr, coeffs);
-    if (ledger)
-        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, (const GenCtl *)nullptr,
-                           (const WalkCtl *)nullptr, 0u, ledger);
+                       (const GenCtl *)nullptr, (const WalkCtl *)nullptr, 0u, coeffs, ledger);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 
@@ -3612,8 +3705,7 @@ mc_status run_binned(const mc_medium *m, const mc_source *src, int n_src, const 
     hipLaunchKernelGGL(k_binned_normalise, dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, s, (const ProbDev *)pd,
                        n_bins, 2.0 * M_PI / n_bins, (const double *)raw, out);
     if (ledger)
-        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, (const GenCtl *)nullptr,
-                           (const WalkCtl *)nullptr, 0u, ledger);
+        hipLaunchKernelGGL(k_ledger_out, dim3(1), dim3(1), 0, s, (const ProbDev *)pd, ledger);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 

@@ -13,12 +13,14 @@ pytestmark = pytest.mark.gpu
 COUNTS = ("packets", "segments", "visits", "scatters")
 
 
-def _run(ph, specs, n, N, adjoint=False, tuning=None, flags=0, w_th=1e-4, m=10.0):
+def _run(ph, specs, n, N, adjoint=False, tuning=None, flags=0, w_th=1e-4, m=10.0, noalloc=False):
     from paper_1608_05238_amd import rmc
     med = rmc.Medium.from_phantom(ph)
     run = rmc.make_run(n, N, seed=7, stream_tag=int(adjoint), flags=flags, w_threshold=w_th, roulette_m=m)
-    fn = rmc.mc_adjoint if adjoint else rmc.mc_forward
-    co, led = fn(med, specs, run, tuning=tuning)
+    if noalloc:
+        co, led = rmc.mc_run_noalloc(med, specs, run, adjoint, tuning=tuning)
+    else:
+        co, led = (rmc.mc_adjoint if adjoint else rmc.mc_forward)(med, specs, run, tuning=tuning)
     return co.cpu().numpy(), rmc.ledger_dict(led)
 
 
@@ -58,9 +60,11 @@ def test_rounds_equal_generations(case, tuning):
     elif case in ("map", "equal_count"):
         specs, adj = [P.map_source(P.residual_like_map(ph, seed=3))], True
         kw = {"flags": 2} if case == "equal_count" else {}
-    # grid_max_packets 1: no whole-grid transport (it is the reference where the pool cannot be smaller than the run)
-    _same(_run(ph, specs, n, N, adj, {"grid_max_packets": 1, **tuning}, **kw),
-          _run(ph, specs, n, N, adj, {"grid_max_packets": 1, "live_packets": 1024} if n > 1024 else None, **kw))
+    got = _run(ph, specs, n, N, adj, tuning, **kw)
+    if n > 1024:
+        _same(got, _run(ph, specs, n, N, adj, {"live_packets": 1024}, **kw))
+    else:   # a pool cannot be smaller: against the whole-grid transport
+        _same(got, _run(ph, specs, n, N, adj, noalloc=True, **kw))
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1025])
