@@ -18,7 +18,9 @@
  *    exception and says so).  Results are valid after the caller
  *    synchronises the stream.  Calls on different streams with different
  *    workspaces may run concurrently.  The library holds no mutable global
- *    state: tuning and timing are passed per call (mc_options).
+ *    state (beside the slots that mc_residual and mc_detect take on the device
+ *    for the time of a call): tuning and timing are passed per call
+ *    (mc_options).
  *  - Return value: MC_OK, or an error code; no call throws.  Invalid
  *    arguments are detected on the host before anything is enqueued.
  *    MC_ERR_DEVICE reports a failed launch; faults inside a kernel surface at
