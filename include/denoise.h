@@ -15,6 +15,7 @@
 #ifndef DENOISE_H
 #define DENOISE_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include "mcrad.h"
@@ -32,6 +33,30 @@ extern "C" {
  * the weights flipped in both spatial directions and ci/co swapped. */
 mc_status dn_conv3x3_fwd(const uint16_t *x_d, const uint16_t *w_d, const float *bias_d, float *y_d, int n, int ci,
                          int co, int h, int w, void *stream);
+
+/* The same from FP32 activations as a program holds them: x_d is FP32 with
+ * element strides strides_h = {n, c, h, w}; the values are rounded to BF16
+ * (nearest even) on their way into the product.  w_d: BF16 [co][3][3][cip] as
+ * dn_pack_weights writes it, cip = ci rounded up to a multiple of 8.  xb_d: if
+ * not NULL, receives the BF16 values, [n][h][w][cip] with zeros past ci, for
+ * dn_conv3x3_grads. */
+mc_status dn_conv3x3_f32(const float *x_d, const int64_t *strides_h, const uint16_t *w_d, const float *bias_d, float *y_d,
+                         uint16_t *xb_d, int n, int ci, int co, int h, int w, void *stream);
+
+/* Weights FP32 [co][ci][3][3] to BF16 [co][3][3][cip] (zeros past ci), or with
+ * flip = 1 to those of the gradient with respect to x: [ci][3][3][cop], both
+ * spatial directions reversed. */
+mc_status dn_pack_weights(const float *w_d, uint16_t *out_d, int co, int ci, int flip, void *stream);
+
+/* Gradients of dn_conv3x3_f32 with respect to the weights, FP32
+ * [co][ci][3][3], and (if gb_d is not NULL) the bias, FP32 [co]: xb_d as that
+ * call wrote it, gy_d FP32 [n][h][w][co].  The weight gradient's products take
+ * gy rounded to BF16, the bias gradient sums gy itself.  scratch_d: at least
+ * dn_conv3x3_grads_bytes() bytes (0 on invalid arguments), 16-byte aligned.
+ * The sums' order is fixed: the result is the same every time. */
+size_t dn_conv3x3_grads_bytes(int n, int ci, int co, int h, int w);
+mc_status dn_conv3x3_grads(const uint16_t *xb_d, const float *gy_d, float *gw_d, float *gb_d, void *scratch_d,
+                           size_t scratch_bytes, int n, int ci, int co, int h, int w, void *stream);
 
 /* Weight gradient of dn_conv3x3_fwd:
  *   gw[co][ky][kx][ci] = sum_{n,h,w} gy[n][h][w][co] x[n][h+ky-1][w+kx-1][ci]

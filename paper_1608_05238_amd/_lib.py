@@ -23,7 +23,8 @@ SYMBOLS = ("mc_workspace_bytes", "mc_forward", "mc_adjoint", "mc_residual", "mc_
            "mc_timer_create", "mc_timer_destroy", "mc_timer_read", "mc_batch_workspace_bytes", "mc_run_batch",
            "mc_run_noalloc",
            "mc_binned_workspace_bytes", "mc_run_binned",
-           "mc_status_string", "mc_build_info", "dn_conv3x3_fwd", "dn_conv3x3_wgrad",
+           "mc_status_string", "mc_build_info", "dn_conv3x3_fwd", "dn_conv3x3_f32", "dn_pack_weights",
+           "dn_conv3x3_grads_bytes", "dn_conv3x3_grads", "dn_conv3x3_wgrad",
            "mb_lds_atomics", "mb_global_atomics_f64", "mb_global_atomics_rows_f64", "mb_copy", "mb_fma_f32", "mb_wall_clock_khz")
 (MB_LDS_ADD_F64, MB_LDS_ADD_F32, MB_LDS_ADD_U64, MB_LDS_ADD_U32, MB_LDS_ADD_F64_ROW33, MB_LDS_ADD_U64_ROW33,
  MB_LDS_ADD_U64_PRE) = range(7)
@@ -132,6 +133,14 @@ def load() -> C.CDLL:
     lib.mc_run_binned.restype = St
     lib.dn_conv3x3_fwd.argtypes = [V, V, V, V, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, V]
     lib.dn_conv3x3_fwd.restype = St
+    lib.dn_conv3x3_f32.argtypes = [V, P(C.c_int64), V, V, V, V, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, V]
+    lib.dn_conv3x3_f32.restype = St
+    lib.dn_pack_weights.argtypes = [V, V, C.c_int, C.c_int, C.c_int, V]
+    lib.dn_pack_weights.restype = St
+    lib.dn_conv3x3_grads_bytes.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]
+    lib.dn_conv3x3_grads_bytes.restype = C.c_size_t
+    lib.dn_conv3x3_grads.argtypes = [V, V, V, V, V, C.c_size_t, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, V]
+    lib.dn_conv3x3_grads.restype = St
     lib.dn_conv3x3_wgrad.argtypes = [V, V, V, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, V]
     lib.dn_conv3x3_wgrad.restype = St
     lib.mb_lds_atomics.argtypes = [C.c_int, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint32, V, V, V]

@@ -1,29 +1,25 @@
 // denoise.hip -- BF16 matrix-core kernels of the learned denoiser: 3x3
 // convolution (stride 1, zero padding 1) as an implicit GEMM on the gfx950
-// MFMA units with FP32 accumulation, and its weight gradient.  The input
-// gradient is the forward kernel applied to the flipped, transposed weights.
+// MFMA units with FP32 accumulation, its weight gradient and the gradient of
+// the bias.  The input gradient is the forward kernel applied to the flipped,
+// transposed weights.
 //
 // Layouts (channels last, so that the GEMM's reduction index -- the input
-// channel -- is contiguous): activations [n][h][w][c] BF16 (raw 16-bit
-// patterns) with c a multiple of 8; weights [co][3][3][ci] BF16; outputs and
-// weight gradients FP32 ([n][h][w][co] and [co][3][3][ci]).
+// channel -- is contiguous): BF16 activations [n][h][w][c] (raw 16-bit
+// patterns) with c a multiple of 8; packed weights [co][3][3][ci] BF16; outputs
+// FP32 [n][h][w][co].  FP32 activations may have any strides.
 //
-// Forward GEMM: D[co][p] = sum_{tap, ci} W[co][tap][ci] X[p + off(tap)][ci]
-// for the pixels p of an 8 x 8 block of one image.  The reduction runs over
-// chunks of 32 input channels (the K of v_mfma_f32_16x16x32_bf16) and, within
-// a chunk, over the nine taps: for a tap, B is the chunk's halo tile read at
-// that tap's offset, so each input pixel is loaded from HBM once per chunk.
-// A workgroup of four waves computes 64 output channels x 64 pixels (each
-// wave a 32 x 32 quarter, 2 x 2 MFMA blocks).  Operands are staged in LDS,
-// double buffered: while the waves multiply chunk c out of one buffer, the
-// 16-byte global loads of chunk c + 1 are in flight into registers, which
-// then fill the other buffer (one barrier per chunk).
+// The layers are narrow (24-160 channels), so at full resolution they are
+// bound by memory, and everything is arranged to read an activation once, as
+// the program holds it, and write the result once: FP32 operands are rounded
+// to BF16 on their way into LDS (one pass less over memory than a conversion
+// before), the BF16 copy the backward pass keeps is written beside, and the
+// bias gradient is summed from the same loads as the weight gradient.
 //
 // MFMA lane layout of v_mfma_f32_16x16x32_bf16 (checked on the device):
 // A[m][k] with m = lane % 16, k = 8 (lane / 16) + i, i = 0..7; B[k][n] with
 // n = lane % 16, k = 8 (lane / 16) + i; D[m][n] with n = lane % 16,
-// m = 4 (lane / 16) + i, i = 0..3.  A lane's eight k values of A or B are
-// eight consecutive channels in LDS: one 16-byte read.
+// m = 4 (lane / 16) + i, i = 0..3.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,16 +37,9 @@ constexpr int kCiC = 32;                   // input channels per chunk (the MFMA
 constexpr int kTCo = 64;                   // output channels per workgroup
 constexpr int kTY = 8, kTX = 8;            // output pixels per workgroup
 constexpr int kHY = kTY + 2, kHX = kTX + 2;
-constexpr int kPitch = kCiC + 8;           // LDS pitch (BF16) of one pixel's or one (co, tap)'s chunk: 80 bytes
 constexpr int kXVec = kHY * kHX * (kCiC / 8);      // 16-byte vectors of a halo tile chunk (400)
-constexpr int kWVec = kTCo * 9 * (kCiC / 8);       // 16-byte vectors of a weight chunk (2304)
 constexpr int kThreads = 256;
 constexpr int kXPer = (kXVec + kThreads - 1) / kThreads;   // 2
-constexpr int kWPer = kWVec / kThreads;                    // 9
-static_assert(kWVec % kThreads == 0, "weight chunk split");
-constexpr int kXBuf = kHY * kHX * kPitch;  // BF16 elements of one X buffer
-constexpr int kWBuf = kTCo * 9 * kPitch;   // BF16 elements of one W buffer
-constexpr size_t kFwdLds = 2 * (size_t)(kXBuf + kWBuf) * sizeof(uint16_t);
 
 __device__ __forceinline__ u32x4 load16(const uint16_t *p) {
     return *reinterpret_cast<const u32x4 *>(p);
@@ -61,131 +50,256 @@ __device__ __forceinline__ uint16_t half_of(const u32x4 v, int q) {
     return (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
 }
 
-// Global loads of one chunk (input channels c0 .. c0 + 31) into registers;
-// zeros outside the image, past the last channel or past the last output channel.
-__device__ __forceinline__ void fwd_fetch(const uint16_t *x, const uint16_t *w, int img, int ty0, int tx0, int co0,
-                                          int c0, int Ci, int Co, int H, int W, u32x4 (&rx)[kXPer],
-                                          u32x4 (&rw)[kWPer]) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ uint16_t to_bf16(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
+
+__device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
+    u32x4 r;
 #pragma unroll
-    for (int j = 0; j < kXPer; ++j) {
-        const int v = tid + j * kThreads;
-        u32x4 val = {0u, 0u, 0u, 0u};
-        if (v < kXVec) {
-            const int pix = v >> 2, part = v & 3;
-            const int hy = pix / kHX, hx = pix - hy * kHX;
-            const int gy = ty0 + hy - 1, gx = tx0 + hx - 1, c = c0 + 8 * part;
-            if (gy >= 0 && gy < H && gx >= 0 && gx < W && c < Ci)
-                val = load16(x + (((size_t)img * H + gy) * W + gx) * Ci + c);
-        }
-        rx[j] = val;
-    }
-#pragma unroll
-    for (int j = 0; j < kWPer; ++j) {
-        const int v = tid + j * kThreads;
-        const int row = v >> 2, part = v & 3;   // row = co_l * 9 + tap
-        const int col = row / 9, tap = row - col * 9;
-        const int co = co0 + col, c = c0 + 8 * part;
-        u32x4 val = {0u, 0u, 0u, 0u};
-        if (co < Co && c < Ci) val = load16(w + ((size_t)co * 9 + tap) * Ci + c);
-        rw[j] = val;
-    }
+    for (int i = 0; i < 4; ++i)
+        r[i] = (uint32_t)to_bf16(v[2 * i]) | ((uint32_t)to_bf16(v[2 * i + 1]) << 16);
+    return r;
 }
 
-__device__ __forceinline__ void fwd_stash(uint16_t *sx, uint16_t *sw, const u32x4 (&rx)[kXPer],
-                                          const u32x4 (&rw)[kWPer]) {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < kXPer; ++j) {
-        const int v = tid + j * kThreads;
-        if (v < kXVec) *reinterpret_cast<u32x4 *>(sx + (v >> 2) * kPitch + 8 * (v & 3)) = rx[j];
-    }
-#pragma unroll
-    for (int j = 0; j < kWPer; ++j) {
-        const int v = tid + j * kThreads;
-        *reinterpret_cast<u32x4 *>(sw + (v >> 2) * kPitch + 8 * (v & 3)) = rw[j];
-    }
+// ---- forward
+// GEMM: D[co][p] = sum_{tap, ci} W[co][tap][ci] X[p + off(tap)][ci] for the
+// pixels p of a TS x TS block of one image and 16 MB output channels.  A chunk
+// of U units of 8 input channels (all of them, if they are few) is staged in
+// LDS: the block's halo tile and the weights.  The sums run over groups of 32
+// channels (four units, one MFMA; units past the last read a unit of zeros)
+// and, within a group, over the nine taps.
+// A workgroup of four waves takes block after block; the next block's (or
+// chunk's) activations are in flight in registers while it multiplies, and the
+// weights stay in LDS if there is one chunk.  LDS rows are an odd number of
+// 16-byte units, so the 16 lanes of a read fall into different banks.
+// 16 x 256^2 pixels, 48 -> 48 channels, with the BF16 copy: 125 us = 4.1 TB/s
+// of what it must read and write; a conversion pass (26 us) and a kernel that
+// staged 32-channel chunks of 8 x 8 blocks without overlap took 366 us.
+enum : int { X_F32 = 0, X_STRIDED = 1, X_BF16 = 2 };   // FP32 channels last, 16-byte rows; FP32, any strides; BF16
+
+struct ConvArgs {
+    const void *x;
+    long long sn, sc, sh, sw;   // element strides (X_STRIDED)
+    const uint16_t *w;          // [co][9][cip]
+    const float *bias;
+    float *y;
+    uint16_t *xb;               // BF16 copy of x, [n][h][w][cip], or NULL
+    int ci, cip, co, h, wd;
+    int tiles_x, tiles_y, n_tiles;
+    int units, nchunk;          // units of 8 channels a chunk; chunks
+};
+
+constexpr int kUnitsMax = 6;    // units a chunk may have
+
+constexpr int halo_units(int ts) { return ((ts + 2) * (ts + 2) * kUnitsMax + kThreads - 1) / kThreads; }
+
+size_t conv_lds(int ts, int mb, int units) {
+    return ((size_t)(ts + 2) * (ts + 2) * (units | 1) + (size_t)16 * mb * ((9 * units) | 1) + 1) * 16;
 }
 
-// y[img][gy][gx][co] = bias[co] + sum_{tap, ci} w[co][tap][ci] x[img][gy + ky - 1][gx + kx - 1][ci]
-__global__ void __launch_bounds__(kThreads) k_conv3x3_fwd(const uint16_t *__restrict__ x,
-                                                          const uint16_t *__restrict__ w,
-                                                          const float *__restrict__ bias, float *__restrict__ y,
-                                                          int Ci, int Co, int H, int W, int tiles_x, int tiles_y) {
-    extern __shared__ uint16_t smem[];   // [2][kXBuf] halo tiles, then [2][kWBuf] weight chunks
-    const int t = blockIdx.x;
-    const int img = t / (tiles_x * tiles_y), tt = t - img * tiles_x * tiles_y;
-    const int ty0 = (tt / tiles_x) * kTY, tx0 = (tt % tiles_x) * kTX;
-    const int co0 = blockIdx.y * kTCo;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;   // this wave's quarter: channels, pixels
-    const int kg = lane >> 4, l16 = lane & 15;
-    f32x4 acc[2][2];
+template <int TS, int MB, int KIND>
+__global__ void __launch_bounds__(kThreads, 2) k_conv3x3(ConvArgs A) {
+    constexpr int HS = TS + 2, NPX = HS * HS, NB = TS * TS / 64;   // halo side and pixels; 16-pixel blocks a wave
+    constexpr int NJ = halo_units(TS);                             // activation units a thread stages
+    extern __shared__ u32x4 lds[];
+    const int U = A.units, pu = U | 1, pw = (9 * U) | 1;
+    // several chunks (of 4 units) of 8 x 8 blocks: weights are prefetched too, these units a thread
+    // (16 x 16 blocks have no registers left for them)
+    constexpr int WJ = TS == 8 ? (16 * MB * 37 + kThreads - 1) / kThreads : 1;
+    u32x4 *xs = lds;                       // [NPX][pu]
+    u32x4 *ws = lds + NPX * pu;            // [16 MB][pw]
+    u32x4 *zero = ws + 16 * MB * pw;        // a unit of zeros
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kg = lane >> 4, l16 = lane & 15;
+    const int co0 = blockIdx.y * 16 * MB;
+    const u32x4 none = {0u, 0u, 0u, 0u};
+    if (tid == 0) *zero = none;
+
+    // the staged units of this thread: pixel of the halo and channel group
+    int upix[NJ];   // pixel << 8 | group; -1: none
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // pixel (py, px) of each B block of this lane in the 8 x 8 tile
-    int bpy[2], bpx[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int p = wn + 16 * b + l16;
-        bpy[b] = p >> 3;
-        bpx[b] = p & 7;
+    for (int j = 0; j < NJ; ++j) {
+        const int v = tid + j * kThreads;
+        const int pix = KIND == X_STRIDED ? v % NPX : v / U, part = KIND == X_STRIDED ? v / NPX : v - (v / U) * U;
+        upix[j] = v < NPX * U ? pix << 8 | part : -1;
     }
-    u32x4 rx[kXPer], rw[kWPer];
-    const int nchunk = (Ci + kCiC - 1) / kCiC;
-    fwd_fetch(x, w, img, ty0, tx0, co0, 0, Ci, Co, H, W, rx, rw);
-    fwd_stash(smem, smem + 2 * kXBuf, rx, rw);
-    __syncthreads();
-    for (int c = 0; c < nchunk; ++c) {
-        const int cur = c & 1;
-        if (c + 1 < nchunk) fwd_fetch(x, w, img, ty0, tx0, co0, (c + 1) * kCiC, Ci, Co, H, W, rx, rw);
-        const uint16_t *X = smem + cur * kXBuf, *Wt = smem + 2 * kXBuf + cur * kWBuf;
+    float rf[KIND == X_BF16 ? 1 : NJ][8];
+    u32x4 rb[KIND == X_BF16 ? NJ : 1];
+    auto fetch = [&](int t, int c) {        // block t, chunk c
+        const int per = A.tiles_x * A.tiles_y, img = t / per, tt = t - img * per;
+        const int ty = (tt / A.tiles_x) * TS - 1, tx = (tt % A.tiles_x) * TS - 1;
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int ky = tap / 3, kx = tap - 3 * ky;
-            bf16x8 fa[2], fb[2];
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const u32x4 v = load16(Wt + ((wm + 16 * a + l16) * 9 + tap) * kPitch + 8 * kg);
-                fa[a] = __builtin_bit_cast(bf16x8, v);
-            }
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const u32x4 v = load16(X + ((bpy[b] + ky) * kHX + bpx[b] + kx) * kPitch + 8 * kg);
-                fb[b] = __builtin_bit_cast(bf16x8, v);
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-        }
-        if (c + 1 < nchunk) fwd_stash(smem + (cur ^ 1) * kXBuf, smem + 2 * kXBuf + (cur ^ 1) * kWBuf, rx, rw);
-        __syncthreads();
-    }
-    // D[m][n]: m = 4 kg + i (output channel), n = l16 (pixel)
-    const bool vec = (Co & 3) == 0;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int gy = ty0 + bpy[b], gx = tx0 + bpx[b];
-            const int co = co0 + wm + 16 * a + 4 * kg;
-            if (gy >= H || gx >= W || co >= Co) continue;
-            float *dst = y + (((size_t)img * H + gy) * W + gx) * Co + co;
-            f32x4 v = acc[a][b];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] += (bias && co + i < Co) ? bias[co + i] : 0.f;
-            if (vec) {
-                *reinterpret_cast<f32x4 *>(dst) = v;
+        for (int j = 0; j < NJ; ++j) {
+            const int pix = upix[j] >> 8, ch = (c * U + (upix[j] & 255)) * 8;
+            const int hy = pix / HS, yy = ty + hy, xx = tx + pix - hy * HS;
+            const bool in = upix[j] >= 0 && (unsigned)yy < (unsigned)A.h && (unsigned)xx < (unsigned)A.wd;
+            if constexpr (KIND == X_BF16) {
+                rb[j] = none;
+                if (in && ch < A.cip)
+                    rb[j] = load16((const uint16_t *)A.x + (((size_t)img * A.h + yy) * A.wd + xx) * A.cip + ch);
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (co + i < Co) dst[i] = v[i];
+                for (int i = 0; i < 8; ++i) rf[j][i] = 0.f;
+                if (KIND == X_F32) {
+                    if (in && ch < A.ci) {
+                        const f32x4 *p = (const f32x4 *)((const float *)A.x + (((size_t)img * A.h + yy) * A.wd + xx) * A.ci + ch);
+                        const f32x4 a = p[0], b = p[1];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            rf[j][i] = a[i];
+                            rf[j][4 + i] = b[i];
+                        }
+                    }
+                } else if (in) {
+                    const float *p = (const float *)A.x + img * A.sn + yy * A.sh + xx * A.sw + ch * A.sc;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (ch + i < A.ci) rf[j][i] = p[i * A.sc];
+                }
             }
         }
+    };
+    auto stash = [&](int t, int c) {        // what fetch(t, c) loaded
+        const int per = A.tiles_x * A.tiles_y, img = t / per, tt = t - img * per;
+        const int ty = (tt / A.tiles_x) * TS - 1, tx = (tt % A.tiles_x) * TS - 1;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            if (upix[j] < 0) continue;
+            const int pix = upix[j] >> 8, part = upix[j] & 255;
+            u32x4 v;
+            if constexpr (KIND == X_BF16) v = rb[j];
+            else v = pack8(rf[j]);
+            xs[pix * pu + part] = v;
+            if (KIND != X_BF16 && A.xb && blockIdx.y == 0) {
+                const int hy = pix / HS, hx = pix - hy * HS, ch = (c * U + part) * 8;
+                if (hy >= 1 && hy <= TS && hx >= 1 && hx <= TS && ty + hy < A.h && tx + hx < A.wd && ch < A.cip)
+                    *(u32x4 *)(A.xb + (((size_t)img * A.h + ty + hy) * A.wd + tx + hx) * A.cip + ch) = v;
+            }
+        }
+    };
+    auto weight = [&](int v, int c) {       // unit v of chunk c's weights in LDS
+        const int row = v / pw, g = v - row * pw, tap = g / U, ch = (c * U + g - tap * U) * 8;
+        return co0 + row < A.co && tap < 9 && ch < A.cip ? load16(A.w + ((size_t)(co0 + row) * 9 + tap) * A.cip + ch) : none;
+    };
+    const int wunits = 16 * MB * pw;
+    auto weights = [&](int c) {
+#pragma unroll 4
+        for (int v = tid; v < wunits; v += kThreads) ws[v] = weight(v, c);
+    };
+    u32x4 rw[WJ];
+    auto fetch_w = [&](int c) {
+#pragma unroll
+        for (int j = 0; j < WJ; ++j) rw[j] = weight(std::min(tid + j * kThreads, wunits - 1), c);
+    };
+    auto stash_w = [&] {
+#pragma unroll
+        for (int j = 0; j < WJ; ++j)
+            if (tid + j * kThreads < wunits) ws[tid + j * kThreads] = rw[j];
+    };
+    // first pixel of each of this lane's 16-pixel blocks in the halo tile
+    int base[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int p = (wave * NB + b) * 16 + l16;
+        base[b] = ((p / TS) * HS + p % TS) * pu;
+    }
+    f32x4 acc[MB][NB];
+    int t = blockIdx.x, c = 0;
+    if (t >= A.n_tiles) return;
+    fetch(t, 0);
+    weights(0);
+    stash(t, 0);
+    __syncthreads();
+    for (;;) {
+        int t1 = t, c1 = c + 1;             // what comes next
+        if (c1 == A.nchunk) {
+            c1 = 0;
+            t1 = t + gridDim.x;
+        }
+        if (t1 < A.n_tiles) {
+            fetch(t1, c1);
+            if (TS == 8 && A.nchunk > 1) fetch_w(c1);
+        }
+        if (c == 0) {
+#pragma unroll
+            for (int a = 0; a < MB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int q = 0; 4 * q < U; ++q) {   // a group of 32 channels: this lane's unit is 4 q + kg
+            const int u = 4 * q + kg;
+            const bool in = u < U;
+            const u32x4 *wr = in ? ws + l16 * pw + u : zero;
+            const int wrow = in ? 16 * pw : 0, wtap = in ? U : 0, xcol = in ? pu : 0;
+            const u32x4 *xr[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) xr[b] = in ? xs + base[b] + u : zero;
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) {
+                bf16x8 fa[MB], fb[NB];
+#pragma unroll
+                for (int a = 0; a < MB; ++a) fa[a] = __builtin_bit_cast(bf16x8, wr[a * wrow + tap * wtap]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    fb[b] = __builtin_bit_cast(bf16x8, xr[b][(tap / 3 * HS + tap % 3) * xcol]);
+#pragma unroll
+                for (int a = 0; a < MB; ++a)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+        if (c1 == 0) {                      // the block is done: D[m][n], m = 4 kg + i (channel), n = l16 (pixel)
+            const int per = A.tiles_x * A.tiles_y, img = t / per, tt = t - img * per;
+            const int ty = (tt / A.tiles_x) * TS, tx = (tt % A.tiles_x) * TS;
+            const bool vec = (A.co & 3) == 0;
+#pragma unroll
+            for (int a = 0; a < MB; ++a) {
+                const int co = co0 + 16 * a + 4 * kg;
+                f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+                if (A.bias)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bias[i] = co + i < A.co ? A.bias[co + i] : 0.f;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int p = (wave * NB + b) * 16 + l16, gy = ty + p / TS, gx = tx + p % TS;
+                    if (gy >= A.h || gx >= A.wd || co >= A.co) continue;
+                    float *dst = A.y + (((size_t)img * A.h + gy) * A.wd + gx) * A.co + co;
+                    const f32x4 v = acc[a][b] + bias;
+                    if (vec) {
+                        *(f32x4 *)dst = v;
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (co + i < A.co) dst[i] = v[i];
+                    }
+                }
+            }
+        }
+        if (t1 >= A.n_tiles) break;
+        stash(t1, c1);
+        if (A.nchunk > 1) {
+            if (TS == 8) stash_w();
+            else weights(c1);
+        }
+        __syncthreads();
+        t = t1;
+        c = c1;
+    }
+}
+
+// Weights [co][ci][3][3] FP32 as the forward kernel reads them: BF16
+// [co][9][cip] (zeros past ci), or with `flip` those of the input gradient,
+// [ci][9][cop], both spatial directions reversed.
+__global__ void k_pack_weights(const float *w, uint16_t *out, int co, int ci, int inner, int flip) {
+    const int rows = flip ? ci : co, cols = flip ? co : ci;
+    const size_t total = (size_t)rows * 9 * inner;
+    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < total; v += (size_t)gridDim.x * blockDim.x) {
+        const int line = (int)(v / (size_t)inner), col = (int)(v - (size_t)line * inner);
+        const int row = line / 9, tap = line - row * 9;
+        float x = 0.f;
+        if (col < cols) x = flip ? w[((size_t)col * ci + row) * 9 + 8 - tap] : w[((size_t)row * ci + col) * 9 + tap];
+        out[v] = to_bf16(x);
+    }
 }
 
 // ---- weight gradient
@@ -304,6 +418,201 @@ __global__ void __launch_bounds__(kThreads) k_conv3x3_wgrad(const uint16_t *__re
         }
 }
 
+// ---- weight and bias gradient from what a layer holds
+// As above, from the BF16 copy of x and the FP32 upstream gradient itself.
+// GEMM per tap with M = output channels, N = input channels, K = pixels.  Both
+// operands lie in LDS as they lie in memory, [pixel][channel]; the transpose
+// to eight consecutive pixels of a channel per lane is done by the LDS read
+// (ds_read_b64_tr_b16: 16 lanes read four pixels x 16 channels and each gets
+// its channel's four pixels, checked on the device), so one copy of the halo
+// tile serves the nine taps.  A workgroup holds 16 MB output x 16 NB input
+// channels x nine taps, the (tap, block of input channels) pairs dealt to its
+// four waves, and runs over every gridDim.x-th 16 x 8 pixel block, the next
+// one in flight in registers.  The workgroups' parts are written to a scratch
+// buffer and added in order by k_wgrad_sum: the result does not depend on
+// timing.  16 x 256^2 pixels, 48 x 48 channels: 94 us, the sum 24 us; from a
+// converted copy (26 us), with transposing stores to LDS, three shifted copies
+// of the halo and atomics 267 us, and 86 us for the bias gradient.
+constexpr int kWY = 8, kWX = 16, kWHalo = (kWY + 2) * (kWX + 2);
+
+struct WgradArgs {
+    const uint16_t *x;     // [n][h][w][cip]
+    const float *gy;       // [n][h][w][co]
+    float *part;           // [slices][co tiles][ci tiles][9 NB][MB][256]
+    float *bpart;          // [slices][co tiles][16 MB]
+    int cip, co, h, wd, tiles_x, tiles_y, n_tiles;
+};
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ s16x4 read_tr(const uint16_t *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+}
+
+template <int MB, int NB, bool VEC>
+__global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
+    constexpr int UX = 2 * NB, UG = 2 * MB, PX = UX | 1, PG = UG | 1;   // units of 8 channels, and LDS pitches
+    constexpr int GT = kThreads / UG * UG;                              // threads that stage gy: each keeps its channels
+    constexpr int XJ = (kWHalo * UX + kThreads - 1) / kThreads, GJ = (kWX * kWY * UG + GT - 1) / GT;
+    constexpr int PW = (9 * NB + 3) / 4;                                // (tap, block) pairs of a wave
+    __shared__ u32x4 xs[kWHalo * PX], gs[kWX * kWY * PG];
+    __shared__ float bs[GT * 8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c0 = blockIdx.z * 16 * NB, co0 = blockIdx.y * 16 * MB;
+    const u32x4 none = {0u, 0u, 0u, 0u};
+    const int gpart = tid % UG, gco = co0 + 8 * gpart;
+    u32x4 rx[XJ];
+    float rg[GJ][8], bsum[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) bsum[i] = 0.f;
+    auto fetch = [&](int t) {
+        const int per = A.tiles_x * A.tiles_y, img = t / per, tt = t - img * per;
+        const int ty = (tt / A.tiles_x) * kWY, tx = (tt % A.tiles_x) * kWX;
+#pragma unroll
+        for (int j = 0; j < XJ; ++j) {
+            const int v = tid + j * kThreads, pix = v / UX, part = v - pix * UX;
+            const int hy = pix / (kWX + 2), yy = ty + hy - 1, xx = tx + pix - hy * (kWX + 2) - 1, ch = c0 + 8 * part;
+            rx[j] = none;
+            if (v < kWHalo * UX && (unsigned)yy < (unsigned)A.h && (unsigned)xx < (unsigned)A.wd && ch < A.cip)
+                rx[j] = load16(A.x + (((size_t)img * A.h + yy) * A.wd + xx) * A.cip + ch);
+        }
+#pragma unroll
+        for (int j = 0; j < GJ; ++j) {
+            const int pix = tid / UG + j * (GT / UG), yy = ty + pix / kWX, xx = tx + pix % kWX;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) rg[j][i] = 0.f;
+            if (tid < GT && pix < kWX * kWY && yy < A.h && xx < A.wd && gco < A.co) {
+                const float *p = A.gy + (((size_t)img * A.h + yy) * A.wd + xx) * A.co + gco;
+                if constexpr (VEC) {
+                    const f32x4 a = *(const f32x4 *)p, b = *(const f32x4 *)(p + 4);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        rg[j][i] = a[i];
+                        rg[j][4 + i] = b[i];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (gco + i < A.co) rg[j][i] = p[i];
+                }
+            }
+        }
+    };
+    auto stash = [&]() {
+#pragma unroll
+        for (int j = 0; j < XJ; ++j) {
+            const int v = tid + j * kThreads, pix = v / UX, part = v - pix * UX;
+            if (v < kWHalo * UX) xs[pix * PX + part] = rx[j];
+        }
+        if (tid < GT)
+#pragma unroll
+            for (int j = 0; j < GJ; ++j) {
+                const int pix = tid / UG + j * (GT / UG);
+                if (pix >= kWX * kWY) continue;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) bsum[i] += rg[j][i];
+                gs[pix * PG + gpart] = pack8(rg[j]);
+            }
+    };
+    f32x4 acc[PW][MB];
+#pragma unroll
+    for (int i = 0; i < PW; ++i)
+#pragma unroll
+        for (int a = 0; a < MB; ++a) acc[i][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // a read of four pixels x 16 channels per 16 lanes: lane's pixel 4 (lane / 16) + (lane % 16) / 4, channels 4 (lane % 4)
+    const int rpix = 4 * (lane >> 4) + ((lane & 15) >> 2), rch = 4 * (lane & 3);
+    const uint16_t *gr = (const uint16_t *)gs + rpix * PG * 8 + rch;
+    const uint16_t *xr[PW];
+#pragma unroll
+    for (int i = 0; i < PW; ++i) {
+        const int p = min(wave + 4 * i, 9 * NB - 1), tap = p / NB, nb = p - tap * NB;   // (a wave's last pair may repeat)
+        xr[i] = (const uint16_t *)xs + ((tap / 3) * (kWX + 2) + tap % 3 + rpix) * PX * 8 + 16 * nb + rch;
+    }
+    int t = blockIdx.x;
+    if (t < A.n_tiles) {
+        fetch(t);
+        stash();
+    }
+    __syncthreads();
+    for (; t < A.n_tiles; t += gridDim.x) {
+        const bool next = t + (int)gridDim.x < A.n_tiles;
+        if (next) fetch(t + gridDim.x);
+#pragma unroll
+        for (int s = 0; s < kWY / 2; ++s) {   // 32 pixels: rows 2 s and 2 s + 1
+            s16x8 fa[MB];
+#pragma unroll
+            for (int a = 0; a < MB; ++a) {
+                const uint16_t *q = gr + (2 * s * kWX) * PG * 8 + 16 * a;
+                fa[a] = __builtin_shufflevector(read_tr(q), read_tr(q + kWX * PG * 8), 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                const uint16_t *q = xr[i] + (2 * s * (kWX + 2)) * PX * 8;
+                const s16x8 fb =
+                    __builtin_shufflevector(read_tr(q), read_tr(q + (kWX + 2) * PX * 8), 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+                for (int a = 0; a < MB; ++a)
+                    acc[i][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[a]),
+                                                                        __builtin_bit_cast(bf16x8, fb), acc[i][a], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+        if (next) stash();
+        __syncthreads();
+    }
+    float *out = A.part + (((size_t)blockIdx.x * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z) * (9 * NB * MB * 256);
+#pragma unroll
+    for (int i = 0; i < PW; ++i)
+        if (wave + 4 * i < 9 * NB)
+#pragma unroll
+            for (int a = 0; a < MB; ++a) *(f32x4 *)(out + ((wave + 4 * i) * MB + a) * 256 + 4 * lane) = acc[i][a];
+    if (blockIdx.z == 0) {
+        if (tid < GT)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) bs[tid * 8 + i] = bsum[i];
+        __syncthreads();
+        if (tid < 16 * MB) {   // channel tid: unit tid / 8 of the threads that staged it
+            double v = 0.;
+            for (int k = tid >> 3; k < GT; k += UG) v += bs[k * 8 + (tid & 7)];
+            A.bpart[((size_t)blockIdx.x * gridDim.y + blockIdx.y) * (16 * MB) + tid] = (float)v;
+        }
+    }
+}
+
+// gw[co][ci][3][3] and gb[co] from the slices' parts.  Sixteen lanes share a
+// value's slices; the sums over slices are FP64 (rounding is then that of the
+// parts: relative error of the bias gradient of 16 x 256^2 pixels 3e-8).
+__global__ void __launch_bounds__(256) k_wgrad_sum(const float *part, const float *bpart, float *gw, float *gb, int slices,
+                                                   int ty, int tz, int mb, int nb, int co, int ci) {
+    const int frag = 9 * nb * mb * 256, bt = ty * 16 * mb;   // a workgroup's 16 values are of one tile
+    const long long total = (long long)ty * tz * frag, v = blockIdx.x * 16ll + (threadIdx.x >> 4);
+    const int sub = threadIdx.x & 15;
+    const float *src = nullptr;
+    size_t step = 0;
+    if (v < total) {
+        src = part + v;
+        step = total;
+    } else if (v < total + bt) {
+        src = bpart + (v - total);
+        step = bt;
+    }
+    double sum = 0.;
+    if (src)
+        for (int k = sub; k < slices; k += 16) sum += src[(size_t)k * step];
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (sub != 0 || !src) return;
+    if (v < total) {
+        const int tile = blockIdx.x / (frag / 16), e = (int)(v - (long long)tile * frag), pair = e / (mb * 256), a = e / 256 - pair * mb, l = (e & 255) >> 2;
+        const int c = (tile / tz) * 16 * mb + 16 * a + 4 * (l >> 4) + (e & 3);
+        const int k = (tile % tz) * 16 * nb + 16 * (pair % nb) + (l & 15);
+        if (c < co && k < ci) gw[((size_t)c * ci + k) * 9 + pair / nb] = (float)sum;
+    } else if (v - total < co && gb) {
+        gb[v - total] = (float)sum;
+    }
+}
+
 __global__ void k_zero_f32(float *p, size_t n) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0.f;
@@ -324,6 +633,110 @@ mc_status set_lds(const void *fn, size_t bytes) {
                : MC_ERR_DEVICE;
 }
 
+// ---- plans
+using ConvFn = void (*)(ConvArgs);
+using WgradFn = void (*)(WgradArgs);
+
+template <int TS, int KIND>
+ConvFn conv_of(int mb) {
+    return mb == 1 ? k_conv3x3<TS, 1, KIND> : mb == 2 ? k_conv3x3<TS, 2, KIND> : mb == 3 ? k_conv3x3<TS, 3, KIND>
+                                                                                        : k_conv3x3<TS, 4, KIND>;
+}
+
+ConvFn conv_fn(int ts, int mb, int kind) {
+    if (ts == 16) return kind == X_F32 ? conv_of<16, X_F32>(mb) : kind == X_BF16 ? conv_of<16, X_BF16>(mb) : conv_of<16, X_STRIDED>(mb);
+    return kind == X_F32 ? conv_of<8, X_F32>(mb) : kind == X_BF16 ? conv_of<8, X_BF16>(mb) : conv_of<8, X_STRIDED>(mb);
+}
+
+// Blocks of 16 channels per workgroup: the count that pads `c` channels least,
+// the largest of those.
+int blocks_for(int c, int most) {
+    int best = 1, pad = 1 << 30;
+    for (int b = 1; b <= most; ++b) {
+        const int p = (c + 16 * b - 1) / (16 * b) * b;
+        if (p <= pad) {
+            pad = p;
+            best = b;
+        }
+    }
+    return best;
+}
+
+mc_status run_conv(ConvArgs A, int kind, int n, hipStream_t s) {
+    // 16 x 16 pixel blocks and all output channels up to 64 in a workgroup read
+    // least (16 x 256^2 pixels, 48 -> 48: 117 us; 8 x 8 blocks 151; 32 channels
+    // a workgroup 141).  With less than two workgroups a CU, 32 channels each
+    // (16 x 64^2, 64 -> 64: 18 us, with 64 channels 23; 3 x 128^2: 17 and 21).
+    // With less than one a CU then, 8 x 8 blocks, and fewer channels until
+    // every CU has one (3 x 64^2, 48 -> 48: 8.3 us, 16 x 16 blocks 10.6; 3 x 32^2,
+    // 64 -> 64: 6.3 against 12.8, with 64 channels 11.5; 3 x 8^2, 128 -> 128:
+    // 8.8 against 20.5, with 64 channels 16.1).
+    const int mb0 = blocks_for(A.co, 4);
+    int ts = 16, mb = mb0;
+    auto groups = [&](int t, int m) {
+        return (long long)n * ((A.h + t - 1) / t) * ((A.wd + t - 1) / t) * ((A.co + 16 * m - 1) / (16 * m));
+    };
+    if (groups(16, mb) < 512) mb = std::min(mb, 2);
+    if (groups(16, mb) < 256) {
+        ts = 8;
+        for (mb = mb0; mb > 1 && groups(8, mb) < 256;) --mb;
+    }
+    const int most = mb >= 4 ? 4 : kUnitsMax;   // chunks that leave room for two workgroups a CU
+    const int total = A.cip / 8;
+    A.units = total <= most ? total : 4;        // several chunks: whole groups of 32 channels
+    A.nchunk = (total + A.units - 1) / A.units;
+    A.tiles_x = (A.wd + ts - 1) / ts;
+    A.tiles_y = (A.h + ts - 1) / ts;
+    const long long tiles = (long long)n * A.tiles_x * A.tiles_y;
+    const int gco = (A.co + 16 * mb - 1) / (16 * mb);
+    if (tiles >= (1ll << 31) || gco > 65535) return MC_ERR_UNSUPPORTED;
+    A.n_tiles = (int)tiles;
+    const size_t lds = conv_lds(ts, mb, A.units);
+    const ConvFn fn = conv_fn(ts, mb, kind);
+    const mc_status st = set_lds(reinterpret_cast<const void *>(fn), lds);
+    if (st != MC_OK) return st;
+    // two workgroups a CU, each taking several blocks: the weights are staged
+    // once and the next block's loads overlap the products
+    const long long most_groups = std::max(1, (ts == 16 ? 2 : 4) * 256 / gco);
+    const long long rounds = (tiles + most_groups - 1) / most_groups;
+    const unsigned gx = (unsigned)((tiles + rounds - 1) / rounds);
+    hipLaunchKernelGGL(fn, dim3(gx, (unsigned)gco), dim3(kThreads), lds, s, A);
+    return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+}
+
+template <int MB, bool VEC>
+WgradFn wgrad_of(int nb) {
+    return nb == 1 ? k_wgrad<MB, 1, VEC> : nb == 2 ? k_wgrad<MB, 2, VEC> : k_wgrad<MB, 3, VEC>;
+}
+
+WgradFn wgrad_fn(int mb, int nb, bool vec) {
+    if (vec) return mb == 1 ? wgrad_of<1, true>(nb) : mb == 2 ? wgrad_of<2, true>(nb) : wgrad_of<3, true>(nb);
+    return mb == 1 ? wgrad_of<1, false>(nb) : mb == 2 ? wgrad_of<2, false>(nb) : wgrad_of<3, false>(nb);
+}
+
+struct WgradPlan {
+    int mb, nb, ty, tz, slices;
+    size_t part_floats() const { return (size_t)slices * ty * tz * 9 * nb * mb * 256; }
+    size_t bias_floats() const { return (size_t)slices * ty * 16 * mb; }
+    long long sum_blocks() const { return ((long long)ty * tz * 9 * nb * mb * 256 + (long long)ty * 16 * mb + 15) / 16; }
+};
+
+// Two workgroups a CU over all channel tiles, no more than there are blocks; up
+// to 48 x 48 channels each (more would not fit the registers beside the next
+// block's loads).
+WgradPlan wgrad_plan(int n, int ci, int co, int h, int w) {
+    WgradPlan P;
+    P.mb = blocks_for(co, 3);
+    P.nb = blocks_for(ci, 3);
+    P.ty = (co + 16 * P.mb - 1) / (16 * P.mb);
+    P.tz = (ci + 16 * P.nb - 1) / (16 * P.nb);
+    const long long tiles = (long long)n * ((w + kWX - 1) / kWX) * ((h + kWY - 1) / kWY);
+    const long long most = std::max<long long>(1, 512 / ((long long)P.ty * P.tz));
+    const long long rounds = (tiles + most - 1) / most;
+    P.slices = (int)((tiles + rounds - 1) / rounds);
+    return P;
+}
+
 }  // namespace
 
 extern "C" {
@@ -333,14 +746,85 @@ mc_status dn_conv3x3_fwd(const uint16_t *x_d, const uint16_t *w_d, const float *
     if (!x_d || !w_d || !y_d || !dims_ok(n, ci, co, h, w) || (ci & 7) || !aligned16(x_d) || !aligned16(w_d) ||
         ((co & 3) == 0 && !aligned16(y_d)))
         return MC_ERR_INVALID_ARG;
-    const int tx = (w + kTX - 1) / kTX, ty = (h + kTY - 1) / kTY;
-    const long long tiles = (long long)n * tx * ty;
-    const unsigned gco = (unsigned)((co + kTCo - 1) / kTCo);
-    if (gco > 65535) return MC_ERR_UNSUPPORTED;
-    mc_status st = set_lds(reinterpret_cast<const void *>(k_conv3x3_fwd), kFwdLds);
-    if (st != MC_OK) return st;
-    hipLaunchKernelGGL(k_conv3x3_fwd, dim3((unsigned)tiles, gco), dim3(kThreads), kFwdLds,
-                       reinterpret_cast<hipStream_t>(stream), x_d, w_d, bias_d, y_d, ci, co, h, w, tx, ty);
+    ConvArgs A{};
+    A.x = x_d;
+    A.w = w_d;
+    A.bias = bias_d;
+    A.y = y_d;
+    A.ci = A.cip = ci;
+    A.co = co;
+    A.h = h;
+    A.wd = w;
+    return run_conv(A, X_BF16, n, reinterpret_cast<hipStream_t>(stream));
+}
+
+mc_status dn_conv3x3_f32(const float *x_d, const int64_t *strides, const uint16_t *w_d, const float *bias_d, float *y_d,
+                         uint16_t *xb_d, int n, int ci, int co, int h, int w, void *stream) {
+    if (!x_d || !strides || !w_d || !y_d || !dims_ok(n, ci, co, h, w) || !aligned16(w_d) ||
+        (xb_d && !aligned16(xb_d)) || ((co & 3) == 0 && !aligned16(y_d)))
+        return MC_ERR_INVALID_ARG;
+    ConvArgs A{};
+    A.x = x_d;
+    A.sn = strides[0];
+    A.sc = strides[1];
+    A.sh = strides[2];
+    A.sw = strides[3];
+    A.w = w_d;
+    A.bias = bias_d;
+    A.y = y_d;
+    A.xb = xb_d;
+    A.ci = ci;
+    A.cip = (ci + 7) & ~7;
+    A.co = co;
+    A.h = h;
+    A.wd = w;
+    // whole units of eight channels, rows of 16 bytes: two 16-byte loads a unit
+    const bool vec = (ci & 7) == 0 && aligned16(x_d) && A.sc == 1 && A.sw == ci && A.sh == (int64_t)w * ci &&
+                     A.sn == (int64_t)h * w * ci;
+    return run_conv(A, vec ? X_F32 : X_STRIDED, n, reinterpret_cast<hipStream_t>(stream));
+}
+
+mc_status dn_pack_weights(const float *w_d, uint16_t *out_d, int co, int ci, int flip, void *stream) {
+    if (!w_d || !out_d || co < 1 || ci < 1 || co > (1 << 16) || ci > (1 << 16) || (flip != 0 && flip != 1))
+        return MC_ERR_INVALID_ARG;
+    const int inner = ((flip ? co : ci) + 7) & ~7;
+    const long long total = (long long)(flip ? ci : co) * 9 * inner;
+    hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)std::min<long long>((total + 255) / 256, 1024)), dim3(256), 0,
+                       reinterpret_cast<hipStream_t>(stream), w_d, out_d, co, ci, inner, flip);
+    return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+}
+
+size_t dn_conv3x3_grads_bytes(int n, int ci, int co, int h, int w) {
+    if (!dims_ok(n, ci, co, h, w)) return 0;
+    const WgradPlan P = wgrad_plan(n, ci, co, h, w);
+    return P.ty > 65535 || P.tz > 65535 || P.sum_blocks() >= (1ll << 31) ? 0 : P.part_floats() * sizeof(float) + P.bias_floats() * sizeof(float);
+}
+
+mc_status dn_conv3x3_grads(const uint16_t *xb_d, const float *gy_d, float *gw_d, float *gb_d, void *scratch_d,
+                           size_t scratch_bytes, int n, int ci, int co, int h, int w, void *stream) {
+    if (!xb_d || !gy_d || !gw_d || !dims_ok(n, ci, co, h, w) || !aligned16(xb_d) || (reinterpret_cast<uintptr_t>(gy_d) & 3))
+        return MC_ERR_INVALID_ARG;
+    const size_t need = dn_conv3x3_grads_bytes(n, ci, co, h, w);
+    if (!need) return MC_ERR_UNSUPPORTED;
+    if (!scratch_d || scratch_bytes < need || !aligned16(scratch_d)) return MC_ERR_WORKSPACE;
+    const WgradPlan P = wgrad_plan(n, ci, co, h, w);
+    const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    WgradArgs A{};
+    A.x = xb_d;
+    A.gy = gy_d;
+    A.part = static_cast<float *>(scratch_d);
+    A.bpart = A.part + P.part_floats();
+    A.cip = (ci + 7) & ~7;
+    A.co = co;
+    A.h = h;
+    A.wd = w;
+    A.tiles_x = (w + kWX - 1) / kWX;
+    A.tiles_y = (h + kWY - 1) / kWY;
+    A.n_tiles = n * A.tiles_x * A.tiles_y;
+    const bool vec = (co & 7) == 0 && aligned16(gy_d);
+    wgrad_fn(P.mb, P.nb, vec)<<<dim3(P.slices, P.ty, P.tz), dim3(kThreads), 0, s>>>(A);
+    hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)P.sum_blocks()), dim3(256), 0, s, A.part, A.bpart, gw_d, gb_d, P.slices,
+                       P.ty, P.tz, P.mb, P.nb, co, ci);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 

@@ -42,64 +42,80 @@ def _pad8(n: int) -> int:
     return (n + 7) // 8 * 8
 
 
-def _nhwc_bf16(t: torch.Tensor, c_pad: int) -> torch.Tensor:
-    """[n][c][h][w] as BF16 in channels-last storage ([n][h][w][c] in memory),
-    zero channels appended up to c_pad."""
-    t = t.detach().to(torch.bfloat16)
-    if c_pad > t.shape[1]:
-        t = F.pad(t, (0, 0, 0, 0, 0, c_pad - t.shape[1]))
-    return t.contiguous(memory_format=torch.channels_last)
+def _packed(w: torch.Tensor, flip: bool) -> torch.Tensor:
+    """Weights [co][ci][3][3] as the kernels read them (dn_pack_weights)."""
+    co, ci = w.shape[:2]
+    rows, cols = (ci, _pad8(co)) if flip else (co, _pad8(ci))
+    w = w.detach()
+    if w.dtype != torch.float32:   # rounded to BF16 once, from its own type
+        w = w.to(torch.bfloat16).float()
+    w = w.contiguous()
+    out = torch.empty((rows, 3, 3, cols), dtype=torch.bfloat16, device=w.device)
+    L.check("dn_pack_weights", L.load().dn_pack_weights(w.data_ptr(), out.data_ptr(), co, ci, int(flip), _stream()))
+    return out
+
+
+def _conv(x: torch.Tensor, wp: torch.Tensor, bias, co: int, keep: bool):
+    """dn_conv3x3_f32 of an FP32 tensor [n][c][h][w] of any strides; returns
+    the FP32 result (channels last) and, with keep, the BF16 copy of x."""
+    n, ci, h, wd = x.shape
+    y = torch.empty((n, co, h, wd), dtype=torch.float32, device=x.device, memory_format=torch.channels_last)
+    xb = torch.empty((n, h, wd, _pad8(ci)), dtype=torch.bfloat16, device=x.device) if keep else None
+    L.check("dn_conv3x3_f32",
+            L.load().dn_conv3x3_f32(x.data_ptr(), (C.c_int64 * 4)(*x.stride()), wp.data_ptr(),
+                                    None if bias is None else bias.data_ptr(), y.data_ptr(),
+                                    None if xb is None else xb.data_ptr(), n, ci, co, h, wd, _stream()))
+    return y, xb
 
 
 class _Conv3x3(torch.autograd.Function):
     """3x3 convolution, stride 1, padding 1, with BF16 operands on the MFMA
-    units.  The kernels take channels-last data with a multiple of 8 channels:
-    the operands are converted here (channels padded with zeros); outputs are
-    channels-last FP32 tensors."""
+    units.  The kernels take FP32 activations as they are and round them on the
+    way in; outputs are channels-last FP32 tensors.  `keep` says whether a
+    backward pass may follow (the BF16 copy of x is written only then)."""
 
     @staticmethod
-    def forward(ctx, x, w, b):
-        lib = L.load()
-        n, ci, h, wd = x.shape
-        co = w.shape[0]
-        cip = _pad8(ci)
-        xb = _nhwc_bf16(x, cip)
-        wb = F.pad(w.detach().to(torch.bfloat16), (0, 0, 0, 0, 0, cip - ci)).permute(0, 2, 3, 1).contiguous()
-        y = torch.empty((n, co, h, wd), dtype=torch.float32, device=x.device, memory_format=torch.channels_last)
-        bias = b.detach().float().contiguous()
-        L.check("dn_conv3x3_fwd", lib.dn_conv3x3_fwd(xb.data_ptr(), wb.data_ptr(), bias.data_ptr(), y.data_ptr(),
-                                                     n, cip, co, h, wd, _stream()))
+    def forward(ctx, x, w, b, keep):
+        x = x.detach()
+        if x.dtype != torch.float32:   # rounded to BF16 once, from its own type
+            x = x.to(torch.bfloat16).float()
+        y, xb = _conv(x, _packed(w, False), b.detach().float().contiguous(), w.shape[0],
+                      keep and ctx.needs_input_grad[1])
         ctx.save_for_backward(xb, w.detach())
-        ctx.shape = (n, ci, co, h, wd)
+        ctx.shape = tuple(x.shape)
         return y
 
     @staticmethod
     def backward(ctx, gy):
         lib = L.load()
         xb, w = ctx.saved_tensors
-        n, ci, co, h, wd = ctx.shape
-        cip, cop = _pad8(ci), _pad8(co)
-        gyb = _nhwc_bf16(gy, cop)
+        n, ci, h, wd = ctx.shape
+        co = w.shape[0]
+        gy = gy.detach().float()
         gx = gw = gb = None
         if ctx.needs_input_grad[0]:
             # the input gradient: the same convolution with the weights flipped
-            # and input / output channels swapped, [ci][3][3][co]
-            wt = F.pad(w.to(torch.bfloat16).flip(2, 3).permute(1, 2, 3, 0), (0, cop - co)).contiguous()
-            gx = torch.empty((n, ci, h, wd), dtype=torch.float32, device=gy.device, memory_format=torch.channels_last)
-            L.check("dn_conv3x3_fwd", lib.dn_conv3x3_fwd(gyb.data_ptr(), wt.data_ptr(), None, gx.data_ptr(),
-                                                         n, cop, ci, h, wd, _stream()))
+            # and input / output channels swapped
+            gx, _ = _conv(gy, _packed(w, True), None, ci, False)
         if ctx.needs_input_grad[1]:
-            g = torch.empty((cop, 3, 3, cip), dtype=torch.float32, device=gy.device)
-            L.check("dn_conv3x3_wgrad", lib.dn_conv3x3_wgrad(xb.data_ptr(), gyb.data_ptr(), g.data_ptr(),
-                                                             n, cip, cop, h, wd, _stream()))
-            gw = g[:co, :, :, :ci].permute(0, 3, 1, 2).contiguous()
-        if ctx.needs_input_grad[2]:
+            gl = gy.contiguous(memory_format=torch.channels_last)
+            if gl.stride() != (co * h * wd, 1, co * wd, co):   # a size of one leaves its stride open
+                gl = gl.permute(0, 2, 3, 1).reshape(n, h, wd, co).contiguous()
+            gw = torch.empty((co, ci, 3, 3), dtype=torch.float32, device=gy.device)
+            gb = torch.empty(co, dtype=torch.float32, device=gy.device) if ctx.needs_input_grad[2] else None
+            need = lib.dn_conv3x3_grads_bytes(n, ci, co, h, wd)
+            ws = torch.empty(max(need, 16), dtype=torch.uint8, device=gy.device)
+            L.check("dn_conv3x3_grads",
+                    lib.dn_conv3x3_grads(xb.data_ptr(), gl.data_ptr(), gw.data_ptr(),
+                                         None if gb is None else gb.data_ptr(), ws.data_ptr(), ws.numel(), n, ci, co, h,
+                                         wd, _stream()))
+        elif ctx.needs_input_grad[2]:
             gb = gy.sum(dim=(0, 2, 3))
-        return gx, gw, gb
+        return gx, gw, gb, None
 
 
 def conv3x3(x, w, b):
-    return _Conv3x3.apply(x, w, b)
+    return _Conv3x3.apply(x, w, b, torch.is_grad_enabled())
 
 
 class Conv3x3(nn.Module):
