@@ -146,8 +146,8 @@ typedef struct {
  *  tile           tile side in pixels, 1 .. 256 (default, or a tile whose
  *                 tally does not fit: the largest square tile whose tally
  *                 fits the LDS of one workgroup per CU, 23 at N = 16)
- *  finish_packets once every packet is launched and at most twice this many
- *                 remain they finish without migration, in rounds of walk
+ *  finish_packets once every packet is launched and at most eight times this
+ *                 many remain they finish without migration, in rounds of walk
  *                 and tally (mc_run_noalloc: at most this many, in one
  *                 kernel).  A run of few packets that the pool holds at once
  *                 does so from its launch.  (default: the smaller of 2^16

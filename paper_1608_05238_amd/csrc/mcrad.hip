@@ -229,7 +229,8 @@ struct LedgerRegs {
 struct LedgerTile {
     double absorbed = 0;
     float escaped = 0.f, gain = 0.f, loss = 0.f;
-    uint32_t segments = 0, visits = 0, scatters = 0;
+    uint32_t segments = 0;   // of the wave
+    uint32_t scatters = 0;
 };
 
 // h = [1, cos t .. cos Nt, sin t .. sin Nt] for the direction (sin t, cos t)
@@ -441,6 +442,51 @@ __device__ __forceinline__ int step(const PP &P, Packet &p, const float4 m, floa
     return scat ? EV_SCATTER : (out ? EV_ESCAPE : EV_CROSS);
 }
 
+// The same for kernels that keep what depends on the direction alone from one
+// scatter to the next, operation by operation as the compiler fuses step()
+// (so that a visit's sums are the same bits).  Along x, a packet's face is at
+// gx and the pixel behind it dx away, the same along z.  The distance to a
+// face it does not move towards is an infinity or, on that face, NaN, which
+// the minimum ignores.
+struct Ahead {
+    float gx, gz;
+    int dx, dz;
+};
+
+__device__ __forceinline__ Ahead ahead_of(float sx, float sz) {
+    return Ahead{sx > 0.f ? 1.f : 0.f, sz > 0.f ? 1.f : 0.f, sx > 0.f ? 1 : -1, sz > 0.f ? 1 : -1};
+}
+
+struct Segment {
+    float T, dw;       // see step()
+    bool at, cx, cz;   // ends at a scatter site; at a face across x, across z (both at a corner)
+};
+
+__device__ __forceinline__ Segment segment(Packet &p, const Ahead &a, const float4 &m) {
+#pragma clang fp contract(off)
+    Segment s;
+    const float dfx = fabsf(a.gx - p.fx) * fabsf(p.isx), dfz = fabsf(a.gz - p.fz) * fabsf(p.isz);
+    const float d = fminf(dfx, dfz);
+    const float od = m.y * d;
+    s.at = od > p.tau;
+    const float l = s.at ? p.tau * m.z : d;
+    const float x = m.x * l;
+    const float wf = p.w * absorbed_per_depth(x);
+    s.dw = wf * x;
+    s.T = wf * l;
+    p.w = fmaf(-x, wf, p.w);
+    s.cx = !s.at & (dfx == d);
+    s.cz = !s.at & (dfz == d);
+    const float nfx = fminf(fmaxf(fmaf(p.sx, l, p.fx), 0.f), 1.f);
+    const float nfz = fminf(fmaxf(fmaf(p.sz, l, p.fz), 0.f), 1.f);
+    p.tau = p.tau - od;   // (a scatter replaces it)
+    p.ix += s.cx ? a.dx : 0;
+    p.iz += s.cz ? a.dz : 0;
+    p.fx = s.cx ? 1.f - a.gx : nfx;
+    p.fz = s.cz ? 1.f - a.gz : nfz;
+    return s;
+}
+
 // sin(pi x) for |x| <= 1/2: the Taylor series of sin t at t = pi x, with pi
 // folded into the coefficients and truncated after t^13 (remainder below
 // (pi/2)^15/15! ~ 7e-10).  Both scatter factors use it: the cosine as
@@ -621,9 +667,13 @@ __device__ __forceinline__ void ledger_flush_tile(double *led, unsigned long lon
     R.escaped = L.escaped;
     R.gain = L.gain;
     R.loss = L.loss;
-    R.segments = L.segments;
-    R.visits = L.visits;
     R.scatters = L.scatters;
+    if (__lane_id() == 0) R.segments = L.segments;
+    // a segment that does not end in a scatter ends a visit
+    uint32_t sc = L.scatters;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sc += __shfl_xor(sc, off);
+    if (__lane_id() == 0) R.visits = L.segments - sc;
     ledger_flush_block(led, ledc, R);
 }
 
@@ -889,23 +939,51 @@ __device__ __forceinline__ void slice_close(const Gen &G, int pool, QueueSlice &
         if (q.base + i < G.cap_c) G.ptile[pool][q.base + i] = kInvalidTile;
 }
 
+// Lanes of the mask below this one.
+__device__ __forceinline__ uint32_t rank_in(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Pairs lanes that want something with lanes that give it, as many as there
+// are of both.  src: the giver's number in a lane that gets something; this
+// lane's own number in one without a partner, and that plus 64 in a giver.
+// Returns false if there is no pair (every lane of the wave calls it).
+__device__ __forceinline__ bool pair_lanes(bool want, bool give, int &src) {
+    const unsigned long long w = __ballot(want), g = __ballot(give);
+    src = __lane_id();
+    if (!w || !g) return false;
+    const int n = min(__popcll(w), __popcll(g)), lane = __lane_id();
+    const int rw = (int)rank_in(w), rg = (int)rank_in(g);
+    // lane r learns the number of the r-th giver
+    const int giver = __builtin_amdgcn_ds_permute(4 * (give ? rg : __popcll(g) + lane - rg), lane);
+    const int from = __shfl(giver, rw & 63);
+    if (want && rw < n) src = from;
+    if (give && rg < n) src = lane + 64;
+    return true;
+}
+
+// Adds n to a counter once for the wave and returns its old value, the same
+// in every lane (every lane of the wave calls it).
+__device__ __forceinline__ uint32_t wave_claim(uint32_t *counter, uint32_t n) {
+    uint32_t b = 0;
+    if (__lane_id() == 0) b = atomicAdd(counter, n);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+}
+
 // Appends the packet of every lane with `put` set to the pool's carried region.
 __device__ __forceinline__ void slice_put(const Gen &G, int pool, QueueSlice &q, bool put, const Packet &p,
                                           uint32_t tile, uint32_t prob) {
     const unsigned long long m = __ballot(put);
     if (!m) return;
     const int n = __popcll(m);
-    const int lane = __lane_id();
     if (!q.valid || q.used + n > G.slice) {
         slice_close(G, pool, q);
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&G.ctl->nc[pool], G.slice);
-        q.base = __shfl(base, 0);
+        q.base = wave_claim(&G.ctl->nc[pool], G.slice);
         q.used = 0;
         q.valid = true;
     }
     if (put) {
-        const uint32_t pos = q.base + q.used + __popcll(m & ((1ull << lane) - 1ull));
+        const uint32_t pos = q.base + q.used + rank_in(m);
         if (pos < G.cap_c) {
             rec_store(G.pool[pool] + pos, p, tile, prob);
             G.ptile[pool][pos] = tile;
@@ -1314,6 +1392,27 @@ __global__ void __launch_bounds__(256) k_gen_scatter(Gen G, int g) {
 }
 
 // ---- generation step 3: move the packets tile by tile
+// Bound by vector issue (95% busy at 4 waves per SIMD): a pass of the inner
+// loop, one segment of every lane, is ~295 vector instructions at N = 16, of
+// which 64 add the segment to the visit's sums, 70 add a finished visit to the
+// tally and 98 deflect, though about half the lanes do either.  So what counts
+// is how many instructions a pass has and how many lanes it moves:
+//  * the stays (records put and taken, claims) are looked after every
+//    kTilePasses passes only, ~125 instructions a time (2 and 8 passes: 622
+//    and 639 ms against 615 for 1e8 packets on a 256^2 disc);
+//  * a pass runs under the mask of the lanes that move, each part under that
+//    of the lanes that need it: no result is selected away;
+//  * conditions of the loop are uniform to the compiler (read through lane 0):
+//    else it keeps a second copy of the sums (80 registers spilled);
+//  * when a job has no more packets, free lanes take over what others hold
+//    ahead (pair_lanes): 618 -> 601 ms; a large job turns quiet early.
+// Lanes idle in 15% of the passes of that run (a third of it each: between two
+// stays, before a job turns quiet, after).  It takes 600 ms, 697 before all
+// of this; 2.83e6 packets of a gradient 145 -> 119; 1e8 of a 32^2 pencil beam
+// 119 -> 91.  (Computing the random blocks of several lanes ahead did not pay:
+// lanes use them at once, so some lane is always without.)
+constexpr int kTilePasses = 4;   // segments between two looks at the stays
+
 template <int NH>
 __global__ void __launch_bounds__(tile_block(NH)) __attribute__((amdgpu_waves_per_eu(NH <= 16 ? 4 : 2)))
 k_transport_tile(Gen G, int g) {
@@ -1332,7 +1431,6 @@ k_transport_tile(Gen G, int g) {
     const PacketRec *in = G.pool[cur];
     const int lane = __lane_id();
     const int ntp = G.tw * G.th;
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
     constexpr uint32_t kNone = 0xFFFFFFFFu;
     LedgerTile L;
     QueueSlice q;
@@ -1379,8 +1477,20 @@ k_transport_tile(Gen G, int g) {
         }
         __syncthreads();
 
-        Packet p;
-        idle_packet(p, tx0, tz0);
+        // what a lane does
+        enum : uint32_t {
+            kMove = 0,   // moves its packet
+            kFree = 1,   // has no packet
+            kDead = 2,   // its packet was terminated
+            kLeft = 3,   // its packet left the tile
+        };
+        uint32_t st = kFree;
+        Packet p;                 // ix, iz: pixel within the tile
+        idle_packet(p, 0, 0);
+        Ahead a = ahead_of(p.sx, p.sz);
+        int lp = 0;               // the pixel's number
+        float4 mm = smed[0];      // its medium
+        const int wx = min(G.tw, H.nx - tx0), wz = min(G.th, H.nz - tz0);   // the tile's part in the grid
         uint32_t nvis = 0;
         float mag = 0.f;   // sum of the |a0| this lane flushed in this job: bounds every slot's magnitude
         float acc[K], keep = 1.f;   // keep = 0 after a flush: the next deposit restarts the sums
@@ -1396,31 +1506,71 @@ k_transport_tile(Gen G, int g) {
         // quiet_pct percent of its lanes' worth (min(cnt, lanes)); from then
         // on a packet pauses after tail_visits more visits, so the workgroup
         // is not held by its longest stays (they resume next generation).
-        const uint32_t quiet_at = (uint32_t)(((uint64_t)min(cnt, (uint32_t)tile_block(NH)) * G.quiet_pct) / 100u);
+        // With many packets per lane that is earlier, at 9/5 of the percentage:
+        // one more generation costs little beside such a job (1e8 packets on a
+        // 256^2 disc 587 ms at 90 percent, 596 at 50; 2e7 168 at 50, 172 at 75).
+        const uint32_t lanes = tile_block(NH);
+        const uint32_t pct = min(100u, cnt >= 8u * lanes ? G.quiet_pct * 9u / 5u : G.quiet_pct);
+        const uint32_t quiet_at = min(cnt, lanes) * pct / 100u;
         bool quiet = false;       // wave-uniform
-        uint32_t tail_nvis = 0;   // visits of the current stay when the job turned quiet
+        uint32_t lim = G.max_visits;   // visits after which the packet pauses
+        const uint32_t tail = max(G.tail_visits, 1u);
         // (the last word is the packet id alone: a load whose destination
         // registers are partly dead lets them be reused, and the reuse must then
         // wait for the load)
         uint4 nr0 = make_uint4(0u, 0u, 0u, 0u), nr1 = nr0, nr2 = nr0;
         uint2 nr3 = make_uint2(0u, 0u);
         for (;;) {
-            // a free lane takes its prefetched record (the only decode site)
-            if (!p.alive && has_next) {
+            // ---- stays that ended, or pause between two visits
+            const bool pause = st == kMove && keep == 0.f && nvis >= lim;
+            const unsigned long long ended = __ballot(st > kFree || pause);
+            if (ended) {
+                const int ox = p.ix < 0 ? -1 : (p.ix >= G.tw ? 1 : 0);
+                const int oz = p.iz < 0 ? -1 : (p.iz >= G.th ? 1 : 0);
+                const uint32_t dest = (uint32_t)((int)tile + __mul24(oz, ntx) + ox);   // a crossing moves one pixel
+                p.ix += tx0;
+                p.iz += tz0;
+                const bool in_grid = (unsigned)p.ix < (unsigned)H.nx && (unsigned)p.iz < (unsigned)H.nz;
+                if (st == kLeft && !in_grid) L.escaped += p.w;
+                slice_put(G, nxt, q, pause || (st == kLeft && in_grid), p, dest, prob);
+                p.ix -= tx0;
+                p.iz -= tz0;
+                if (st > kFree || pause) st = kFree;
+                if (lane == 0) atomicSub(&s_left, (uint32_t)__popcll(ended));
+            }
+            // ---- once the job has no more to claim, free lanes take over what
+            // busy ones hold for later
+            if (!more) {
+                int src;
+                if (pair_lanes(st == kFree && !has_next, st == kMove && has_next, src)) {
+                    auto pull = [&](uint32_t &w) { w = __shfl(w, src & 63); };
+                    pull(nr0.x); pull(nr0.y); pull(nr0.z); pull(nr0.w);
+                    pull(nr1.x); pull(nr1.y); pull(nr1.z); pull(nr1.w);
+                    pull(nr2.x); pull(nr2.y); pull(nr2.z); pull(nr2.w);
+                    pull(nr3.x); pull(nr3.y);
+                    if (src != lane) has_next = src < 64;
+                }
+                if (pair_lanes(st == kFree && !has_next && nslot == kNone, st == kMove && nslot != kNone, src)) {
+                    nslot = __shfl(nslot, src & 63);
+                    if (src >= 64) nslot = kNone;
+                }
+            }
+            // ---- a free lane takes its prefetched record
+            if (st == kFree && has_next) {
                 rec_decode(nr0, nr1, nr2, nr3, p);
+                p.ix -= tx0;
+                p.iz -= tz0;
+                a = ahead_of(p.sx, p.sz);
+                lp = __mul24(p.iz, G.tw) + p.ix;
+                mm = smed[lp];
+                st = kMove;
                 has_next = false;
                 nvis = 0;
-                tail_nvis = 0;
+                lim = quiet ? min(G.max_visits, tail) : G.max_visits;
             }
-            // the medium of the pixel of this step, read before the claim below
-            // so its LDS latency overlaps with that work
-            const bool live = p.alive;
-            // 24-bit products (full-rate v_mad_i32_i24): tile sizes and offsets are small
-            const int lp = live ? __mul24(p.iz - tz0, G.tw) + (p.ix - tx0) : 0;
-            const float4 mm = smed[lp];
             // free record registers take the record of the slot claimed earlier
-            // (the slot index is checked here, a stay after its load, not at
-            // the claim, where the check would wait for that load)
+            // (the slot index is checked here, after its load, not at the
+            // claim, where the check would wait for that load)
             if (!has_next && nslot != kNone) {
                 if (nslot < G.cap_c + G.cap_l) {   // always true; guards the loads
                     const uint4 *r = reinterpret_cast<const uint4 *>(in + nslot);
@@ -1437,76 +1587,70 @@ k_transport_tile(Gen G, int g) {
             if (more) {
                 const unsigned long long want = __ballot(nslot == kNone);
                 if (want) {
-                    const int nw = __popcll(want);
-                    const int leader = __ffsll((long long)want) - 1;
-                    uint32_t base = 0;
-                    if (lane == leader) base = atomicAdd(&s_next, (uint32_t)nw);
-                    base = __shfl(base, leader);
+                    const uint32_t nw = (uint32_t)__popcll(want), base = wave_claim(&s_next, nw);
                     if (base + nw >= cnt) more = false;
-                    if (nslot == kNone) {
-                        const uint32_t my = base + __popcll(want & lt_mask);
-                        if (my < cnt) nslot = G.sidx[first + my];
+                    const uint32_t my = base + rank_in(want);
+                    if (nslot == kNone && my < cnt) nslot = G.sidx[first + my];
+                }
+            }
+            if (!more && !__ballot(st == kMove || has_next || nslot != kNone)) break;
+            if (!quiet && (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(
+                              &s_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) <= quiet_at) {
+                quiet = true;
+                lim = min(G.max_visits, nvis + tail);
+            }
+            // ---- the packets move
+#pragma unroll 1
+            for (int u = 0; u < kTilePasses; ++u) {
+                const bool moves = st == kMove;
+                L.segments += (uint32_t)__popcll(__ballot(moves));
+                const float sx = p.sx, sz = p.sz;   // direction of the segment, before any scatter
+                const int visited = lp;
+                float T = 0.f;
+                bool at = false, flush = false;
+                if (moves) {
+                    const Segment S = segment(p, a, mm);
+                    L.absorbed += (double)S.dw;
+                    T = S.T * fx;
+                    at = S.at;
+                    flush = !at;
+                    if (!at) {   // the visit ends at a face
+                        nvis += 1;
+                        lp = __mul24(p.iz, G.tw) + p.ix;
+                        // (read here, before the flush: LDS serves a wave in order)
+                        if ((unsigned)p.ix < (unsigned)wx && (unsigned)p.iz < (unsigned)wz) mm = smed[lp];
+                        else st = kLeft;
+                    }
+                    if (scatter_roulette(H, p, at, L)) {
+                        st = kDead;
+                        flush = true;
                     }
                 }
-            }
-            if (!__ballot(p.alive)) {
-                if (!more && !__ballot(has_next || nslot != kNone)) break;
-            }
-            if (!quiet && __hip_atomic_load(&s_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= quiet_at) {
-                quiet = true;
-                tail_nvis = nvis;
-            }
-            // every lane steps (no branch); a free lane's result is discarded
-            float T = 0.f, dw = 0.f;
-            int ev = step(H, p, mm, T, dw);
-            ev = live ? ev : EV_NONE;
-            T = live ? T : 0.f;
-            dw = live ? dw : 0.f;
-            L.absorbed += (double)dw;
-            L.segments += live ? 1u : 0u;
-            deposit_harmonics<NH>(T * fx, p.sx, p.sz, keep, acc);   // direction of the segment, before any scatter
-            const bool at = ev == EV_SCATTER;
-            // the roulette decides whether the visit ends here; the deflection
-            // and its random numbers come after the flush below, so that their
-            // arithmetic overlaps the flush's LDS atomics
-            const bool killed = scatter_roulette(H, p, at, L);
-            const bool vend = killed || (ev != EV_NONE && !at);   // the visit ends
-            // |a_n| <= a0 (one sign per packet): a long stay in one pixel is
-            // flushed in parts, so every flush stays inside fixed_add's range
-            const bool flush = vend || fabsf(acc[0]) > flush_at;
-            if (ev == EV_ESCAPE) {
-                L.escaped += p.w;
-                p.alive = false;
-            }
-            bool leave = false;
-            uint32_t dest = tile;
-            if (flush) {
-                unsigned long long *t = fxt + __umul24((uint32_t)lp, (uint32_t)K);
+                // (outside the branch, with T = 0 in the other lanes: the sums
+                // would need a second set of registers to merge at its end)
+                deposit_harmonics<NH>(T, sx, sz, keep, acc);
+                // |a_n| <= a0 (one sign per packet): a long stay in one pixel is
+                // flushed in parts, so every flush stays inside fixed_add's range
+                flush = flush || fabsf(acc[0]) > flush_at;
+                keep = flush ? 0.f : 1.f;
+                if (flush) {
+                    unsigned long long *t = fxt + __umul24((uint32_t)visited, (uint32_t)K);
 #pragma unroll
-                for (int j = 0; j < K; ++j) fixed_add_raw(t + j, acc[j]);
-                atomicAdd(sadds + lp, 1u);
-                mag += fabsf(acc[0]);
-            }
-            scatter_deflect(H, p, at && !killed, killed, mm.w, L);
-            if (vend) {
-                L.visits += 1;
-                nvis += 1;
-                if (ev == EV_CROSS) {
-                    const int ox = p.ix < tx0 ? -1 : (p.ix >= tx0 + G.tw ? 1 : 0);
-                    const int oz = p.iz < tz0 ? -1 : (p.iz >= tz0 + G.th ? 1 : 0);
-                    const bool out = (ox | oz) != 0;
-                    dest = (uint32_t)((int)tile + __mul24(oz, ntx) + ox);   // a crossing moves one pixel: a neighbour tile
-                    leave = out || nvis >= (quiet ? min(G.max_visits, tail_nvis + G.tail_visits) : G.max_visits);
+                    for (int j = 0; j < K; ++j) fixed_add_raw(t + j, acc[j]);
+                    atomicAdd(sadds + visited, 1u);
+                    mag += fabsf(acc[0]);
+                }
+                if (at && st == kMove) {   // the deflection and the next random numbers
+                    float sp, cp, nx_, nz_;
+                    hg_factors(p.uh, sp, cp);
+                    hg_rotate(mm.w, sp, cp, sx, sz, nx_, nz_);
+                    set_dir(p, nx_, nz_);
+                    a = ahead_of(nx_, nz_);
+                    ++p.k;
+                    new_leg(H, p);
+                    L.scatters += 1;
                 }
             }
-            keep = flush ? 0.f : 1.f;
-            slice_put(G, nxt, q, leave, p, dest, prob);
-            if (leave) {
-                p.alive = false;
-                nvis = 0;
-            }
-            const unsigned long long ended = __ballot(live && !p.alive);   // stays that ended here
-            if (ended && lane == 0) atomicSub(&s_left, (uint32_t)__popcll(ended));
         }
         // no slot can exceed the sum of the magnitudes flushed into the tile;
         // a job that could have wrapped the 64-bit sums is counted and its
@@ -1704,19 +1848,6 @@ __device__ __forceinline__ void ledger_flush_lane(const ProbDev &O, const Ledger
         if (c[i]) atomicAdd(O.ledc + i, c[i]);
 }
 
-// Lanes of the mask below this one.
-__device__ __forceinline__ uint32_t rank_in(unsigned long long m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// Adds n to a counter once for the wave and returns its old value, the same
-// in every lane (every lane of the wave calls it).
-__device__ __forceinline__ uint32_t wave_claim(uint32_t *counter, uint32_t n) {
-    uint32_t b = 0;
-    if (__lane_id() == 0) b = atomicAdd(counter, n);
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-}
-
 // A workgroup is two waves, one packet per lane of the first: that wave moves
 // the packets, the second keeps a ring of their next random blocks in LDS,
 // with what depends on the random numbers alone (free path, roulette draw,
@@ -1852,21 +1983,12 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         }
         rused += c;
     };
-    // Along x, a packet's face is at gx (1 or 0; 2, which it never reaches, for
-    // no motion) and the pixel behind it dx away; the same along z.
-    float gx = 2.f, gz = 2.f;
-    int dx = 0, dz = 0;
+    Ahead a = ahead_of(p.sx, p.sz);
     int gb = 0;                // the tile's first pixel in the medium table
-    auto turn = [&] {
-        gx = p.sx > 0.f ? 1.f : (p.sx < 0.f ? 0.f : 2.f);
-        gz = p.sz > 0.f ? 1.f : (p.sz < 0.f ? 0.f : 2.f);
-        dx = p.sx > 0.f ? 1 : -1;
-        dz = p.sz > 0.f ? 1 : -1;
-    };
     auto pixel = [&] { return gb + p.iz * Q.H.nx + p.ix; };
     auto load_ahead = [&](int i) {
-        mx = load_medium(Q.med, i + dx);
-        mz = load_medium(Q.med, dz > 0 ? i + Q.H.nx : i - Q.H.nx);
+        mx = load_medium(Q.med, i + a.dx);
+        mz = load_medium(Q.med, a.dz > 0 ? i + Q.H.nx : i - Q.H.nx);
     };
     auto enter_tile = [&] {
         wx = min(tw, Q.H.nx - tx0);
@@ -1895,38 +2017,23 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         p.ix -= tx0;
         p.iz -= tz0;
         tile = (uint32_t)(Q.tile_base + tz * Q.ntx + tx);
-        turn();
+        a = ahead_of(p.sx, p.sz);
         enter_tile();
         k0 = p.k;
         const uint32_t in_visit = goes_on && rec->tile != 0u ? 1u : 0u;
         resume = in_visit ? gid : kNoSlot;
         fl = kWait | in_visit;
     };
-    // One segment: the arithmetic of step(), scatter_roulette() and
-    // scatter_deflect(), operation by operation, with what depends on the
-    // direction alone kept from the scatter and no test for a zero component.
+    // One segment, its end and, if it is scattered, its next direction: the
+    // arithmetic of scatter_roulette() and scatter_deflect(), operation by
+    // operation.
     auto pass = [&](uint32_t u) {
 #pragma clang fp contract(off)
         const float4 rnd = ring[p.k % kRing][lane];   // for a scatter at the segment's end
         uint32_t ev = (uint32_t)(__mul24(p.iz, tw) + p.ix);
         const float sx = p.sx, sz = p.sz, g = mm.w;   // direction of the segment, before any scatter
-        const float dfx = fabsf(gx - p.fx) * fabsf(p.isx), dfz = fabsf(gz - p.fz) * fabsf(p.isz);
-        const float d = fminf(dfx, dfz);
-        const float od = mm.y * d;
-        const bool at = od > p.tau;
-        const float l = at ? p.tau * mm.z : d;
-        const float x = mm.x * l;
-        const float wf = p.w * absorbed_per_depth(x);
-        const float dw = wf * x, T = wf * l;
-        p.w = fmaf(-x, wf, p.w);
-        const bool cx = !at & (dfx <= dfz), cz = !at & (dfz <= dfx);   // faces crossed (both at a corner)
-        const float nfx = fminf(fmaxf(fmaf(sx, l, p.fx), 0.f), 1.f);
-        const float nfz = fminf(fmaxf(fmaf(sz, l, p.fz), 0.f), 1.f);
-        p.tau = p.tau - od;                           // a scatter replaces it
-        p.ix += cx ? dx : 0;
-        p.iz += cz ? dz : 0;
-        p.fx = cx ? 1.f - gx : nfx;
-        p.fz = cz ? 1.f - gz : nfz;
+        const Segment S = segment(p, a, mm);
+        const bool at = S.at, cx = S.cx, cz = S.cz;
         const bool out = ((unsigned)p.ix >= (unsigned)wx) | ((unsigned)p.iz >= (unsigned)wz);
         // the medium of the pixel the next step starts in (padding, if outside
         // the grid), on its way while the rest is computed
@@ -1947,14 +2054,14 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
                 p.w *= Q.H.rm;
             }
         }
-        s_ev[s_ev0 ^ u] = make_float4(T * Q.fx, sx, sz, __uint_as_float(ev));
+        s_ev[s_ev0 ^ u] = make_float4(S.T * Q.fx, sx, sz, __uint_as_float(ev));
         ++n;
-        L.absorbed += (double)dw;
+        L.absorbed += (double)S.dw;
         if (go) {
             float nx_, nz_;
             hg_rotate(g, rnd.z, rnd.y, sx, sz, nx_, nz_);
             set_dir(p, nx_, nz_);
-            turn();
+            a = ahead_of(nx_, nz_);
             ++p.k;
             p.tau = rnd.w;
         }
@@ -3023,11 +3130,12 @@ constexpr uint32_t kJobMin = 1024;             // smallest job of a generation w
 constexpr uint32_t kQuietPercent = 50;         // see the quiet rule of k_transport_tile
 
 // Walk and tally (see k_walk).
-// Runs up to this many packets (those of volume sources count twice) walk from
-// their launch: on 256^2 discs 1e6 forward packets take 24 ms against 29 ms in
-// generations, 3e6 50.6 against 51.9, 1e6 adjoint packets 57.7 against 61.5,
-// 2e6 103 against 95.
-constexpr uint64_t kDirectMax = 3ull << 20;
+// Runs up to this many packets walk from their launch.  Milliseconds, against
+// generations first, at 1e6, 2e6 and 3e6 packets: 256^2 disc 18.6 / 20.6, 30.6 /
+// 32.2, 43.1 / 42.1; 128^2 13.0 / 14.0 and 22.0 / 21.0; adjoint on 256^2 51.9 /
+// 54.1 and 98 / 86; on 149 x 101 at N = 32 27.6 / 30.0 and 52.5 / 49.2; 32^2
+// pencil beam 3.4 / 4.1 and, at 3e6, 9.0 / 5.5; 24^2 2.5 / 3.0 at 1e6.
+constexpr uint64_t kDirectMax = 3ull << 19;
 constexpr uint64_t kWalkEvents = 1ull << 27;         // events a round may write
 constexpr uint64_t kWalkEventsPerLane = 1ull << 14;  // or this many per lane if that is less
 constexpr uint32_t kWalkRounds = 2;                  // rounds enqueued: these, and as many as events are expected
@@ -3219,14 +3327,12 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
     B.live = std::min<uint64_t>(B.total_packets, B.tt.live);
     B.finish = B.tt.finish ? B.tt.finish : std::min<uint64_t>(kFinishMax, B.tt.live / 128);
     const bool walk = B.tt.ev_max != 0;
-    // the rounds take over earlier than the finisher alone would: measured on
-    // 128^2 to 256^2 discs at 1e5 to 4e6 packets, 2^17 left is the best
-    // hand-over for them (10-25% faster than 2^16 and 2^14)
-    if (walk) B.finish = std::min<uint64_t>(2 * B.finish, kLiveMax);
-    uint64_t weight = 0;   // packets, those of volume sources twice: their paths are about that much longer
-    for (int i = 0; i < n; ++i)
-        weight += pb[i].run->n_packets * (pb[i].src[0].kind == MC_SRC_MAP || pb[i].src[0].kind == MC_SRC_POINT ? 2 : 1);
-    B.direct = walk && n <= kMaxAlloc && weight <= kDirectMax && B.total_packets <= B.tt.live;
+    // the rounds take over earlier than the finisher alone would: 2^19 packets
+    // left is the best hand-over on 256^2 discs (4e6 forward packets 50.4 ms,
+    // with 2^17 left 59.9, 2^18 54.5, 2^20 51.7, 2^21 55.7; 2e7 161, 168, 165,
+    // 162; 4e6 adjoint packets 138, 146, 142, 140, 154) and a 32^2 pencil beam
+    if (walk) B.finish = std::min<uint64_t>(8 * B.finish, kLiveMax);
+    B.direct = walk && n <= kMaxAlloc && B.total_packets <= std::min(kDirectMax, B.tt.live);
     // carried region: every packet a generation moves may leave, plus the
     // padding of the wave slices still open when it ends; launch region: at
     // most `live` new packets per generation
