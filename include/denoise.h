@@ -48,6 +48,24 @@ mc_status dn_conv3x3_f32(const float *x_d, const int64_t *strides_h, const uint1
  * spatial directions reversed. */
 mc_status dn_pack_weights(const float *w_d, uint16_t *out_d, int co, int ci, int flip, void *stream);
 
+/* The denoiser's network, without gradients: an encoder and decoder over
+ * `levels` levels (1 .. 8) of the given widths (host array; widths[0] <= 512).
+ * Every level is two 3x3 convolutions with ReLU; a level's map goes to the
+ * next by 2 x 2 maxima (odd sizes round up) and comes back repeated 2 x 2 (cut
+ * to size) before the channels of the map kept on the way down; last,
+ *   y = x + out_w a + out_b
+ * with out_w FP32 [channels][widths[0]].  weights (host array of 4 levels - 2
+ * device pointers): FP32 [co][ci][3][3], encoder from the top, then decoder
+ * from the bottom; biases: FP32 [co].  x_d, y_d: FP32 with element strides
+ * {n, c, h, w}; they may not overlap.  The same values as dn_conv3x3_f32 layer
+ * by layer.  scratch_d: at least dn_unet_bytes() bytes (0: the network or sizes
+ * are not supported), 16-byte aligned. */
+size_t dn_unet_bytes(int channels, int levels, const int32_t *widths, int n, int h, int w);
+mc_status dn_unet_forward(int channels, int levels, const int32_t *widths, const float *const *weights,
+                          const float *const *biases, const float *out_w, const float *out_b, const float *x_d,
+                          const int64_t *x_strides, float *y_d, const int64_t *y_strides, void *scratch_d,
+                          size_t scratch_bytes, int n, int h, int w, void *stream);
+
 /* Gradients of dn_conv3x3_f32 with respect to the weights, FP32
  * [co][ci][3][3], and (if gb_d is not NULL) the bias, FP32 [co]: xb_d as that
  * call wrote it, gy_d FP32 [n][h][w][co].  The weight gradient's products take

@@ -24,7 +24,7 @@ SYMBOLS = ("mc_workspace_bytes", "mc_forward", "mc_adjoint", "mc_residual", "mc_
            "mc_run_noalloc",
            "mc_binned_workspace_bytes", "mc_run_binned",
            "mc_status_string", "mc_build_info", "dn_conv3x3_fwd", "dn_conv3x3_f32", "dn_pack_weights",
-           "dn_conv3x3_grads_bytes", "dn_conv3x3_grads", "dn_conv3x3_wgrad",
+           "dn_conv3x3_grads_bytes", "dn_conv3x3_grads", "dn_conv3x3_wgrad", "dn_unet_bytes", "dn_unet_forward",
            "mb_lds_atomics", "mb_global_atomics_f64", "mb_global_atomics_rows_f64", "mb_copy", "mb_fma_f32", "mb_wall_clock_khz")
 (MB_LDS_ADD_F64, MB_LDS_ADD_F32, MB_LDS_ADD_U64, MB_LDS_ADD_U32, MB_LDS_ADD_F64_ROW33, MB_LDS_ADD_U64_ROW33,
  MB_LDS_ADD_U64_PRE) = range(7)
@@ -141,6 +141,11 @@ def load() -> C.CDLL:
     lib.dn_conv3x3_grads_bytes.restype = C.c_size_t
     lib.dn_conv3x3_grads.argtypes = [V, V, V, V, V, C.c_size_t, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, V]
     lib.dn_conv3x3_grads.restype = St
+    lib.dn_unet_bytes.argtypes = [C.c_int, C.c_int, P(C.c_int32), C.c_int, C.c_int, C.c_int]
+    lib.dn_unet_bytes.restype = C.c_size_t
+    lib.dn_unet_forward.argtypes = [C.c_int, C.c_int, P(C.c_int32), P(V), P(V), V, V, V, P(C.c_int64), V, P(C.c_int64), V,
+                                    C.c_size_t, C.c_int, C.c_int, C.c_int, V]
+    lib.dn_unet_forward.restype = St
     lib.dn_conv3x3_wgrad.argtypes = [V, V, V, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, V]
     lib.dn_conv3x3_wgrad.restype = St
     lib.mb_lds_atomics.argtypes = [C.c_int, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint32, V, V, V]

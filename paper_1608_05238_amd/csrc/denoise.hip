@@ -74,7 +74,10 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
 // 16 x 256^2 pixels, 48 -> 48 channels, with the BF16 copy: 125 us = 4.1 TB/s
 // of what it must read and write; a conversion pass (26 us) and a kernel that
 // staged 32-channel chunks of 8 x 8 blocks without overlap took 366 us.
-enum : int { X_F32 = 0, X_STRIDED = 1, X_BF16 = 2 };   // FP32 channels last, 16-byte rows; FP32, any strides; BF16
+// FP32 channels last, 16-byte rows; FP32, any strides; BF16; or FP32 channels
+// last put together on the way in: the 2 x 2 maxima of a map twice the size, or
+// a map of half the size repeated, and the channels of a second map after it
+enum : int { X_F32 = 0, X_STRIDED = 1, X_BF16 = 2, X_MIX = 3 };
 
 struct ConvArgs {
     const void *x;
@@ -86,9 +89,14 @@ struct ConvArgs {
     int ci, cip, co, h, wd;
     int tiles_x, tiles_y, n_tiles;
     int units, nchunk;          // units of 8 channels a chunk; chunks
+    // X_MIX: x is [n][hs][ws][ca]; x2 [n][h][w][ci - ca] or NULL (maxima)
+    const float *x2;
+    int hs, ws, ca, vec;        // vec: whole units of each map's channels
 };
 
 constexpr int kUnitsMax = 6;    // units a chunk may have
+constexpr int kUnetLevels = 8, kUnetLayers = 4 * kUnetLevels - 2;   // of a network in one call
+constexpr int kUnetOutMax = 512;                                    // its first width (LDS of k_unet_out)
 
 constexpr int halo_units(int ts) { return ((ts + 2) * (ts + 2) * kUnitsMax + kThreads - 1) / kThreads; }
 
@@ -96,7 +104,49 @@ size_t conv_lds(int ts, int mb, int units) {
     return ((size_t)(ts + 2) * (ts + 2) * (units | 1) + (size_t)16 * mb * ((9 * units) | 1) + 1) * 16;
 }
 
-template <int TS, int MB, int KIND>
+// The larger, NaN if either is (as a maximum pool)
+__device__ __forceinline__ float max_nan(float a, float b) { return a > b || a != a ? a : b; }
+
+// Eight channels from ch on of a pixel of X_MIX.
+__device__ __forceinline__ void mixed8(const ConvArgs &A, int img, int yy, int xx, int ch, float (&v)[8]) {
+    const float *x = (const float *)A.x;
+    if (!A.x2) {
+        const int y = 2 * yy, c = 2 * xx;
+        const float *p = x + (((size_t)img * A.hs + y) * A.ws + c) * A.ca + ch;
+        const size_t right = c + 1 < A.ws ? A.ca : 0, down = y + 1 < A.hs ? (size_t)A.ws * A.ca : 0;
+        if (A.vec) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 4) {
+                const f32x4 a = *(const f32x4 *)(p + i), b = *(const f32x4 *)(p + right + i);
+                const f32x4 e = *(const f32x4 *)(p + down + i), g = *(const f32x4 *)(p + down + right + i);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[i + k] = max_nan(max_nan(a[k], b[k]), max_nan(e[k], g[k]));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (ch + i < A.ci) v[i] = max_nan(max_nan(p[i], p[right + i]), max_nan(p[down + i], p[down + right + i]));
+        }
+        return;
+    }
+    const float *p = x + (((size_t)img * A.hs + (yy >> 1)) * A.ws + (xx >> 1)) * A.ca + ch;
+    const float *q = A.x2 + (((size_t)img * A.h + yy) * A.wd + xx) * (A.ci - A.ca) + (ch - A.ca);
+    if (A.vec) {
+        const f32x4 *r = (const f32x4 *)(ch < A.ca ? p : q);
+        const f32x4 a = r[0], b = r[1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = a[i];
+            v[4 + i] = b[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (ch + i < A.ci) v[i] = ch + i < A.ca ? p[i] : q[i];
+    }
+}
+
+template <int TS, int MB, int KIND, bool RELU>
 __global__ void __launch_bounds__(kThreads, 2) k_conv3x3(ConvArgs A) {
     constexpr int HS = TS + 2, NPX = HS * HS, NB = TS * TS / 64;   // halo side and pixels; 16-pixel blocks a wave
     constexpr int NJ = halo_units(TS);                             // activation units a thread stages
@@ -138,7 +188,9 @@ __global__ void __launch_bounds__(kThreads, 2) k_conv3x3(ConvArgs A) {
             } else {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) rf[j][i] = 0.f;
-                if (KIND == X_F32) {
+                if constexpr (KIND == X_MIX) {
+                    if (in && ch < A.ci) mixed8(A, img, yy, xx, ch, rf[j]);
+                } else if (KIND == X_F32) {
                     if (in && ch < A.ci) {
                         const f32x4 *p = (const f32x4 *)((const float *)A.x + (((size_t)img * A.h + yy) * A.wd + xx) * A.ci + ch);
                         const f32x4 a = p[0], b = p[1];
@@ -264,7 +316,10 @@ __global__ void __launch_bounds__(kThreads, 2) k_conv3x3(ConvArgs A) {
                     const int p = (wave * NB + b) * 16 + l16, gy = ty + p / TS, gx = tx + p % TS;
                     if (gy >= A.h || gx >= A.wd || co >= A.co) continue;
                     float *dst = A.y + (((size_t)img * A.h + gy) * A.wd + gx) * A.co + co;
-                    const f32x4 v = acc[a][b] + bias;
+                    f32x4 v = acc[a][b] + bias;
+                    if constexpr (RELU)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = v[i] <= 0.f ? 0.f : v[i];   // (NaN stays)
                     if (vec) {
                         *(f32x4 *)dst = v;
                     } else {
@@ -290,15 +345,82 @@ __global__ void __launch_bounds__(kThreads, 2) k_conv3x3(ConvArgs A) {
 // Weights [co][ci][3][3] FP32 as the forward kernel reads them: BF16
 // [co][9][cip] (zeros past ci), or with `flip` those of the input gradient,
 // [ci][9][cop], both spatial directions reversed.
-__global__ void k_pack_weights(const float *w, uint16_t *out, int co, int ci, int inner, int flip) {
+__device__ __forceinline__ void pack_weights(const float *w, uint16_t *out, int co, int ci, int inner, int flip) {
     const int rows = flip ? ci : co, cols = flip ? co : ci;
     const size_t total = (size_t)rows * 9 * inner;
     for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < total; v += (size_t)gridDim.x * blockDim.x) {
-        const int line = (int)(v / (size_t)inner), col = (int)(v - (size_t)line * inner);
+        const int line = (int)(total >> 32 ? v / (size_t)inner : (uint32_t)v / (uint32_t)inner);
+        const int col = (int)(v - (size_t)line * inner);
         const int row = line / 9, tap = line - row * 9;
         float x = 0.f;
         if (col < cols) x = flip ? w[((size_t)col * ci + row) * 9 + 8 - tap] : w[((size_t)row * ci + col) * 9 + tap];
         out[v] = to_bf16(x);
+    }
+}
+
+__global__ void k_pack_weights(const float *w, uint16_t *out, int co, int ci, int inner, int flip) {
+    pack_weights(w, out, co, ci, inner, flip);
+}
+
+// All layers of a network in one launch (blockIdx.y: the layer).
+struct PackList {
+    const float *w[kUnetLayers];
+    uint16_t *out[kUnetLayers];
+    int co[kUnetLayers], ci[kUnetLayers];
+};
+
+__global__ void k_pack_layers(PackList P) {
+    const int l = blockIdx.y;
+    pack_weights(P.w[l], P.out[l], P.co[l], P.ci[l], (P.ci[l] + 7) & ~7, 0);
+}
+
+// ---- output layer of the network: y = x + W a + b per pixel
+// a: FP32 [pixels][c]; x, y: FP32 of any strides.  A workgroup stages 64 pixels
+// of a in LDS, transposed; each of its waves then takes every fourth group of
+// four output channels, a pixel a lane.  Bound by memory (one read of a and x,
+// one write of y); 3 x 256^2 pixels, 24 -> 33 channels: 30 us, 2.3 TB/s (as a
+// matrix product, two sums and a copy: 95 us).
+struct Strided {
+    long long n, c, h, w;
+};
+
+__global__ void __launch_bounds__(kThreads) k_unet_out(const float *a, const float *w, const float *b, const float *x, Strided sx,
+                                                       float *y, Strided sy, int c, int channels, int h, int wd, int pixels) {
+    extern __shared__ u32x4 lds[];
+    float *as = (float *)lds;   // [c][65]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p0 = blockIdx.x * 64, np = min(64, pixels - p0);
+#pragma unroll 4
+    for (int e = tid; e < np * c; e += kThreads) {
+        const int px = e / c, ch = e - px * c;
+        as[ch * 65 + px] = a[(size_t)p0 * c + e];
+    }
+    __syncthreads();
+    const int p = p0 + min(lane, np - 1), img = p / (h * wd), q = p - img * (h * wd), yy = q / wd, xx = q - yy * wd;
+    const float *xp = x + img * sx.n + yy * sx.h + xx * sx.w;
+    float *yp = y + img * sy.n + yy * sy.h + xx * sy.w;
+    for (int o0 = 4 * wave; o0 < channels; o0 += 16) {
+        float acc[4] = {0.f, 0.f, 0.f, 0.f}, xv[4];
+        int row[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            row[i] = min(o0 + i, channels - 1) * c;
+            xv[i] = xp[min(o0 + i, channels - 1) * sx.c];   // on its way during the sums
+        }
+        auto add = [&](int k) {
+            const float v = as[k * 65 + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = fmaf(w[row[i] + k], v, acc[i]);
+        };
+        int k = 0;
+        for (; k + 8 <= c; k += 8)   // (the weights come as scalar loads of eight)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) add(k + j);
+        for (; k < c; ++k) add(k);
+        if (lane < np)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (o0 + i < channels) yp[(o0 + i) * sy.c] = xv[i] + (acc[i] + b[o0 + i]);
     }
 }
 
@@ -637,15 +759,20 @@ mc_status set_lds(const void *fn, size_t bytes) {
 using ConvFn = void (*)(ConvArgs);
 using WgradFn = void (*)(WgradArgs);
 
-template <int TS, int KIND>
+template <int TS, int KIND, bool RELU>
 ConvFn conv_of(int mb) {
-    return mb == 1 ? k_conv3x3<TS, 1, KIND> : mb == 2 ? k_conv3x3<TS, 2, KIND> : mb == 3 ? k_conv3x3<TS, 3, KIND>
-                                                                                        : k_conv3x3<TS, 4, KIND>;
+    return mb == 1   ? k_conv3x3<TS, 1, KIND, RELU>
+           : mb == 2 ? k_conv3x3<TS, 2, KIND, RELU>
+           : mb == 3 ? k_conv3x3<TS, 3, KIND, RELU>
+                     : k_conv3x3<TS, 4, KIND, RELU>;
 }
 
-ConvFn conv_fn(int ts, int mb, int kind) {
-    if (ts == 16) return kind == X_F32 ? conv_of<16, X_F32>(mb) : kind == X_BF16 ? conv_of<16, X_BF16>(mb) : conv_of<16, X_STRIDED>(mb);
-    return kind == X_F32 ? conv_of<8, X_F32>(mb) : kind == X_BF16 ? conv_of<8, X_BF16>(mb) : conv_of<8, X_STRIDED>(mb);
+template <int TS>
+ConvFn conv_fn(int mb, int kind, bool relu) {
+    if (kind == X_MIX) return conv_of<TS, X_MIX, true>(mb);
+    if (kind == X_BF16) return conv_of<TS, X_BF16, false>(mb);
+    if (kind == X_F32) return relu ? conv_of<TS, X_F32, true>(mb) : conv_of<TS, X_F32, false>(mb);
+    return relu ? conv_of<TS, X_STRIDED, true>(mb) : conv_of<TS, X_STRIDED, false>(mb);
 }
 
 // Blocks of 16 channels per workgroup: the count that pads `c` channels least,
@@ -662,7 +789,8 @@ int blocks_for(int c, int most) {
     return best;
 }
 
-mc_status run_conv(ConvArgs A, int kind, int n, hipStream_t s) {
+// relu: negative results become zero (kinds X_F32, X_STRIDED, and X_MIX always)
+mc_status run_conv(ConvArgs A, int kind, int n, hipStream_t s, bool relu = false) {
     // 16 x 16 pixel blocks and all output channels up to 64 in a workgroup read
     // least (16 x 256^2 pixels, 48 -> 48: 117 us; 8 x 8 blocks 151; 32 channels
     // a workgroup 141).  With less than two workgroups a CU, 32 channels each
@@ -692,7 +820,7 @@ mc_status run_conv(ConvArgs A, int kind, int n, hipStream_t s) {
     if (tiles >= (1ll << 31) || gco > 65535) return MC_ERR_UNSUPPORTED;
     A.n_tiles = (int)tiles;
     const size_t lds = conv_lds(ts, mb, A.units);
-    const ConvFn fn = conv_fn(ts, mb, kind);
+    const ConvFn fn = ts == 16 ? conv_fn<16>(mb, kind, relu) : conv_fn<8>(mb, kind, relu);
     const mc_status st = set_lds(reinterpret_cast<const void *>(fn), lds);
     if (st != MC_OK) return st;
     // two workgroups a CU, each taking several blocks: the weights are staged
@@ -702,6 +830,62 @@ mc_status run_conv(ConvArgs A, int kind, int n, hipStream_t s) {
     const unsigned gx = (unsigned)((tiles + rounds - 1) / rounds);
     hipLaunchKernelGGL(fn, dim3(gx, (unsigned)gco), dim3(kThreads), lds, s, A);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+}
+
+// Sets the FP32 input of a convolution; returns how it is read.
+int f32_input(ConvArgs &A, const float *x, const int64_t *strides, int ci, int h, int w) {
+    A.x = x;
+    A.sn = strides[0];
+    A.sc = strides[1];
+    A.sh = strides[2];
+    A.sw = strides[3];
+    A.ci = ci;
+    A.cip = (ci + 7) & ~7;
+    A.h = h;
+    A.wd = w;
+    // whole units of eight channels, rows of 16 bytes: two 16-byte loads a unit
+    const bool vec = (ci & 7) == 0 && aligned16(x) && A.sc == 1 && A.sw == ci && A.sh == (int64_t)w * ci &&
+                     A.sn == (int64_t)h * w * ci;
+    return vec ? X_F32 : X_STRIDED;
+}
+
+// A network's layers and where their data lie in the scratch buffer.
+struct UnetPlan {
+    int levels, layers;
+    int h[kUnetLevels], w[kUnetLevels];
+    int ci[kUnetLayers], co[kUnetLayers];
+    size_t map[kUnetLevels], hidden, packed[kUnetLayers], bytes;
+};
+
+bool unet_plan(UnetPlan &P, int channels, int levels, const int32_t *widths, int n, int h, int w) {
+    if (channels < 1 || levels < 1 || levels > kUnetLevels || widths[0] > kUnetOutMax) return false;
+    P.levels = levels;
+    P.layers = 4 * levels - 2;
+    size_t off = 0, hidden = 0;
+    auto take = [&](size_t b) {
+        const size_t at = off;
+        off += (b + 255) & ~(size_t)255;
+        return at;
+    };
+    for (int i = 0; i < levels; ++i) {
+        P.h[i] = i ? (P.h[i - 1] + 1) / 2 : h;
+        P.w[i] = i ? (P.w[i - 1] + 1) / 2 : w;
+        if (widths[i] < 1 || !dims_ok(n, i ? widths[i - 1] : channels, widths[i], P.h[i], P.w[i])) return false;
+        const size_t b = (size_t)n * P.h[i] * P.w[i] * widths[i] * sizeof(float);
+        P.map[i] = take(b);
+        hidden = std::max(hidden, b);
+        P.ci[2 * i] = i ? widths[i - 1] : channels;
+        P.co[2 * i] = P.ci[2 * i + 1] = P.co[2 * i + 1] = widths[i];
+    }
+    for (int i = levels - 2, l = 2 * levels; i >= 0; --i, l += 2) {
+        P.ci[l] = widths[i + 1] + widths[i];
+        P.co[l] = P.ci[l + 1] = P.co[l + 1] = widths[i];
+        if (!dims_ok(n, P.ci[l], P.co[l], P.h[i], P.w[i])) return false;
+    }
+    P.hidden = take(hidden);
+    for (int l = 0; l < P.layers; ++l) P.packed[l] = take((size_t)P.co[l] * 9 * ((P.ci[l] + 7) & ~7) * sizeof(uint16_t));
+    P.bytes = off;
+    return true;
 }
 
 template <int MB, bool VEC>
@@ -764,24 +948,13 @@ mc_status dn_conv3x3_f32(const float *x_d, const int64_t *strides, const uint16_
         (xb_d && !aligned16(xb_d)) || ((co & 3) == 0 && !aligned16(y_d)))
         return MC_ERR_INVALID_ARG;
     ConvArgs A{};
-    A.x = x_d;
-    A.sn = strides[0];
-    A.sc = strides[1];
-    A.sh = strides[2];
-    A.sw = strides[3];
+    const int kind = f32_input(A, x_d, strides, ci, h, w);
     A.w = w_d;
     A.bias = bias_d;
     A.y = y_d;
     A.xb = xb_d;
-    A.ci = ci;
-    A.cip = (ci + 7) & ~7;
     A.co = co;
-    A.h = h;
-    A.wd = w;
-    // whole units of eight channels, rows of 16 bytes: two 16-byte loads a unit
-    const bool vec = (ci & 7) == 0 && aligned16(x_d) && A.sc == 1 && A.sw == ci && A.sh == (int64_t)w * ci &&
-                     A.sn == (int64_t)h * w * ci;
-    return run_conv(A, vec ? X_F32 : X_STRIDED, n, reinterpret_cast<hipStream_t>(stream));
+    return run_conv(A, kind, n, reinterpret_cast<hipStream_t>(stream));
 }
 
 mc_status dn_pack_weights(const float *w_d, uint16_t *out_d, int co, int ci, int flip, void *stream) {
@@ -791,6 +964,98 @@ mc_status dn_pack_weights(const float *w_d, uint16_t *out_d, int co, int ci, int
     const long long total = (long long)(flip ? ci : co) * 9 * inner;
     hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)std::min<long long>((total + 255) / 256, 1024)), dim3(256), 0,
                        reinterpret_cast<hipStream_t>(stream), w_d, out_d, co, ci, inner, flip);
+    return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+}
+
+size_t dn_unet_bytes(int channels, int levels, const int32_t *widths, int n, int h, int w) {
+    UnetPlan P;
+    return widths && unet_plan(P, channels, levels, widths, n, h, w) ? P.bytes : 0;
+}
+
+// One call and 24 launches for six levels instead of ~110: what is between two
+// convolutions (ReLU, maxima, repetition, joining channels) is done where one
+// writes or the next reads, and the weights of all layers are packed at once.
+// Three 256^2 maps of 33 channels, widths 24 to 128: 990 us (bound by the host's
+// launches, ~270 us of it passes over memory) -> 424 us, of which 75 are the
+// caller's normalisation; bound now by the small layers' latency (8 - 17 us each
+// from 64^2 down) and by memory at 256^2.
+mc_status dn_unet_forward(int channels, int levels, const int32_t *widths, const float *const *weights,
+                          const float *const *biases, const float *out_w, const float *out_b, const float *x_d,
+                          const int64_t *x_strides, float *y_d, const int64_t *y_strides, void *scratch_d,
+                          size_t scratch_bytes, int n, int h, int w, void *stream) {
+    UnetPlan P;
+    if (!widths || !weights || !biases || !out_w || !out_b || !x_d || !x_strides || !y_d || !y_strides)
+        return MC_ERR_INVALID_ARG;
+    if (!unet_plan(P, channels, levels, widths, n, h, w)) return MC_ERR_UNSUPPORTED;
+    if (!scratch_d || scratch_bytes < P.bytes || !aligned16(scratch_d)) return MC_ERR_WORKSPACE;
+    for (int l = 0; l < P.layers; ++l)
+        if (!weights[l] || !biases[l]) return MC_ERR_INVALID_ARG;
+    const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    char *base = static_cast<char *>(scratch_d);
+    PackList pk{};
+    for (int l = 0; l < P.layers; ++l) {
+        pk.w[l] = weights[l];
+        pk.out[l] = reinterpret_cast<uint16_t *>(base + P.packed[l]);
+        pk.co[l] = P.co[l];
+        pk.ci[l] = P.ci[l];
+    }
+    hipLaunchKernelGGL(k_pack_layers, dim3(64, (unsigned)P.layers), dim3(256), 0, s, pk);
+    auto map = [&](int i) { return reinterpret_cast<float *>(base + P.map[i]); };
+    float *hidden = reinterpret_cast<float *>(base + P.hidden);
+    // layer l at level i, from A's input
+    auto conv = [&](ConvArgs A, int kind, int l, int i, float *y) {
+        A.w = pk.out[l];
+        A.bias = biases[l];
+        A.y = y;
+        A.co = P.co[l];
+        A.h = P.h[i];
+        A.wd = P.w[i];
+        A.ci = P.ci[l];
+        A.cip = (P.ci[l] + 7) & ~7;
+        return run_conv(A, kind, n, s, true);
+    };
+    auto second = [&](int l, int i) {   // hidden -> the level's map
+        ConvArgs A{};
+        const int64_t c = P.ci[l], st[4] = {c * P.w[i] * P.h[i], 1, c * P.w[i], c};
+        const int kind = f32_input(A, hidden, st, P.ci[l], P.h[i], P.w[i]);
+        return conv(A, kind, l, i, map(i));
+    };
+    for (int i = 0; i < levels; ++i) {
+        ConvArgs A{};
+        int kind = X_MIX;
+        if (i == 0) {
+            kind = f32_input(A, x_d, x_strides, channels, h, w);
+        } else {
+            A.x = map(i - 1);
+            A.hs = P.h[i - 1];
+            A.ws = P.w[i - 1];
+            A.ca = widths[i - 1];
+            A.vec = (A.ca & 7) == 0;
+        }
+        mc_status st = conv(A, kind, 2 * i, i, hidden);
+        if (st == MC_OK) st = second(2 * i + 1, i);
+        if (st != MC_OK) return st;
+    }
+    for (int i = levels - 2, l = 2 * levels; i >= 0; --i, l += 2) {
+        ConvArgs A{};
+        A.x = map(i + 1);
+        A.x2 = map(i);
+        A.hs = P.h[i + 1];
+        A.ws = P.w[i + 1];
+        A.ca = widths[i + 1];
+        A.vec = (A.ca & 7) == 0 && (widths[i] & 7) == 0;
+        mc_status st = conv(A, X_MIX, l, i, hidden);
+        if (st == MC_OK) st = second(l + 1, i);   // over the map that was read
+        if (st != MC_OK) return st;
+    }
+    const int pixels = n * h * w;
+    const size_t lds = (size_t)widths[0] * 65 * sizeof(float);
+    const mc_status st = set_lds(reinterpret_cast<const void *>(k_unet_out), lds);
+    if (st != MC_OK) return st;
+    const Strided sx{x_strides[0], x_strides[1], x_strides[2], x_strides[3]};
+    const Strided sy{y_strides[0], y_strides[1], y_strides[2], y_strides[3]};
+    hipLaunchKernelGGL(k_unet_out, dim3((unsigned)((pixels + 63) / 64)), dim3(kThreads), lds, s, map(0), out_w, out_b, x_d, sx,
+                       y_d, sy, widths[0], channels, h, w, pixels);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
 

@@ -4,8 +4,9 @@ A small U-Net maps the 2N+1 coefficient maps of a run with few packets to
 those of a run with many packets, so that a gradient evaluation can stand on
 fewer packets.  Its 3x3 convolutions (forward, input gradient and weight
 gradient) are the hand-written MFMA kernels of denoise.h (BF16 operands,
-FP32 accumulation); pooling, upsampling, ReLU and the 1x1 output layer are
-plain PyTorch.  Training pairs come from the Monte Carlo itself, run as
+FP32 accumulation); without gradients the whole network is one call
+(dn_unet_forward), in training pooling, upsampling, ReLU and the 1x1 output
+layer are plain PyTorch.  Training pairs come from the Monte Carlo itself, run as
 batches of problems (mc_run_batch).  The plain Monte Carlo stays the
 reference and the fallback: `denoise_or_mc` runs the low-count input as two
 independent halves, predicts the error of that input's denoised maps from
@@ -29,6 +30,8 @@ import numpy as np
 import torch
 import torch.nn as nn
 import torch.nn.functional as F
+from torch.autograd import forward_ad
+from torch.nn.modules import module as nn_module
 
 from . import _lib as L
 from . import rmc
@@ -146,7 +149,61 @@ class UNet(nn.Module):
         self.out = nn.Parameter(torch.zeros(channels, c))   # 1x1 output layer
         self.out_bias = nn.Parameter(torch.zeros(channels))
 
+    def _layers(self):
+        return [c for pair in (*self.enc, *self.dec) for c in pair]
+
+    def _plain(self, x) -> bool:
+        """Whether a call without gradients may run as one: plain FP32 tensors
+        on the current device and nothing that has to see the layers (hooks,
+        tracing, forward-mode derivatives, autocast, replaced layers)."""
+        if (torch.is_grad_enabled() or type(x) is not torch.Tensor or not x.is_cuda or x.dim() != 4 or x.numel() == 0
+                or x.shape[1] != self.out.shape[0] or torch.is_autocast_enabled("cuda") or torch.jit.is_tracing()
+                or torch.compiler.is_compiling() or forward_ad._current_level >= 0
+                or x.device.index != torch.cuda.current_device() or nn_module._has_any_global_hook()):
+            return False
+        layers = self._layers()
+        if any(type(c) is not Conv3x3 or c._forward_hooks or c._forward_pre_hooks or "forward" in c.__dict__
+               for c in layers):
+            return False
+        tensors = [x, self.out, self.out_bias]
+        for c in layers:
+            tensors += [c.weight, c.bias]
+        return all(type(t) in (torch.Tensor, nn.Parameter) and t.dtype == torch.float32 and t.device == x.device
+                   for t in tensors) and all(t.is_contiguous() for t in tensors[1:])
+
+    def _inference(self, x):
+        """The layers below in one call of dn_unet_forward, or None if it does
+        not take this network or size."""
+        lib, layers = L.load(), self._layers()
+        n, ch, h, w = x.shape
+        widths = [c2.weight.shape[0] for _, c2 in self.enc]
+        ci = [ch, *widths[:-1]]
+        for i, (c1, c2) in enumerate((*self.enc, *self.dec)):   # the shapes of the network as it was built
+            lv = i if i < len(widths) else 2 * len(widths) - 2 - i
+            want = ci[lv] if i < len(widths) else widths[lv + 1] + widths[lv]
+            if (c1.weight.shape != (widths[lv], want, 3, 3) or c2.weight.shape != (widths[lv], widths[lv], 3, 3)
+                    or c1.bias.shape != (widths[lv],) or c2.bias.shape != (widths[lv],)):
+                return None
+        if self.out.shape != (ch, widths[0]) or self.out_bias.shape != (ch,):
+            return None
+        levels, wd = len(widths), (C.c_int32 * len(widths))(*widths)
+        need = lib.dn_unet_bytes(ch, levels, wd, n, h, w)
+        if not need:
+            return None
+        y = torch.empty_like(x)
+        scratch = torch.empty(need, dtype=torch.uint8, device=x.device)
+        ptrs = C.c_void_p * len(layers)
+        L.check("dn_unet_forward", lib.dn_unet_forward(
+            ch, levels, wd, ptrs(*[c.weight.data_ptr() for c in layers]), ptrs(*[c.bias.data_ptr() for c in layers]),
+            self.out.data_ptr(), self.out_bias.data_ptr(), x.data_ptr(), (C.c_int64 * 4)(*x.stride()), y.data_ptr(),
+            (C.c_int64 * 4)(*y.stride()), scratch.data_ptr(), need, n, h, w, _stream()))
+        return y
+
     def forward(self, x):
+        if self._plain(x):
+            y = self._inference(x)
+            if y is not None:
+                return y
         skips = []
         h = x
         for i, (c1, c2) in enumerate(self.enc):
