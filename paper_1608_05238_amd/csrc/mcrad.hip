@@ -1694,17 +1694,18 @@ k_transport_tile(Gen G, int g) {
 // at that point hands its FP32 sums from one round's tally to the next
 // (carry), so every visit adds the same integers as in any other kernel.
 // Measured (start to end of mc_forward / mc_adjoint): 1e6 packets on a 256^2
-// disc 45.6 -> 23.2 ms, 5e5 adjoint packets at N = 32 on 149 x 101 34.1 -> 14.2
+// disc 45.6 -> 19.0 ms, 5e5 adjoint packets at N = 32 on 149 x 101 34.1 -> 13.1
 // ms, against generations and a finisher that added each visit to HBM.  What
 // bounds it now: for few packets the ~170 instructions of a segment in a lone
-// wave (0.5 us); for many, issue (62% busy) and memory latency in k_walk, the
-// LDS atomics (75% active) in k_tally.
+// wave (0.45 us); for many, issue in k_walk, the LDS atomics (75% active) in
+// k_tally.
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 constexpr uint32_t kRunSlice = 256;         // run slots a wave reserves at a time
 constexpr uint32_t kRunMax = 32;           // a longer run is cut at the end of a visit (tally lanes stay balanced)
-constexpr uint32_t kWalkLanes = 7u << 14;  // lanes that walk at once
+constexpr uint32_t kWalkLanes = 7u << 14;  // lanes that walk at once (kWalkRing)
+constexpr uint32_t kWalkLanesAll = 16u << 14;   // the same in runs of many packets (kWalkAll)
 constexpr uint32_t kWalkSpread = 1u << 10;  // waves that walk few packets
-constexpr uint32_t kWalkAhead = 64u * kWalkSpread;   // few packets: at most this many
+constexpr uint32_t kWalkFew = 64u * kWalkSpread;   // few packets: at most this many
 constexpr uint32_t kVisitEnd = 0x80000000u;
 // The handed-over packets are taken through one cursor per part, each on a
 // cache line of its own: a single cursor serialises the waves' atomics when
@@ -1848,27 +1849,34 @@ __device__ __forceinline__ void ledger_flush_lane(const ProbDev &O, const Ledger
         if (c[i]) atomicAdd(O.ledc + i, c[i]);
 }
 
-// A workgroup is two waves, one packet per lane of the first: that wave moves
-// the packets, the second keeps a ring of their next random blocks in LDS,
-// with what depends on the random numbers alone (free path, roulette draw,
-// factors of the deflection) worked out.  With few packets a pass costs the
-// latency of its instructions, and this takes half of them off the chain;
-// with many, a block is computed once per scatter instead of once per segment.
-// Workgroups this small spread over the CUs one by one, so that a few thousand
-// packets use every SIMD.  Each pass of the inner loop is one segment; runs,
-// refills and the space left are looked after every fourth.
-// ONE: a single problem, whose parameters are the same in every lane.
-// AHEAD: the round has few packets (kWalkAhead): they are spread over as many
-// waves as there are SIMDs, with free lanes in each (a wave waits for whatever
-// one of its lanes has to look after), and the medium of both pixels a packet
-// may enter next is loaded a segment ahead.
-template <bool ONE, bool AHEAD>
+// One packet per lane; each pass of the inner loop is one segment, and runs,
+// refills and the space left are looked after every fourth.  ONE: a single
+// problem, whose parameters are the same in every lane.  The passes' random
+// numbers come in one of three ways:
+//  * kWalkAll: a wave works out its own.  Bound by issue, with 16 waves a CU
+//    (1.34e8 events of 1e6 packets on a 256^2 disc: 1.1 - 1.3 ms, against 1.6
+//    with rings, whose LDS leaves room for 7 workgroups a CU).
+//  * kWalkRing: a workgroup is two waves; the first moves the packets, the
+//    second keeps a ring of their next random blocks in LDS, with what depends
+//    on the random numbers alone (free path, roulette draw, factors of the
+//    deflection) worked out.  With few packets a pass costs the latency of its
+//    instructions, and this takes half of them off the chain (1e5 packets of a
+//    32^2 pencil beam 0.97 ms, 1.05 with kWalkAll).
+//  * kWalkAhead: so few packets (kWalkFew) that they are spread over as many
+//    waves as there are SIMDs, with free lanes in each (a wave waits for
+//    whatever one of its lanes has to look after); rings as above, and the
+//    medium of both pixels a packet may enter next is loaded a segment ahead.
+enum : int { kWalkAll = 0, kWalkRing = 1, kWalkAhead = 2 };
+
+template <bool ONE, int MODE>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k_walk(Walk W, int r) {
     // entry k % kRing: roulette draw, cos and sin factors of block k, optical depth of block k + 1
-    __shared__ float4 ring[kRing][64];
+    constexpr bool RINGS = MODE != kWalkAll, AHEAD = MODE == kWalkAhead;
+    constexpr int R = RINGS ? kRing : 1, RL = RINGS ? 64 : 1;
+    __shared__ float4 ring[R][RL];
     // what the first wave posts, by parity of the post
-    __shared__ uint32_t s_k[2][64], s_new[2][64], s_prob[2][64];
-    __shared__ uint64_t s_pid[2][64];
+    __shared__ uint32_t s_k[2][RL], s_new[2][RL], s_prob[2][RL];
+    __shared__ uint64_t s_pid[2][RL];
     __shared__ uint32_t s_stop[2];
     // four events per lane on their way to memory; lane l's event u of a batch
     // is at (4 l + (l / 4) % 4) ^ u, which spreads both sides over the banks
@@ -1876,12 +1884,12 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
     WalkCtl *C = W.ctl;
     if ((uint32_t)r >= C->w_end) return;
     const uint32_t lanes = C->lanes;
-    if ((lanes <= kWalkAhead) != AHEAD) return;
+    if ((lanes <= kWalkFew) != AHEAD) return;
     const uint32_t per = AHEAD ? min(64u, (lanes + kWalkSpread - 1u) / kWalkSpread) : 64u;   // lanes a wave uses
     if (blockIdx.x * per >= lanes) return;
     const int lane = __lane_id();
 
-    if (threadIdx.x >= 64u) {
+    if (RINGS && threadIdx.x >= 64u) {
         uint64_t seed = W.probs[0].seed, pid = 0;
         uint32_t tag = W.probs[0].tag;
         uint32_t have = 0;   // blocks up to this one are in the ring
@@ -1890,14 +1898,14 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         for (uint32_t side = 0;; side ^= 1u) {
             __syncthreads();
             if (s_stop[side]) break;
-            const uint32_t k = s_k[side][lane];
+            const uint32_t k = s_k[side][lane % RL];
             const bool live = k != kNoSlot;
-            if (s_new[side][lane]) {
+            if (s_new[side][lane % RL]) {
                 have = k - 1u;
-                pid = s_pid[side][lane];
+                pid = s_pid[side][lane % RL];
                 if constexpr (!ONE) {
-                    seed = W.probs[s_prob[side][lane]].seed;
-                    tag = W.probs[s_prob[side][lane]].tag;
+                    seed = W.probs[s_prob[side][lane % RL]].seed;
+                    tag = W.probs[s_prob[side][lane % RL]].tag;
                 }
             }
             // Until the next post the first wave uses blocks up to k + 4 and the
@@ -1912,8 +1920,8 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
                     const float tau = __builtin_amdgcn_logf(u01(b.x)) * -0.693147180559945309f;   // see new_leg
                     float sp, cp;
                     hg_factors(u01(b.y), sp, cp);
-                    ring[(have - 1u) % kRing][lane].w = tau;
-                    float4 &e = ring[have % kRing][lane];
+                    ring[(have - 1u) % R][lane % RL].w = tau;
+                    float4 &e = ring[have % R][lane % RL];
                     e.x = u01(b.z);
                     e.y = cp;
                     e.z = sp;
@@ -2022,14 +2030,16 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         k0 = p.k;
         const uint32_t in_visit = goes_on && rec->tile != 0u ? 1u : 0u;
         resume = in_visit ? gid : kNoSlot;
-        fl = kWait | in_visit;
+        fl = (RINGS ? kWait : kMove) | in_visit;
     };
     // One segment, its end and, if it is scattered, its next direction: the
     // arithmetic of scatter_roulette() and scatter_deflect(), operation by
     // operation.
     auto pass = [&](uint32_t u) {
 #pragma clang fp contract(off)
-        const float4 rnd = ring[p.k % kRing][lane];   // for a scatter at the segment's end
+        // for a scatter at the segment's end
+        float4 rnd = make_float4(p.ur, 0.f, 0.f, 0.f);
+        if constexpr (RINGS) rnd = ring[p.k % R][lane % RL];
         uint32_t ev = (uint32_t)(__mul24(p.iz, tw) + p.ix);
         const float sx = p.sx, sz = p.sz, g = mm.w;   // direction of the segment, before any scatter
         const Segment S = segment(p, a, mm);
@@ -2059,11 +2069,13 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         L.absorbed += (double)S.dw;
         if (go) {
             float nx_, nz_;
+            if constexpr (!RINGS) hg_factors(p.uh, rnd.z, rnd.y);
             hg_rotate(g, rnd.z, rnd.y, sx, sz, nx_, nz_);
             set_dir(p, nx_, nz_);
             a = ahead_of(nx_, nz_);
             ++p.k;
-            p.tau = rnd.w;
+            if constexpr (RINGS) p.tau = rnd.w;
+            else new_leg(Q.H, p);
         }
         if constexpr (AHEAD) {
             // taken as late as can be: the loads have had a whole pass
@@ -2137,16 +2149,20 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
             lim = min(cap - 3u, run0 + kRunMax);
         }
         const uint32_t side = post++ & 1u;
-        s_k[side][lane] = fl < kLeft || fl >= kWait ? p.k : kNoSlot;
-        s_new[side][lane] = fresh;
-        if (fresh) {
-            s_pid[side][lane] = p.pid;
-            s_prob[side][lane] = (uint32_t)prob;
-        }
         const bool stop = !__ballot(fl < kLeft || fl >= kWait || fl == kEmpty);
-        if (lane == 0) s_stop[side] = stop ? 1u : 0u;
-        __syncthreads();
-        if (stop) break;
+        if constexpr (!RINGS) {
+            if (stop) break;
+        } else {
+            s_k[side][lane % RL] = fl < kLeft || fl >= kWait ? p.k : kNoSlot;
+            s_new[side][lane % RL] = fresh;
+            if (fresh) {
+                s_pid[side][lane % RL] = p.pid;
+                s_prob[side][lane % RL] = (uint32_t)prob;
+            }
+            if (lane == 0) s_stop[side] = stop ? 1u : 0u;
+            __syncthreads();
+            if (stop) break;
+        }
         const unsigned long long moved = __ballot(fl < kLeft);
         const uint32_t n4 = n;   // a multiple of 4 in lanes that move
 #pragma unroll
@@ -2170,9 +2186,11 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
         const uint32_t slot = wave_claim(&C->n_state(par ^ 1), (uint32_t)__popcll(m)) + rank_in(m);
         if (going) {
             L.scatters += p.k - k0;
-            const uint4 b = rng_block(Q.H, p.pid, p.k);   // the record holds the draws of its block
-            p.uh = u01(b.y);
-            p.ur = u01(b.z);
+            if constexpr (RINGS) {
+                const uint4 b = rng_block(Q.H, p.pid, p.k);   // the record holds the draws of its block
+                p.uh = u01(b.y);
+                p.ur = u01(b.z);
+            }
             Packet q = p;
             q.ix += tx0;
             q.iz += tz0;
@@ -3353,7 +3371,11 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
             65536, kGenBase + kGenPerTile * side + kGenPerPool * ((B.total_packets + B.live - 1) / B.live));
     }
     if (walk) {
-        const uint64_t most = std::min<uint64_t>(B.direct ? B.total_packets : std::min(B.finish, B.live), kWalkLanes);
+        // twice as many packets as lanes keep the lanes busy to a round's end
+        // (1e6 packets on a 256^2 disc 17.7 ms with kWalkLanesAll, 18.4 with
+        // kWalkLanes; 2e5 on 48^2 five times 5.4 and 5.1)
+        const uint64_t walkers = B.direct ? B.total_packets : std::min(B.finish, B.live);
+        const uint64_t most = std::min<uint64_t>(walkers, walkers >= 2 * kWalkLanesAll ? kWalkLanesAll : kWalkLanes);
         B.lanes = (most + 63) & ~63ull;
         B.ev_cap = std::min<uint64_t>(B.tt.ev_max, most * kWalkEventsPerLane);
         // a run takes four events or more; up to 63 of a slice's slots stay empty
@@ -3626,10 +3648,13 @@ mc_status enqueue_rounds(const Walk &W, const BatchLayout &B, int N, int n_gen, 
         LaunchTimer tw(timer);
         if ((st = tw.begin(s)) != MC_OK) return st;
         const bool one = W.runs.nprob == 1;
-        if (B.lanes > kWalkAhead)
-            hipLaunchKernelGGL((one ? k_walk<true, false> : k_walk<false, false>), dim3((unsigned)(B.lanes / 64)),
+        if (B.lanes > kWalkLanes)
+            hipLaunchKernelGGL((one ? k_walk<true, kWalkAll> : k_walk<false, kWalkAll>), dim3((unsigned)(B.lanes / 64)),
+                               dim3(64), 0, s, W, (int)r);
+        else if (B.lanes > kWalkFew)
+            hipLaunchKernelGGL((one ? k_walk<true, kWalkRing> : k_walk<false, kWalkRing>), dim3((unsigned)(B.lanes / 64)),
                                dim3(128), 0, s, W, (int)r);
-        hipLaunchKernelGGL((one ? k_walk<true, true> : k_walk<false, true>),
+        hipLaunchKernelGGL((one ? k_walk<true, kWalkAhead> : k_walk<false, kWalkAhead>),
                            dim3((unsigned)std::min<uint64_t>(B.lanes, kWalkSpread)), dim3(128), 0, s, W, (int)r);
         if ((st = tw.end(s)) != MC_OK) return st;
         hipLaunchKernelGGL(k_run_count, dim3(cgrid), dim3(kGenBlock), count_lds, s, W, (int)r);
