@@ -552,7 +552,7 @@ __global__ void __launch_bounds__(kThreads) k_conv3x3_wgrad(const uint16_t *__re
 // four waves, and runs over every gridDim.x-th 16 x 8 pixel block, the next
 // one in flight in registers.  The workgroups' parts are written to a scratch
 // buffer and added in order by k_wgrad_sum: the result does not depend on
-// timing.  16 x 256^2 pixels, 48 x 48 channels: 94 us, the sum 24 us; from a
+// timing.  16 x 256^2 pixels, 48 x 48 channels: 90 us, the sum 9 us; from a
 // converted copy (26 us), with transposing stores to LDS, three shifted copies
 // of the halo and atomics 267 us, and 86 us for the bias gradient.
 constexpr int kWY = 8, kWX = 16, kWHalo = (kWY + 2) * (kWX + 2);
@@ -702,31 +702,35 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
     }
 }
 
-// gw[co][ci][3][3] and gb[co] from the slices' parts.  Sixteen lanes share a
-// value's slices; the sums over slices are FP64 (rounding is then that of the
-// parts: relative error of the bias gradient of 16 x 256^2 pixels 3e-8).
-__global__ void __launch_bounds__(256) k_wgrad_sum(const float *part, const float *bpart, float *gw, float *gb, int slices,
-                                                   int ty, int tz, int mb, int nb, int co, int ci) {
-    const int frag = 9 * nb * mb * 256, bt = ty * 16 * mb;   // a workgroup's 16 values are of one tile
-    const long long total = (long long)ty * tz * frag, v = blockIdx.x * 16ll + (threadIdx.x >> 4);
-    const int sub = threadIdx.x & 15;
-    const float *src = nullptr;
-    size_t step = 0;
-    if (v < total) {
-        src = part + v;
-        step = total;
-    } else if (v < total + bt) {
-        src = bpart + (v - total);
-        step = bt;
-    }
+// gw[co][ci][3][3] and gb[co] from the slices' parts.  A lane takes a value, the
+// sixteen waves of a workgroup share its slices (so a load is of 64
+// consecutive values), and the first adds their sums in order; the sums over
+// slices are FP64 (rounding is then that of the parts: relative error of the
+// bias gradient of 16 x 256^2 pixels 3e-8).  Bound by the parts' bytes and, with
+// few values, by latency: 512 slices of 48 x 48 channels, 42 MB, 9 us (24
+// with a value's slices in consecutive lanes).
+constexpr int kSumWaves = 16;
+
+__global__ void __launch_bounds__(64 * kSumWaves) k_wgrad_sum(const float *part, const float *bpart, float *gw, float *gb,
+                                                              int slices, int ty, int tz, int mb, int nb, int co, int ci) {
+    __shared__ double s_sum[kSumWaves][64];
+    const int frag = 9 * nb * mb * 256, bt = ty * 16 * mb;   // a workgroup's 64 values are of one tile
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long total = (long long)ty * tz * frag, v = blockIdx.x * 64ll + lane;
+    const bool bias = v >= total;
+    const size_t step = bias ? (size_t)bt : (size_t)total;
+    const float *src = bias ? bpart + (v - total) : part + v;
     double sum = 0.;
-    if (src)
-        for (int k = sub; k < slices; k += 16) sum += src[(size_t)k * step];
+    if (v < total + bt)
+#pragma unroll 8
+        for (int k = wave; k < slices; k += kSumWaves) sum += src[(size_t)k * step];
+    s_sum[wave][lane] = sum;
+    __syncthreads();
+    if (wave != 0 || v >= total + bt) return;
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if (sub != 0 || !src) return;
-    if (v < total) {
-        const int tile = blockIdx.x / (frag / 16), e = (int)(v - (long long)tile * frag), pair = e / (mb * 256), a = e / 256 - pair * mb, l = (e & 255) >> 2;
+    for (int w = 1; w < kSumWaves; ++w) sum += s_sum[w][lane];
+    if (!bias) {
+        const int tile = blockIdx.x / (frag / 64), e = (int)(v - (long long)tile * frag), pair = e / (mb * 256), a = e / 256 - pair * mb, l = (e & 255) >> 2;
         const int c = (tile / tz) * 16 * mb + 16 * a + 4 * (l >> 4) + (e & 3);
         const int k = (tile % tz) * 16 * nb + 16 * (pair % nb) + (l & 15);
         if (c < co && k < ci) gw[((size_t)c * ci + k) * 9 + pair / nb] = (float)sum;
@@ -902,7 +906,7 @@ struct WgradPlan {
     int mb, nb, ty, tz, slices;
     size_t part_floats() const { return (size_t)slices * ty * tz * 9 * nb * mb * 256; }
     size_t bias_floats() const { return (size_t)slices * ty * 16 * mb; }
-    long long sum_blocks() const { return ((long long)ty * tz * 9 * nb * mb * 256 + (long long)ty * 16 * mb + 15) / 16; }
+    long long sum_blocks() const { return ((long long)ty * tz * 9 * nb * mb * 256 + (long long)ty * 16 * mb + 63) / 64; }
 };
 
 // Two workgroups a CU over all channel tiles, no more than there are blocks; up
@@ -1088,7 +1092,7 @@ mc_status dn_conv3x3_grads(const uint16_t *xb_d, const float *gy_d, float *gw_d,
     A.n_tiles = n * A.tiles_x * A.tiles_y;
     const bool vec = (co & 7) == 0 && aligned16(gy_d);
     wgrad_fn(P.mb, P.nb, vec)<<<dim3(P.slices, P.ty, P.tz), dim3(kThreads), 0, s>>>(A);
-    hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)P.sum_blocks()), dim3(256), 0, s, A.part, A.bpart, gw_d, gb_d, P.slices,
+    hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)P.sum_blocks()), dim3(64 * kSumWaves), 0, s, A.part, A.bpart, gw_d, gb_d, P.slices,
                        P.ty, P.tz, P.mb, P.nb, co, ci);
     return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
 }
