@@ -627,7 +627,7 @@ def main() -> int:
     ops = algo_ops(segments, scatters, packets, N)
     achieved = per_launch(ops) / launch_s if tr_launches else 0.0
     value = 2 * Np * args.steps / (ms_total * 1e-3)
-    kern = "k_transport_tile<16> + k_finish<16>"
+    kern = "k_transport_tile<16> + k_walk, k_tally<16> + k_finish<16>"
     out = {
         "metric": "packets/s fwd+adj MC (N=16 harmonics)",
         "value": value,
