@@ -152,10 +152,10 @@ typedef struct {
  *                 kernel).  A run of few packets that the pool holds at once
  *                 does so from its launch.  (default: the smaller of 2^16
  *                 and live_packets / 128)
- *  grid_max_packets  mc_run_noalloc: a run whose tally fits one workgroup's
- *                 LDS uses the whole-grid kernel only up to this many
- *                 packets, larger runs the tiled transport (default 2^21);
- *                 the other entry points have no whole-grid runs
+ *  grid_max_packets  a single run whose tally fits one workgroup's LDS uses
+ *                 the whole-grid kernel up to this many packets, larger
+ *                 runs the tiled transport (default 2^21); up to 2^17
+ *                 packets it walks instead, except in mc_run_noalloc
  *  flush_track    a pixel visit whose accumulated track length, in units of
  *                 the run's weight bound, exceeds this many pixels is added
  *                 to the tile tally in parts, 0 .. 65536 (default 65536)

@@ -3157,7 +3157,14 @@ constexpr uint64_t kDirectMax = 3ull << 19;
 constexpr uint64_t kWalkEvents = 1ull << 27;         // events a round may write
 constexpr uint64_t kWalkEventsPerLane = 1ull << 14;  // or this many per lane if that is less
 constexpr uint32_t kWalkRounds = 2;                  // rounds enqueued: these, and as many as events are expected
-constexpr uint64_t kWalkRoundEvents = 6144;          // per packet
+// Rounds are enqueued for this many events per packet, or, in a run that walks
+// from its launch, for kWalkSideEvents per pixel of the longest grid's width and
+// height if that is less: a history ends at the boundary, and a round that finds
+// nothing to do still costs five launches (1.7e5 packets on 9 x 19 pixels 0.49
+// ms with nine rounds, 0.44 with three).  The finisher takes what they leave.
+constexpr uint64_t kWalkRoundEvents = 6144;
+constexpr uint64_t kWalkSideEvents = 48;
+constexpr uint64_t kWalkGridMax = 1ull << 17;        // packets: see is_tiled
 constexpr uint32_t kRunJobMin = 256;                  // smallest tally job of a round with few runs
 
 // The tuning a call runs with: the caller's fields, defaults where zero.
@@ -3238,17 +3245,19 @@ size_t tile_lds_bytes(int tw, int th, int K) {
     return tal + (size_t)tw * th * (sizeof(float4) + sizeof(uint32_t));
 }
 
-// The whole-grid transport serves runs that have no event buffer for walk and
-// tally (mc_run_noalloc), if the whole tally (8 bytes per value) fits one
-// workgroup's LDS and the run is small (generations alone cost ~10 ms a run;
+// The whole-grid transport serves runs whose tally (8 bytes per value) fits one
+// workgroup's LDS, up to grid_max packets (generations alone cost ~10 ms a run;
 // measured on a 32x32 pencil beam, they overtake the whole-grid kernel near
-// 2e6 packets and are 5x faster at 1e8).  With the buffer, walking is faster
-// at every size: 32x32, N = 8: 1e3 packets 0.95 against 1.68 ms, 1e5 1.5
-// against 2.1, 2e6 7.7 against 18.6.
+// 2e6 packets and are 5x faster at 1e8).  Where there is an event buffer
+// (everywhere but in mc_run_noalloc), runs of few packets, bound by their
+// longest histories, walk: 32x32 pencil beam, 1e5 packets 1.0 against 1.5 ms;
+// 32x32 at mus 12 / mm, g 0.7, 1e5 packets 9.3 against 14.5, 2e5 12.0 and 15.3,
+// 3e5 16.1 and 17.0, 6e5 25.4 and 19.6; 12x10 of that medium 7.8 and 10.6, 10.7
+// and 11.0, 13.4 and 11.9, 20.0 and 14.3.  (More packets in a thin medium walk
+// faster too, but what a medium is like only the device knows.)
 bool is_tiled(const mc_medium *m, const mc_run *run, const TileTuning &tt) {
-    if (tt.ev_max) return true;
     if ((size_t)m->nx * m->nz * (2 * run->n_harm + 1) * sizeof(double) > kLdsGridMax) return true;
-    return run->n_packets > tt.grid_max;
+    return run->n_packets > tt.grid_max || (tt.ev_max && run->n_packets <= kWalkGridMax);
 }
 
 // Whole-grid mode workspace: problem, medium, CDF, tally, ledger, per-chunk counters.
@@ -3382,7 +3391,13 @@ BatchLayout batch_layout(const BatchProblem *pb, int n, const TileTuning &tt) {
         B.run_cap = B.ev_cap / 4 * kRunSlice / (kRunSlice - 63) + kRunSlice * (B.lanes / 64 + 1);
         B.run_jobs = (uint64_t)B.ntiles + std::max<uint64_t>(B.run_cap / kJobSize, 2ull * kTileSlotsMax) + 2;
         // every round but the last ones fills the buffer
-        B.rounds = kWalkRounds + (uint32_t)((B.direct ? B.total_packets : B.finish) * kWalkRoundEvents / B.ev_cap);
+        uint64_t events = kWalkRoundEvents * (B.direct ? B.total_packets : B.finish);
+        if (B.direct) {
+            uint64_t side = 0;
+            for (int i = 0; i < n; ++i) side = std::max<uint64_t>(side, (uint64_t)pb[i].m->nx + pb[i].m->nz);
+            events = std::min(kWalkRoundEvents, kWalkSideEvents * side) * B.total_packets;
+        }
+        B.rounds = kWalkRounds + (uint32_t)(events / B.ev_cap);
         if (B.direct && tt.max_gen) B.rounds = tt.max_gen;
     }
     B.probs = off;
