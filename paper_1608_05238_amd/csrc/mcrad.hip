@@ -2909,17 +2909,41 @@ __global__ void k_normalise(const ProbDev *pd, int N, const GenCtl *ctl, const W
 // up to kRedBlocks workgroups; its value does not depend on their order (each
 // leaves its part, and the last to finish adds the parts in theirs).  The
 // parts need memory that no other call in flight uses: a slot of a pool held
-// by the device, taken by a kernel on the caller's stream (red_begin), which
+// by the device, taken by a kernel on the caller's stream (k_red_begin), which
 // hands its number on through the result's own eight bytes, and given back by
 // the workgroup that writes the result.  With every slot taken, the first
 // workgroup computes all parts itself.  256^2, N = 16: mc_detect 509 -> 16 us,
 // mc_residual 29 -> 12 us against one workgroup (with 2 us of k_red_begin).
+//
+// A slot's number is handed on as a signalling NaN that no sum can be
+// (red_store): a workgroup that starts after the first one has written the
+// result must not take the sum for a slot.
 constexpr int kRedBlocks = 256, kRedThreads = 256, kRedSlots = 64;
+constexpr unsigned long long kRedTag = 0x7FF4526564530000ull, kRedQuiet = 0x0008000000000000ull;
 struct RedSlot {
     uint32_t busy, done;
     double part[kRedBlocks];
 };
 __device__ RedSlot red_slots[kRedSlots];
+
+// The slot (1 .. kRedSlots) that the result's bytes name; 0: none.
+__device__ __forceinline__ uint32_t red_slot(const double *result) {
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(result),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return v > kRedTag && v <= kRedTag + kRedSlots ? (uint32_t)(v - kRedTag) : 0u;
+}
+
+__device__ __forceinline__ void red_store(double *result, double v) {
+    unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
+    if (v != v) bits |= kRedQuiet;   // (what an operation gives is quiet already)
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(result), bits, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void red_release(RedSlot &R) {
+    __threadfence();
+    __hip_atomic_store(&R.busy, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __global__ void __launch_bounds__(kRedSlots) k_red_begin(unsigned long long *result) {
     const int t = threadIdx.x;
@@ -2932,11 +2956,20 @@ __global__ void __launch_bounds__(kRedSlots) k_red_begin(unsigned long long *res
         if (t == leader) got = atomicCAS(&red_slots[t].busy, 0u, 1u) == 0u;
         open = open && t != leader;
         if (__ballot(got)) {
-            if (got) *result = (unsigned long long)t + 1ull;
+            if (got) {
+                __hip_atomic_store(&red_slots[t].done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                *result = kRedTag + (unsigned long long)t + 1ull;
+            }
             return;
         }
     }
     if (t == 0) *result = 0ull;   // no slot
+}
+
+// Gives back the slot of a sum that was not launched.
+__global__ void k_red_cancel(double *result) {
+    const uint32_t slot = red_slot(result);
+    if (slot) red_release(red_slots[slot - 1u]);
 }
 
 // Sum over the workgroup's threads, valid in the first.
@@ -2959,14 +2992,16 @@ __device__ __forceinline__ void sum_over(int n, double scale, double *result, F 
     __shared__ double part[kRedBlocks];
     __shared__ uint32_t s_last;
     const int nb = gridDim.x, t = threadIdx.x;
-    const unsigned long long slot = *reinterpret_cast<const unsigned long long *>(result);
+    // read before any workgroup can have written the result, or after the first
+    // one has, which has no slot then and writes none
+    const uint32_t slot = red_slot(result);
     auto part_of = [&](int b) {
         double s = 0;
         for (int i = b * kRedThreads + t; i < n; i += nb * kRedThreads) s += term(i);
         return block_sum(s, red);
     };
     if (slot) {
-        RedSlot &R = red_slots[slot - 1ull];
+        RedSlot &R = red_slots[slot - 1u];
         const double s = part_of(blockIdx.x);
         if (t == 0) {
             __hip_atomic_store(&R.part[blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2979,10 +3014,8 @@ __device__ __forceinline__ void sum_over(int n, double scale, double *result, F 
         const double v = t < nb ? __hip_atomic_load(&R.part[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
         const double all = block_sum(v, red);
         if (t == 0) {
-            *result = scale * all;
-            __hip_atomic_store(&R.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __threadfence();
-            __hip_atomic_store(&R.busy, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            red_store(result, scale * all);
+            red_release(R);
         }
         return;
     }
@@ -2993,11 +3026,19 @@ __device__ __forceinline__ void sum_over(int n, double scale, double *result, F 
     }
     __syncthreads();
     const double all = block_sum(t < nb ? part[t] : 0.0, red);
-    if (t == 0) *result = scale * all;
+    if (t == 0) red_store(result, scale * all);
 }
 static_assert(kRedBlocks <= kRedThreads, "the last workgroup adds one part a thread");
 
 unsigned red_blocks(int n) { return (unsigned)std::min((n + kRedThreads - 1) / kRedThreads, kRedBlocks); }
+
+// After the launch of a sum: if it failed, its slot goes back.  (If the error is
+// an older one, the sum has written its result by then: nothing to give back.)
+mc_status red_launched(double *result, hipStream_t s) {
+    if (hipGetLastError() == hipSuccess) return MC_OK;
+    hipLaunchKernelGGL(k_red_cancel, dim3(1), dim3(1), 0, s, result);
+    return MC_ERR_DEVICE;
+}
 
 // Residual (Sec. 2, Sec. 6).
 __global__ void __launch_bounds__(kRedThreads) k_residual(int npix, double area, const float *mua, const double *a0,
@@ -4099,7 +4140,7 @@ mc_status mc_residual(const mc_medium *m, const double *coeffs_d, const double *
     hipLaunchKernelGGL(k_red_begin, dim3(1), dim3(kRedSlots), 0, s, reinterpret_cast<unsigned long long *>(eps_d));
     hipLaunchKernelGGL(k_residual, dim3(red_blocks(npix)), dim3(kRedThreads), 0, s, npix, (double)m->dx * m->dx,
                        m->mua_d, coeffs_d, hmeas_d, q_star_d, eps_d);
-    return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+    return red_launched(eps_d, s);
 }
 
 mc_status mc_gradient(const mc_medium *m, int n_harm, const double *fwd_d, const double *adj_d, const double *hmeas_d,
@@ -4152,7 +4193,7 @@ mc_status mc_detect(const mc_medium *m, int n_harm, const double *coeffs_d, cons
     hipLaunchKernelGGL(k_red_begin, dim3(1), dim3(kRedSlots), 0, s, reinterpret_cast<unsigned long long *>(out_d));
     hipLaunchKernelGGL(k_detect, dim3(red_blocks(npix)), dim3(kRedThreads), 0, s, npix, n_harm,
                        (double)m->dx * m->dx, coeffs_d, det_d, out_d);
-    return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+    return red_launched(out_d, s);
 }
 
 mc_status mc_trace(const mc_medium *m, const mc_source *src, int n_src, const mc_run *run, int adjoint,
