@@ -2985,16 +2985,18 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
     return s;
 }
 
-// *result = scale * sum of term(i) over i < n; gridDim.x <= kRedBlocks.
+// *result = scale * sum of term(i) over i < n, in nb <= kRedBlocks parts; term is
+// called once for each i.  `alone`: the grid is one workgroup, and the result is
+// not touched before every term is done (it may lie in what they read).
 template <class F>
-__device__ __forceinline__ void sum_over(int n, double scale, double *result, F term) {
+__device__ __forceinline__ void sum_over(int n, int nb, bool alone, double scale, double *result, F term) {
     __shared__ double red[kRedThreads];
     __shared__ double part[kRedBlocks];
     __shared__ uint32_t s_last;
-    const int nb = gridDim.x, t = threadIdx.x;
+    const int t = threadIdx.x;
     // read before any workgroup can have written the result, or after the first
     // one has, which has no slot then and writes none
-    const uint32_t slot = red_slot(result);
+    const uint32_t slot = alone ? 0u : red_slot(result);
     auto part_of = [&](int b) {
         double s = 0;
         for (int i = b * kRedThreads + t; i < n; i += nb * kRedThreads) s += term(i);
@@ -3040,16 +3042,21 @@ mc_status red_launched(double *result, hipStream_t s) {
     return MC_ERR_DEVICE;
 }
 
-// Residual (Sec. 2, Sec. 6).
-__global__ void __launch_bounds__(kRedThreads) k_residual(int npix, double area, const float *mua, const double *a0,
-                                                          const double *hmeas, double *qs, double *eps) {
-    if (qs)
-        for (int i = blockIdx.x * kRedThreads + threadIdx.x; i < npix; i += gridDim.x * kRedThreads) {
-            const double m = mua[i];
-            qs[i] = m * (hmeas[i] - m * a0[i]);
-        }
-    sum_over(npix, 0.5 * area, eps, [=](int i) {
-        const double r = hmeas[i] - (double)mua[i] * a0[i];
+// Whether the result's eight bytes lie in the given range.
+bool in_range(const double *result, const void *p, size_t bytes) {
+    const uintptr_t r = reinterpret_cast<uintptr_t>(result), a = reinterpret_cast<uintptr_t>(p);
+    return p && r + sizeof(double) > a && r < a + bytes;
+}
+
+// Residual (Sec. 2, Sec. 6).  In one pass, so that qs may be hmeas or a0: a
+// thread reads a pixel once, before it writes it.
+__global__ void __launch_bounds__(kRedThreads) k_residual(int npix, int nb, bool alone, double area, const float *mua,
+                                                          const double *a0, const double *hmeas, double *qs,
+                                                          double *eps) {
+    sum_over(npix, nb, alone, 0.5 * area, eps, [=](int i) {
+        const double m = mua[i];
+        const double r = hmeas[i] - m * a0[i];
+        if (qs) qs[i] = m * r;
         return r * r;
     });
 }
@@ -3091,9 +3098,9 @@ __global__ void k_adjoint_source(int npix, double inv_area, const float *mua, co
     if (i < npix) qs[i] = -(double)mua[i] * gh[i] * inv_area;
 }
 
-__global__ void __launch_bounds__(kRedThreads) k_detect(int npix, int N, double area, const double *c, const double *d,
-                                                        double *out) {
-    sum_over(npix, area, out, [=](int i) {
+__global__ void __launch_bounds__(kRedThreads) k_detect(int npix, int nb, bool alone, int N, double area,
+                                                        const double *c, const double *d, double *out) {
+    sum_over(npix, nb, alone, area, out, [=](int i) {
         const double ip = 0.31830988618379067154;
         double v = c[i] * d[i] * (0.5 * ip);
 #pragma unroll 4
@@ -4137,9 +4144,15 @@ mc_status mc_residual(const mc_medium *m, const double *coeffs_d, const double *
         return MC_ERR_INVALID_ARG;
     const int npix = m->nx * m->nz;
     const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(k_red_begin, dim3(1), dim3(kRedSlots), 0, s, reinterpret_cast<unsigned long long *>(eps_d));
-    hipLaunchKernelGGL(k_residual, dim3(red_blocks(npix)), dim3(kRedThreads), 0, s, npix, (double)m->dx * m->dx,
-                       m->mua_d, coeffs_d, hmeas_d, q_star_d, eps_d);
+    const size_t map = (size_t)npix * sizeof(double);
+    const bool alone = in_range(eps_d, hmeas_d, map) || in_range(eps_d, coeffs_d, map) || in_range(eps_d, q_star_d, map) ||
+                       in_range(eps_d, m->mua_d, (size_t)npix * sizeof(float));
+    const unsigned nb = red_blocks(npix);
+    if (!alone)
+        hipLaunchKernelGGL(k_red_begin, dim3(1), dim3(kRedSlots), 0, s, reinterpret_cast<unsigned long long *>(eps_d));
+    hipLaunchKernelGGL(k_residual, dim3(alone ? 1 : nb), dim3(kRedThreads), 0, s, npix, (int)nb, alone,
+                       (double)m->dx * m->dx, m->mua_d, coeffs_d, hmeas_d, q_star_d, eps_d);
+    if (alone) return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
     return red_launched(eps_d, s);
 }
 
@@ -4190,9 +4203,14 @@ mc_status mc_detect(const mc_medium *m, int n_harm, const double *coeffs_d, cons
     if (n_harm < 0 || n_harm > MC_NHARM_MAX) return MC_ERR_INVALID_ARG;
     const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int npix = m->nx * m->nz;
-    hipLaunchKernelGGL(k_red_begin, dim3(1), dim3(kRedSlots), 0, s, reinterpret_cast<unsigned long long *>(out_d));
-    hipLaunchKernelGGL(k_detect, dim3(red_blocks(npix)), dim3(kRedThreads), 0, s, npix, n_harm,
+    const size_t maps = (size_t)npix * (2 * n_harm + 1) * sizeof(double);
+    const bool alone = in_range(out_d, coeffs_d, maps) || in_range(out_d, det_d, maps);
+    const unsigned nb = red_blocks(npix);
+    if (!alone)
+        hipLaunchKernelGGL(k_red_begin, dim3(1), dim3(kRedSlots), 0, s, reinterpret_cast<unsigned long long *>(out_d));
+    hipLaunchKernelGGL(k_detect, dim3(alone ? 1 : nb), dim3(kRedThreads), 0, s, npix, (int)nb, alone, n_harm,
                        (double)m->dx * m->dx, coeffs_d, det_d, out_d);
+    if (alone) return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE;
     return red_launched(out_d, s);
 }
 
