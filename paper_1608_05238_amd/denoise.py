@@ -176,6 +176,8 @@ class UNet(nn.Module):
         not take this network or size."""
         lib, layers = L.load(), self._layers()
         n, ch, h, w = x.shape
+        if len(self.dec) != len(self.enc) - 1:   # not the network as it was built: the layers below say what is wrong
+            return None
         widths = [c2.weight.shape[0] for _, c2 in self.enc]
         ci = [ch, *widths[:-1]]
         for i, (c1, c2) in enumerate((*self.enc, *self.dec)):   # the shapes of the network as it was built
