@@ -49,7 +49,7 @@ def _packed(w: torch.Tensor, flip: bool) -> torch.Tensor:
     """Weights [co][ci][3][3] as the kernels read them (dn_pack_weights)."""
     co, ci = w.shape[:2]
     rows, cols = (ci, _pad8(co)) if flip else (co, _pad8(ci))
-    w = w.detach()
+    w = w.detach().resolve_neg()   # (a view may carry a sign that its memory does not)
     if w.dtype != torch.float32:   # rounded to BF16 once, from its own type
         w = w.to(torch.bfloat16).float()
     w = w.contiguous()
@@ -79,10 +79,10 @@ class _Conv3x3(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, w, b, keep):
-        x = x.detach()
+        x = x.detach().resolve_neg()
         if x.dtype != torch.float32:   # rounded to BF16 once, from its own type
             x = x.to(torch.bfloat16).float()
-        y, xb = _conv(x, _packed(w, False), b.detach().float().contiguous(), w.shape[0],
+        y, xb = _conv(x, _packed(w, False), b.detach().resolve_neg().float().contiguous(), w.shape[0],
                       keep and ctx.needs_input_grad[1])
         ctx.save_for_backward(xb, w.detach())
         ctx.shape = tuple(x.shape)
@@ -94,7 +94,7 @@ class _Conv3x3(torch.autograd.Function):
         xb, w = ctx.saved_tensors
         n, ci, h, wd = ctx.shape
         co = w.shape[0]
-        gy = gy.detach().float()
+        gy = gy.detach().resolve_neg().float()
         gx = gw = gb = None
         if ctx.needs_input_grad[0]:
             # the input gradient: the same convolution with the weights flipped
@@ -169,7 +169,7 @@ class UNet(nn.Module):
         for c in layers:
             tensors += [c.weight, c.bias]
         return all(type(t) in (torch.Tensor, nn.Parameter) and t.dtype == torch.float32 and t.device == x.device
-                   for t in tensors) and all(t.is_contiguous() for t in tensors[1:])
+                   and not t.is_neg() for t in tensors) and all(t.is_contiguous() for t in tensors[1:])
 
     def _inference(self, x):
         """The layers below in one call of dn_unet_forward, or None if it does
