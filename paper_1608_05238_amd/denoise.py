@@ -94,8 +94,10 @@ class _Conv3x3(torch.autograd.Function):
         xb, w = ctx.saved_tensors
         n, ci, h, wd = ctx.shape
         co = w.shape[0]
-        gy = gy.detach().resolve_neg().float()
         gx = gw = gb = None
+        if ctx.needs_input_grad[2] and gy.requires_grad and torch.is_grad_enabled():
+            gb = gy.sum(dim=(0, 2, 3))   # part of a graph of its own (create_graph)
+        gy = gy.detach().resolve_neg().float()
         if ctx.needs_input_grad[0]:
             # the input gradient: the same convolution with the weights flipped
             # and input / output channels swapped
@@ -105,14 +107,16 @@ class _Conv3x3(torch.autograd.Function):
             if gl.stride() != (co * h * wd, 1, co * wd, co):   # a size of one leaves its stride open
                 gl = gl.permute(0, 2, 3, 1).reshape(n, h, wd, co).contiguous()
             gw = torch.empty((co, ci, 3, 3), dtype=torch.float32, device=gy.device)
-            gb = torch.empty(co, dtype=torch.float32, device=gy.device) if ctx.needs_input_grad[2] else None
+            sums = ctx.needs_input_grad[2] and gb is None
+            if sums:
+                gb = torch.empty(co, dtype=torch.float32, device=gy.device)
             need = lib.dn_conv3x3_grads_bytes(n, ci, co, h, wd)
             ws = torch.empty(max(need, 16), dtype=torch.uint8, device=gy.device)
             L.check("dn_conv3x3_grads",
                     lib.dn_conv3x3_grads(xb.data_ptr(), gl.data_ptr(), gw.data_ptr(),
-                                         None if gb is None else gb.data_ptr(), ws.data_ptr(), ws.numel(), n, ci, co, h,
+                                         gb.data_ptr() if sums else None, ws.data_ptr(), ws.numel(), n, ci, co, h,
                                          wd, _stream()))
-        elif ctx.needs_input_grad[2]:
+        elif ctx.needs_input_grad[2] and gb is None:
             gb = gy.sum(dim=(0, 2, 3))
         return gx, gw, gb, None
 
