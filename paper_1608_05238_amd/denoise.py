@@ -122,6 +122,12 @@ class _Conv3x3(torch.autograd.Function):
 
 
 def conv3x3(x, w, b):
+    # the kernels take sizes and addresses on trust
+    if x.dim() != 4 or w.dim() != 4 or w.shape[1:] != (x.shape[1], 3, 3) or b.numel() < w.shape[0]:
+        raise ValueError(f"conv3x3: input {tuple(x.shape)}, weights {tuple(w.shape)} and bias {tuple(b.shape)} do not "
+                         "go together")
+    if not x.is_cuda or w.device != x.device or b.device != x.device:
+        raise ValueError(f"conv3x3: input, weights and bias must be on one GPU, not {x.device}, {w.device}, {b.device}")
     return _Conv3x3.apply(x, w, b, torch.is_grad_enabled())
 
 
