@@ -939,6 +939,14 @@ __device__ __forceinline__ void slice_close(const Gen &G, int pool, QueueSlice &
         if (q.base + i < G.cap_c) G.ptile[pool][q.base + i] = kInvalidTile;
 }
 
+// What lanes of a wave wrote to LDS before is there for its other lanes after.
+// (LDS serves a wave in order: this keeps the compiler to it.)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Lanes of the mask below this one.
 __device__ __forceinline__ uint32_t rank_in(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -2168,6 +2176,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
 #pragma unroll
         for (uint32_t u = 0; u < 4u; ++u)
             if (fl < kLeft) pass(u);
+        wave_sync();
         // the batch's events, four lanes to a lane's 64 bytes: written one by
         // one, each event of 16 bytes is a request of its own to the L2
 #pragma unroll
@@ -2178,6 +2187,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) k
             const uint32_t at = (blockIdx.x * per + src) * cap + __shfl(n4, (int)src) + u;
             if ((moved >> src) & 1ull) W.ev[at] = v;
         }
+        wave_sync();
     }
     // packets alive go on in the next round
     const bool going = (fl & kPark) != 0u;
@@ -2424,9 +2434,7 @@ constexpr int kBlockFinish = 256;
 // only LDS and its atomics go out back to back.
 __device__ __forceinline__ void finish_flush_stage(const float *stage, const unsigned long long *stage_dst,
                                                    const double *stage_scale, int n, int K) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     const int total = n * K;
     for (int e = __lane_id(); e < total; e += 64) {
         const int v = e / K;
@@ -2435,9 +2443,7 @@ __device__ __forceinline__ void finish_flush_stage(const float *stage, const uns
             tally_add(reinterpret_cast<double *>(stage_dst[v]) + (e - v * K),
                       __builtin_rint((double)val) * stage_scale[v]);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
 }
 
 // Few packets per lane and long histories make this kernel latency-bound, so
