@@ -154,8 +154,9 @@ typedef struct {
  *                 and live_packets / 128)
  *  grid_max_packets  a single run whose tally fits one workgroup's LDS uses
  *                 the whole-grid kernel up to this many packets, larger
- *                 runs the tiled transport (default 2^21); up to 2^17
- *                 packets it walks instead, except in mc_run_noalloc
+ *                 runs the tiled transport (default 2^21, where runs of up
+ *                 to 2^17 packets walk instead, except in mc_run_noalloc;
+ *                 with another value none of them does)
  *  flush_track    a pixel visit whose accumulated track length, in units of
  *                 the run's weight bound, exceeds this many pixels is added
  *                 to the tile tally in parts, 0 .. 65536 (default 65536)

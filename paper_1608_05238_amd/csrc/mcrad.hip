@@ -3228,6 +3228,7 @@ struct TileTuning {
     uint64_t finish = 0;   // 0: min(2^16, live / 128)
     int tile = 0;          // 0: largest square tile whose tally fits one workgroup's LDS
     uint64_t grid_max = kGridMaxPackets;
+    bool grid_walks = true;    // small grids with few packets walk (unless the caller chose another grid_max)
     double flush_track = kFlushTrackMax;
     uint32_t max_gen = 0;      // 0: kGenBase + kGenPerPool per pool of live packets the run holds
     uint32_t job_min = kJobMin;
@@ -3253,7 +3254,10 @@ bool tuning_from(const mc_options *o, TileTuning &v) {
     if (t.max_visits) v.maxvis = t.max_visits;
     if (t.tile) v.tile = (int)t.tile;
     if (t.finish_packets) v.finish = t.finish_packets;
-    if (t.grid_max_packets) v.grid_max = t.grid_max_packets;
+    if (t.grid_max_packets && t.grid_max_packets != kGridMaxPackets) {   // (the default passed on is no choice)
+        v.grid_max = t.grid_max_packets;
+        v.grid_walks = false;
+    }
     if (t.flush_track > 0.f) v.flush_track = (double)t.flush_track;
     if (t.tail_visits) v.tailvis = t.tail_visits;
     if (t.max_generations) v.max_gen = t.max_generations;
@@ -3308,10 +3312,11 @@ size_t tile_lds_bytes(int tw, int th, int K) {
 // 32x32 at mus 12 / mm, g 0.7, 1e5 packets 9.3 against 14.5, 2e5 12.0 and 15.3,
 // 3e5 16.1 and 17.0, 6e5 25.4 and 19.6; 12x10 of that medium 7.8 and 10.6, 10.7
 // and 11.0, 13.4 and 11.9, 20.0 and 14.3.  (More packets in a thin medium walk
-// faster too, but what a medium is like only the device knows.)
+// faster too, but what a medium is like only the device knows.)  A caller who
+// sets grid_max_packets gets the kernel it names.
 bool is_tiled(const mc_medium *m, const mc_run *run, const TileTuning &tt) {
     if ((size_t)m->nx * m->nz * (2 * run->n_harm + 1) * sizeof(double) > kLdsGridMax) return true;
-    return run->n_packets > tt.grid_max || (tt.ev_max && run->n_packets <= kWalkGridMax);
+    return run->n_packets > tt.grid_max || (tt.ev_max && tt.grid_walks && run->n_packets <= kWalkGridMax);
 }
 
 // Whole-grid mode workspace: problem, medium, CDF, tally, ledger, per-chunk counters.
