@@ -141,8 +141,9 @@ typedef struct {
  *                 (a run or batch whose pool holds fewer than 2^23 live
  *                 packets uses half that, to spread over more workgroups;
  *                 default 16384)
- *  max_visits     visits in one tile before a packet pauses until the next
- *                 generation, >= 1 (default 64)
+ *  max_visits     visits in one tile after which a packet pauses until the next
+ *                 generation, >= 1 (default 64); looked at every fourth
+ *                 segment, between two visits
  *  tile           tile side in pixels, 1 .. 256 (default, or a tile whose
  *                 tally does not fit: the largest square tile whose tally
  *                 fits the LDS of one workgroup per CU, 23 at N = 16)
@@ -161,7 +162,8 @@ typedef struct {
  *                 the run's weight bound, exceeds this many pixels is added
  *                 to the tile tally in parts, 0 .. 65536 (default 65536)
  *  tail_visits    once a job has turned quiet (quiet_percent), its packets
- *                 pause after this many more visits, 0 .. 2^30 (default 1)
+ *                 pause after this many more visits, 0 .. 2^30 (default 1);
+ *                 looked at like max_visits
  *  max_generations  tiled generations (rounds, in a run without generations)
  *                 enqueued per call, 1 .. 65536
  *                 (default 0: 100, plus 30 per tile along the longest
@@ -178,7 +180,8 @@ typedef struct {
  *                 has not ended number at most this percent of
  *                 min(job packets, threads of a tile workgroup: 1024 for
  *                 N <= 16, else 512); its packets then pause after
- *                 tail_visits more visits, 1 .. 100 (default 50) */
+ *                 tail_visits more visits, 1 .. 100 (default 50, for which
+ *                 it is 90 in a job of at least eight packets a thread) */
 typedef struct {
     uint64_t live_packets;
     uint32_t job_packets;

@@ -853,6 +853,7 @@ struct Gen {
     uint32_t slots;               // workgroups of the tile kernel
     uint32_t direct;              // the packets walk from their launch: no records are counted or sorted
     uint32_t quiet_pct;           // a job turns quiet when this percent of its lanes' worth of stays is left
+    uint32_t quiet_many;          // the same for a job of many packets a lane
     uint32_t slice;               // slots a wave reserves at a time in a carried region (64 .. 256)
     const ProbDev *probs;
     const uint32_t *tile_prob;    // problem of each global tile
@@ -1514,11 +1515,11 @@ k_transport_tile(Gen G, int g) {
         // quiet_pct percent of its lanes' worth (min(cnt, lanes)); from then
         // on a packet pauses after tail_visits more visits, so the workgroup
         // is not held by its longest stays (they resume next generation).
-        // With many packets per lane that is earlier, at 9/5 of the percentage:
+        // With many packets per lane that is earlier by default (quiet_many):
         // one more generation costs little beside such a job (1e8 packets on a
         // 256^2 disc 587 ms at 90 percent, 596 at 50; 2e7 168 at 50, 172 at 75).
         const uint32_t lanes = tile_block(NH);
-        const uint32_t pct = min(100u, cnt >= 8u * lanes ? G.quiet_pct * 9u / 5u : G.quiet_pct);
+        const uint32_t pct = cnt >= 8u * lanes ? G.quiet_many : G.quiet_pct;
         const uint32_t quiet_at = min(cnt, lanes) * pct / 100u;
         bool quiet = false;       // wave-uniform
         uint32_t lim = G.max_visits;   // visits after which the packet pauses
@@ -3199,7 +3200,8 @@ constexpr uint32_t kGenBase = 100, kGenPerTile = 30, kGenPerPool = 48;
 constexpr int kTileWavesMax = 256 * 16;       // bound on resident waves of the tiled kernel
 constexpr int kTileSlotsMax = kTileWavesMax / (tile_block(MC_NHARM_MAX) / 64);   // and on its workgroups
 constexpr uint32_t kJobMin = 1024;             // smallest job of a generation with few packets (see gen_scan)
-constexpr uint32_t kQuietPercent = 50;         // see the quiet rule of k_transport_tile
+// see the quiet rule of k_transport_tile; many: jobs of eight packets a lane, unless the caller chose a percentage
+constexpr uint32_t kQuietPercent = 50, kQuietPercentMany = 90;
 
 // Walk and tally (see k_walk).
 // Runs up to this many packets walk from their launch.  Milliseconds, against
@@ -3791,6 +3793,7 @@ mc_status run_batch(const BatchProblem *pb, int n, const TileTuning &tt, mc_time
     G.job_size = B.job;
     G.job_min = std::min(B.tt.job_min, B.job);
     G.quiet_pct = B.tt.quiet;
+    G.quiet_many = B.tt.quiet == kQuietPercent ? kQuietPercentMany : B.tt.quiet;
     G.max_visits = B.tt.maxvis;
     G.tail_visits = B.tt.tailvis;
     G.finish_at = (uint32_t)B.finish;
