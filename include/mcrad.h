@@ -219,7 +219,11 @@ typedef struct {
 } mc_options;
 
 /* Bytes of device workspace a forward/adjoint run needs (tallies, packet
- * queues, source tables).  0 on invalid arguments. */
+ * queues, source tables, and for the events of packets that walk 400 KiB per
+ * packet, up to 3 GiB).  0 on invalid arguments.  With less memory at hand the
+ * same results come later: with grid_max_packets set on a grid whose tally fits
+ * LDS (its kernel needs the grid alone), else with live_packets below the run's
+ * packets and a small finish_packets. */
 size_t mc_workspace_bytes(const mc_medium *medium, const mc_source *src, int n_src, const mc_run *run,
                           const mc_options *opts);
 

@@ -176,6 +176,30 @@ class _Options:
         return C.byref(self.o)
 
 
+def _workspace(need, name: str, tuning: Optional[dict], timer: Optional[Timer], n_packets: int, device):
+    """A workspace of need(options) bytes, aligned, and the options that go with it.
+    Where the device has no room for it the run takes a schedule that needs
+    less -- small grids the whole-grid kernel, others a pool that holds not
+    all of their packets, of which few walk at the end -- and gives the same
+    results, later."""
+    small = {**(tuning or {}), "finish_packets": 16,
+             "live_packets": max(1024, min((tuning or {}).get("live_packets") or 1 << 26, n_packets - 1))}
+    if (tuning or {}).get("grid_max_packets") in (None, 0, 1 << 21):
+        small["grid_max_packets"] = (1 << 21) - 1
+    for i, t in enumerate((tuning, small)):
+        opts = _Options(t, timer)
+        size = need(opts.ref())
+        if size == 0:
+            raise L.MCError(name, L.MC_ERR_INVALID_ARG)
+        try:
+            ws = torch.empty(size + 256, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            if i == 1:
+                raise
+            continue
+        return ws, opts
+
+
 def mc_workspace_bytes(medium: Medium, sources: Sequence, run: L.mc_run, tuning: Optional[dict] = None) -> int:
     dev = medium.mua.device
     src = _Sources(sources, dev)
@@ -188,12 +212,11 @@ def _mc(name: str, medium: Medium, sources: Sequence, run: L.mc_run, out: Option
     dev = medium.mua.device
     src = _Sources(sources, dev)
     m = medium.c()
+    need = lambda o: lib.mc_workspace_bytes(C.byref(m), src.arr, src.n, C.byref(run), o)
     opts = _Options(tuning, timer)
-    need = lib.mc_workspace_bytes(C.byref(m), src.arr, src.n, C.byref(run), opts.ref())
-    if need == 0:
-        raise L.MCError("mc_workspace_bytes", L.MC_ERR_INVALID_ARG)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+    size = 0 if workspace is None else need(opts.ref())
+    if not size or workspace.numel() < size:
+        workspace, opts = _workspace(need, "mc_workspace_bytes", tuning, timer, run.n_packets, dev)
     base = workspace.data_ptr()
     off = (-base) % 256
     K = 2 * run.n_harm + 1
@@ -356,12 +379,8 @@ def mc_run_batch(problems: Sequence[Problem], ledger: bool = True, stream=None, 
         led = torch.zeros(C.sizeof(L.mc_ledger), dtype=torch.uint8, device=dev) if ledger else None
         outs.append((out, led))
         arr[i] = L.mc_problem(pr.medium.c(), src.arr, src.n, pr.run, int(bool(pr.adjoint)), out.data_ptr(), _ptr(led))
-    opts = _Options(tuning, timer)
-    need = lib.mc_batch_workspace_bytes(arr, n, opts.ref())
-    if need == 0:
-        raise L.MCError("mc_batch_workspace_bytes", L.MC_ERR_INVALID_ARG)
-    dev = problems[0].medium.mua.device
-    ws = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+    ws, opts = _workspace(lambda o: lib.mc_batch_workspace_bytes(arr, n, o), "mc_batch_workspace_bytes", tuning, timer,
+                          sum(pr.run.n_packets for pr in problems), problems[0].medium.mua.device)
     off = (-ws.data_ptr()) % 256
     L.check("mc_run_batch", lib.mc_run_batch(arr, n, opts.ref(), ws.data_ptr() + off, ws.numel() - off,
                                              _stream(stream)))

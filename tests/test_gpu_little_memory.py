@@ -1,0 +1,65 @@
+"""Runs on a device with little memory left: where the buffer for the events
+of walking packets (up to 3 GiB) does not fit, a schedule without it gives the
+same results.  The limit is the allocator's own, 600 MiB above what the process
+holds."""
+import pytest
+
+import phantoms as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def little_memory():
+    import torch
+
+    def limit(mib):
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        total = torch.cuda.get_device_properties(0).total_memory
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (mib << 20)) / total)
+
+    yield limit
+    torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.empty_cache()
+
+
+def _cases(rmc):
+    big = P.disc_phantom(256, 0.1, 0.02, 8.0, 0.9, seed=3, radius=(1.0, 4.0))
+    small = P.homogeneous(32, 32, 0.5, 0.05, 5.0, 0.8)
+    thin = P.homogeneous(24, 24, 0.25, 0.05, 6.0, 0.85)
+    mbig, msmall, mthin = (rmc.Medium.from_phantom(p) for p in (big, small, thin))
+    q = P.map_source(P.residual_like_map(big, seed=4))
+    tuned = rmc.default_tuning()
+    fwd = lambda m, s, n, N, t=None: lambda: rmc.mc_forward(m, s, rmc.make_run(n, N, seed=5), tuning=t)[0]
+    return [fwd(mthin, [P.point_source(2.0, 2.5)], 4000, 5), fwd(msmall, P.pencil_top_centre(small), 100_000, 8),
+            fwd(msmall, P.pencil_top_centre(small), 100_000, 8, tuned), fwd(mbig, P.four_side_lines(big), 10_000, 16),
+            fwd(mbig, P.four_side_lines(big), 1_000_000, 16),
+            lambda: rmc.mc_adjoint(mbig, [q], rmc.make_run(50_000, 16, seed=6, stream_tag=1))[0],
+            lambda: rmc.mc_run_batch([rmc.Problem(mbig, P.four_side_lines(big), rmc.make_run(60_000, 8, seed=7)),
+                                      rmc.Problem(msmall, P.pencil_top_centre(small), rmc.make_run(50_000, 8, seed=8))])]
+
+
+def test_runs_without_room_for_the_events(little_memory):
+    import torch
+    from paper_1608_05238_amd import rmc
+    cases = _cases(rmc)
+    flat = lambda r: [o for o, _ in r] if isinstance(r, list) else [r]
+    want = [[o.cpu() for o in flat(c())] for c in cases]
+    little_memory(600)
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
+    for i, (c, w) in enumerate(zip(cases, want)):
+        for a, b in zip(flat(c()), w):
+            assert torch.equal(a.cpu(), b), i
+        torch.cuda.empty_cache()
+
+
+def test_no_room_at_all_is_still_an_error(little_memory):
+    import torch
+    from paper_1608_05238_amd import rmc
+    ph = P.homogeneous(256, 256, 0.1, 0.02, 8.0, 0.9)
+    med = rmc.Medium.from_phantom(ph)
+    little_memory(64)
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        rmc.mc_forward(med, P.pencil_top_centre(ph), rmc.make_run(100_000, 16))
