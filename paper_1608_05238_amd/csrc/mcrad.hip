@@ -4352,8 +4352,9 @@ mc_status mc_timer_read(mc_timer *timer, double *transport_ms, uint64_t *launche
 }
 
 const char *mc_build_info(void) {
-    return "librmc gfx950: FP32 transport; 64-bit fixed-point tally in LDS (whole grid when it fits, else square "
-           "tiles with packet migration between tiles, generations steered on the device), added to an FP64 HBM map";
+    return "librmc gfx950: FP32 transport; 64-bit fixed-point tally in LDS, of the whole grid or of square tiles "
+           "(packets migrate between tiles in generations, or few of them walk and are tallied in rounds; steered on "
+           "the device), added to an FP64 HBM map";
 }
 
 }  // extern "C"
