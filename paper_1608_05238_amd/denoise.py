@@ -165,15 +165,18 @@ class UNet(nn.Module):
     def _plain(self, x) -> bool:
         """Whether a call without gradients may run as one: plain FP32 tensors
         on the current device and nothing that has to see the layers (hooks,
-        tracing, forward-mode derivatives, autocast, replaced layers)."""
+        tracing, forward-mode derivatives, autocast, replaced layers).  Some of
+        this PyTorch keeps in names that are its own: where one is missing the
+        call goes layer by layer."""
         if (torch.is_grad_enabled() or type(x) is not torch.Tensor or not x.is_cuda or x.dim() != 4 or x.numel() == 0
                 or x.shape[1] != self.out.shape[0] or torch.is_autocast_enabled("cuda") or torch.jit.is_tracing()
-                or torch.compiler.is_compiling() or forward_ad._current_level >= 0
-                or x.device.index != torch.cuda.current_device() or nn_module._has_any_global_hook()):
+                or torch.compiler.is_compiling() or getattr(forward_ad, "_current_level", 0) >= 0
+                or x.device.index != torch.cuda.current_device()
+                or getattr(nn_module, "_has_any_global_hook", lambda: True)()):
             return False
         layers = self._layers()
-        if any(type(c) is not Conv3x3 or c._forward_hooks or c._forward_pre_hooks or "forward" in c.__dict__
-               for c in layers):
+        if any(type(c) is not Conv3x3 or getattr(c, "_forward_hooks", True) or getattr(c, "_forward_pre_hooks", True)
+               or "forward" in c.__dict__ for c in layers):
             return False
         tensors = [x, self.out, self.out_bias]
         for c in layers:
