@@ -459,10 +459,22 @@ def batch_workload(args) -> dict:
             "tuning": tuned}
 
 
+WALK_MAX = 3 << 19   # packets up to which a run walks from its launch (kDirectMax)
+
+
+def transport_mode(n: int, generations: int) -> str:
+    """How a run of n packets with default tuning moved them; generations from
+    its ledger (none in the whole-grid kernel)."""
+    if generations == 0:
+        return "whole grid"
+    return "walk and tally" if n <= WALK_MAX else "tiled"
+
+
 def pencil32(args) -> dict:
     """Forward MC on the 32x32 pencil-beam medium (0.5 mm pixels, mua 0.05,
     mus 5, g 0.8) at args.packets packets, N = 8 and N = 16 (at 1e8 packets
-    both take the tiled transport; small runs walk from their launch)."""
+    both take the tiled transport; smaller runs the whole-grid kernel or a
+    walk from their launch, see "mode")."""
     import torch
     import phantoms as P
     from paper_1608_05238_amd import rmc
@@ -479,7 +491,7 @@ def pencil32(args) -> dict:
         dt = time.perf_counter() - t0
         L = rmc.ledger_dict(led)
         res[f"N{N}"] = {"packets_per_s": n / dt, "ms": dt * 1e3, "visits_per_packet": L["visits"] / n,
-                        "mode": "walk and tally" if n <= 3 << 20 else "tiled"}
+                        "mode": transport_mode(n, L["generations"])}
         log(f"pencil32 N={N}: {n / dt:.3e} packets/s")
     out = {"metric": "packets/s fwd MC, 32x32 pencil beam", "value": res["N8"]["packets_per_s"],
            "unit": "packets/s", "higher_is_better": True, "n_gpus": 1, "dtype": "f32", "data": "synthetic",
