@@ -424,7 +424,8 @@ __global__ void __launch_bounds__(kThreads) k_unet_out(const float *a, const flo
     }
 }
 
-// ---- weight gradient
+// ---- weight gradient from BF16 operands, for C callers that hold those and no
+// scratch memory (dn_conv3x3_wgrad); a layer's own is below
 // gw[co][tap][ci] = sum_p gy[p][co] x[p + off(tap)][ci].  GEMM per tap with
 // M = output channels, N = input channels, K = pixels.  A workgroup holds 64
 // output channels x one chunk of 32 input channels x the nine taps and runs

@@ -523,10 +523,12 @@ def gradient_study(model: UNet, n_harm: int, ref_packets: int, counts: Sequence[
 def conv_bench(reps: int = 20, log=None) -> dict:
     """Achieved rate of the convolution kernels on the U-Net's layer shapes
     at 256x256 (batch 16, channels of the 6-level configuration and of the
-    3-level one): forward, input gradient (the forward kernel on the flipped
-    weights) and weight gradient, each the fastest of `reps` launches (HIP
-    events), in dense BF16 TFLOP/s (2 flops per multiply-add of the 3x3
-    convolution, padding channels not counted)."""
+    3-level one), as a training step calls them: forward from FP32 activations
+    with the BF16 copy for the backward pass (the input gradient is the same
+    kernel on the flipped weights, without the copy), and weight and bias
+    gradient from that copy and the FP32 upstream gradient; each the fastest of
+    `reps` calls (HIP events), in dense BF16 TFLOP/s (2 flops per multiply-add of
+    the 3x3 convolution, padding channels not counted)."""
     lib = L.load()
     dev = torch.device("cuda", torch.cuda.current_device())
     st = _stream()
@@ -535,11 +537,15 @@ def conv_bench(reps: int = 20, log=None) -> dict:
     rows = []
     for n, ci, co, h, w in shapes:
         g = torch.Generator(device="cpu").manual_seed(ci * co)
-        x = torch.randn(n, h, w, ci, generator=g).to(dev, torch.bfloat16)
-        wt = (torch.randn(co, 3, 3, ci, generator=g) / (3 * ci ** 0.5)).to(dev, torch.bfloat16)
-        gy = torch.randn(n, h, w, co, generator=g).to(dev, torch.bfloat16)
+        x = torch.randn(n, h, w, ci, generator=g).to(dev)
+        wp = _packed((torch.randn(co, ci, 3, 3, generator=g) / (3 * ci ** 0.5)).to(dev), False)
+        gy = torch.randn(n, h, w, co, generator=g).to(dev)
+        bias = torch.zeros(co, device=dev)
         y = torch.empty(n, h, w, co, device=dev)
-        gw = torch.empty(co, 3, 3, ci, device=dev)
+        xb = torch.empty(n, h, w, _pad8(ci), dtype=torch.bfloat16, device=dev)
+        gw, gb = torch.empty(co, ci, 3, 3, device=dev), torch.empty(co, device=dev)
+        ws = torch.empty(lib.dn_conv3x3_grads_bytes(n, ci, co, h, w), dtype=torch.uint8, device=dev)
+        strides = (C.c_int64 * 4)(h * w * ci, 1, w * ci, ci)
         flops = 2.0 * 9 * ci * co * n * h * w
 
         def best(fn):
@@ -555,10 +561,10 @@ def conv_bench(reps: int = 20, log=None) -> dict:
                 b = min(b, e0.elapsed_time(e1) * 1e-3)
             return b
 
-        tf = best(lambda: L.check("dn_conv3x3_fwd", lib.dn_conv3x3_fwd(x.data_ptr(), wt.data_ptr(), None, y.data_ptr(),
-                                                                        n, ci, co, h, w, st)))
-        tg = best(lambda: L.check("dn_conv3x3_wgrad", lib.dn_conv3x3_wgrad(x.data_ptr(), gy.data_ptr(), gw.data_ptr(),
-                                                                            n, ci, co, h, w, st)))
+        tf = best(lambda: L.check("dn_conv3x3_f32", lib.dn_conv3x3_f32(
+            x.data_ptr(), strides, wp.data_ptr(), bias.data_ptr(), y.data_ptr(), xb.data_ptr(), n, ci, co, h, w, st)))
+        tg = best(lambda: L.check("dn_conv3x3_grads", lib.dn_conv3x3_grads(
+            xb.data_ptr(), gy.data_ptr(), gw.data_ptr(), gb.data_ptr(), ws.data_ptr(), ws.numel(), n, ci, co, h, w, st)))
         r = {"shape": [n, ci, co, h, w], "gflop": flops / 1e9, "fwd_ms": tf * 1e3, "fwd_tflops": flops / tf / 1e12,
              "wgrad_ms": tg * 1e3, "wgrad_tflops": flops / tg / 1e12}
         rows.append(r)
