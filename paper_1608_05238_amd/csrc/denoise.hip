@@ -556,7 +556,16 @@ __global__ void __launch_bounds__(kThreads) k_conv3x3_wgrad(const uint16_t *__re
 // timing.  16 x 256^2 pixels, 48 x 48 channels: 90 us, the sum 9 us; from a
 // converted copy (26 us), with transposing stores to LDS, three shifted copies
 // of the halo and atomics 267 us, and 86 us for the bias gradient.
+//
+// A sum of many FP32 terms in one register loses a rounding a term, so every
+// kWFold blocks the sums go into a second set and start again.  48 x 48 channels
+// leave no registers for one (248 of 256): there a workgroup takes at most
+// kWBlocks blocks.  Relative error against 64 bits, 16 x 256^2 pixels: 224 x 128
+// channels (455 blocks a workgroup) 1.5e-6 -> 2.0e-7, the bias 5.5e-7 -> 1.6e-7;
+// 96 x 96 channels 5.0e-7 -> 3.3e-7.  896 -> 870 us for the former.
 constexpr int kWY = 8, kWX = 16, kWHalo = (kWY + 2) * (kWX + 2);
+constexpr int kWFold = 8, kWBlocks = 32;
+constexpr bool wgrad_folds(int mb, int nb) { return mb * nb < 9; }
 
 struct WgradArgs {
     const uint16_t *x;     // [n][h][w][cip]
@@ -579,6 +588,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
     constexpr int GT = kThreads / UG * UG;                              // threads that stage gy: each keeps its channels
     constexpr int XJ = (kWHalo * UX + kThreads - 1) / kThreads, GJ = (kWX * kWY * UG + GT - 1) / GT;
     constexpr int PW = (9 * NB + 3) / 4;                                // (tap, block) pairs of a wave
+    constexpr bool FOLD = wgrad_folds(MB, NB);
     __shared__ u32x4 xs[kWHalo * PX], gs[kWX * kWY * PG];
     __shared__ float bs[GT * 8];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -586,9 +596,12 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
     const u32x4 none = {0u, 0u, 0u, 0u};
     const int gpart = tid % UG, gco = co0 + 8 * gpart;
     u32x4 rx[XJ];
-    float rg[GJ][8], bsum[8];
+    float rg[GJ][8], bsum[8], btot[FOLD ? 8 : 1];
 #pragma unroll
     for (int i = 0; i < 8; ++i) bsum[i] = 0.f;
+    if constexpr (FOLD)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) btot[i] = 0.f;
     auto fetch = [&](int t) {
         const int per = A.tiles_x * A.tiles_y, img = t / per, tt = t - img * per;
         const int ty = (tt / A.tiles_x) * kWY, tx = (tt % A.tiles_x) * kWX;
@@ -628,21 +641,45 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
             const int v = tid + j * kThreads, pix = v / UX, part = v - pix * UX;
             if (v < kWHalo * UX) xs[pix * PX + part] = rx[j];
         }
-        if (tid < GT)
+        if (tid < GT) {
 #pragma unroll
             for (int j = 0; j < GJ; ++j) {
                 const int pix = tid / UG + j * (GT / UG);
-                if (pix >= kWX * kWY) continue;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) bsum[i] += rg[j][i];
-                gs[pix * PG + gpart] = pack8(rg[j]);
+                if (pix < kWX * kWY) gs[pix * PG + gpart] = pack8(rg[j]);
             }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {   // (zeros past the block)
+                float v = rg[0][i];
+#pragma unroll
+                for (int j = 1; j < GJ; ++j) v += rg[j][i];
+                bsum[i] += v;
+            }
+        }
     };
-    f32x4 acc[PW][MB];
+    f32x4 acc[PW][MB], tot[FOLD ? PW : 1][FOLD ? MB : 1];
 #pragma unroll
     for (int i = 0; i < PW; ++i)
 #pragma unroll
-        for (int a = 0; a < MB; ++a) acc[i][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int a = 0; a < MB; ++a) {
+            acc[i][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (FOLD) tot[i][a] = acc[i][a];
+        }
+    auto fold = [&] {
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int i = 0; i < PW; ++i)
+#pragma unroll
+                for (int a = 0; a < MB; ++a) {
+                    tot[i][a] += acc[i][a];
+                    acc[i][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                btot[i] += bsum[i];
+                bsum[i] = 0.f;
+            }
+        }
+    };
     // a read of four pixels x 16 channels per 16 lanes: lane's pixel 4 (lane / 16) + (lane % 16) / 4, channels 4 (lane % 4)
     const int rpix = 4 * (lane >> 4) + ((lane & 15) >> 2), rch = 4 * (lane & 3);
     const uint16_t *gr = (const uint16_t *)gs + rpix * PG * 8 + rch;
@@ -658,7 +695,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
         stash();
     }
     __syncthreads();
-    for (; t < A.n_tiles; t += gridDim.x) {
+    for (int k = 1; t < A.n_tiles; t += gridDim.x, ++k) {
         const bool next = t + (int)gridDim.x < A.n_tiles;
         if (next) fetch(t + gridDim.x);
 #pragma unroll
@@ -681,8 +718,18 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
             }
         }
         __syncthreads();
+        if (FOLD && k % kWFold == 0) fold();
         if (next) stash();
         __syncthreads();
+    }
+    if constexpr (FOLD) {
+        fold();
+#pragma unroll
+        for (int i = 0; i < PW; ++i)
+#pragma unroll
+            for (int a = 0; a < MB; ++a) acc[i][a] = tot[i][a];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) bsum[i] = btot[i];
     }
     float *out = A.part + (((size_t)blockIdx.x * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z) * (9 * NB * MB * 256);
 #pragma unroll
@@ -707,7 +754,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_wgrad(WgradArgs A) {
 // sixteen waves of a workgroup share its slices (so a load is of 64
 // consecutive values), and the first adds their sums in order; the sums over
 // slices are FP64 (rounding is then that of the parts: relative error of the
-// bias gradient of 16 x 256^2 pixels 3e-8).  Bound by the parts' bytes and, with
+// bias gradient of 16 x 256^2 pixels 3e-8 of values of one sign, 9e-8 of both).  Bound by the parts' bytes and, with
 // few values, by latency: 512 slices of 48 x 48 channels, 42 MB, 9 us (24
 // with a value's slices in consecutive lanes).
 constexpr int kSumWaves = 16;
@@ -912,7 +959,10 @@ struct WgradPlan {
 
 // Two workgroups a CU over all channel tiles, no more than there are blocks; up
 // to 48 x 48 channels each (more would not fit the registers beside the next
-// block's loads).
+// block's loads).  More workgroups where one that cannot fold would take too many
+// blocks (96 x 96 channels, 16 x 256^2 pixels: 275 us, 232 with 64 blocks each; 48 x
+// 32 channels each, which fold, 351; sums stored between blocks spill, and take
+// 268 and, with 48 x 48 channels, 91 for 74).
 WgradPlan wgrad_plan(int n, int ci, int co, int h, int w) {
     WgradPlan P;
     P.mb = blocks_for(co, 3);
@@ -921,7 +971,11 @@ WgradPlan wgrad_plan(int n, int ci, int co, int h, int w) {
     P.tz = (ci + 16 * P.nb - 1) / (16 * P.nb);
     const long long tiles = (long long)n * ((w + kWX - 1) / kWX) * ((h + kWY - 1) / kWY);
     const long long most = std::max<long long>(1, 512 / ((long long)P.ty * P.tz));
-    const long long rounds = (tiles + most - 1) / most;
+    long long rounds = (tiles + most - 1) / most;
+    if (!wgrad_folds(P.mb, P.nb)) {   // whole multiples of the workgroups that fit at once
+        const long long times = (rounds + kWBlocks - 1) / kWBlocks;
+        rounds = (rounds + times - 1) / times;
+    }
     P.slices = (int)((tiles + rounds - 1) / rounds);
     return P;
 }
