@@ -178,11 +178,16 @@ class UNet(nn.Module):
         if any(type(c) is not Conv3x3 or getattr(c, "_forward_hooks", True) or getattr(c, "_forward_pre_hooks", True)
                or "forward" in c.__dict__ for c in layers):
             return False
-        tensors = [x, self.out, self.out_bias]
+        if x.dtype is not torch.float32 or x.is_neg():
+            return False
+        dev, held = x.device, [self.out, self.out_bias]
         for c in layers:
-            tensors += [c.weight, c.bias]
-        return all(type(t) in (torch.Tensor, nn.Parameter) and t.dtype == torch.float32 and t.device == x.device
-                   and not t.is_neg() for t in tensors) and all(t.is_contiguous() for t in tensors[1:])
+            held += (c.weight, c.bias)
+        for t in held:   # (a loop: some fifty tensors, checked on every call)
+            if (type(t) not in (nn.Parameter, torch.Tensor) or t.dtype is not torch.float32 or t.device != dev
+                    or t.is_neg() or not t.is_contiguous()):
+                return False
+        return True
 
     def _inference(self, x):
         """The layers below in one call of dn_unet_forward, or None if it does
