@@ -14,7 +14,8 @@ average, so a counter of a plain copy of known size can calibrate the others;
 (from the per-dispatch kernel trace), e.g. the launches of a benchmark's
 timed steps; `counters-tail` sums each counter over the last n dispatches of
 the named kernels; `runs` cuts a kernel trace into Monte Carlo runs and sums
-each run's generation, tile and finisher kernels.  Given <launches>, `tail`
+each run's generation, tile, walk, tally and finisher kernels.  A kernel is named
+as the tables show it, or without its template arguments (all of them).  Given <launches>, `tail`
 and `counters-tail` also divide the totals by it: a benchmark's timer may
 bracket fewer launches than the dispatches its steps make (a launch that
 returns at once and is not timed), and the per-launch figures then match the
@@ -38,6 +39,10 @@ def _short(name: str) -> str:
 
 def _find(root: str, suffix: str) -> list:
     return sorted(glob.glob(os.path.join(root, "**", f"*{suffix}"), recursive=True))
+
+
+def _named(k: str, kernels: list) -> bool:
+    return k in kernels or k.split("<")[0] in kernels
 
 
 def stats(root: str) -> str:
@@ -93,7 +98,7 @@ def counters_tail(root: str, n: int, kernels: list, launches: int = 0) -> str:
         with open(f, newline="") as fh:
             for r in csv.DictReader(fh):
                 k = _short(r["Kernel_Name"])
-                if k in kernels:
+                if _named(k, kernels):
                     d = (int(r["Dispatch_Id"]), r.get("Agent_Id", ""))
                     vals[d][r["Counter_Name"]] += float(r["Counter_Value"])
                     names[d] = k
@@ -120,12 +125,13 @@ def counters_tail(root: str, n: int, kernels: list, launches: int = 0) -> str:
     return "\n".join(out)
 
 
-def runs(root: str, first_kernel: str = "k_ctl_init") -> str:
-    """The kernel trace cut into Monte Carlo runs (a run starts at each
-    dispatch of first_kernel): per run its span from that dispatch to the end
-    of its last transport dispatch, the summed durations of the generation
-    kernels, of the tile kernel and of the finisher, and how many tile
-    launches found work (longer than 6 us)."""
+def runs(root: str) -> str:
+    """The kernel trace cut into Monte Carlo runs (or batches: a run starts at
+    the first k_setup after another kernel, or at the k_map_cdf before it): per
+    run its span from there to the end of its last transport dispatch, the
+    summed durations of the tile kernel and how many of its launches found
+    work (longer than 6 us), of the generation kernels, of the rounds' walks,
+    tallies and sorts, and of the finisher."""
     files = _find(root, "kernel_trace.csv")
     if not files:
         raise SystemExit(f"no *kernel_trace.csv under {root}")
@@ -135,29 +141,25 @@ def runs(root: str, first_kernel: str = "k_ctl_init") -> str:
             for r in csv.DictReader(fh):
                 rows.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), _short(r["Kernel_Name"])))
     rows.sort()
-    out = ["| run | span ms | tile ms | busy / tile launches | generation kernels ms | finisher ms |",
-           "|---|---|---|---|---|---|"]
-    cur, k = None, 0
-    def emit(run, k):
-        tr = [x for x in run if x[2].startswith(("k_transport_tile", "k_finish", "k_gen_"))]
-        if not tr:
-            return
-        span = (tr[-1][1] - run[0][0]) / 1e6
-        tile = [(e - b) / 1e3 for b, e, n in run if n.startswith("k_transport_tile")]
-        gen = sum((e - b) / 1e3 for b, e, n in run if n.startswith("k_gen_"))
-        fin = sum((e - b) / 1e3 for b, e, n in run if n.startswith("k_finish"))
-        busy = sum(1 for t in tile if t > 6.0)
-        out.append(f"| {k} | {span:.1f} | {sum(tile) / 1e3:.1f} | {busy} / {len(tile)} | {gen / 1e3:.1f} | {fin / 1e3:.1f} |")
+    out = ["| run | span ms | tile ms | busy / tile launches | generation kernels ms | walk ms | tally ms | "
+           "count and sort ms | finisher ms |", "|---|---|---|---|---|---|---|---|---|"]
+    first = ("k_setup", "k_map_cdf")
+    transport = ("k_transport_tile", "k_finish", "k_gen_", "k_walk", "k_tally", "k_run_")
+    all_runs, last = [], ""
     for row in rows:
-        if row[2] == first_kernel:
-            if cur:
-                emit(cur, k)
-                k += 1
-            cur = []
-        if cur is not None:
-            cur.append(row)
-    if cur:
-        emit(cur, k)
+        if row[2] in first and last not in first:
+            all_runs.append([])
+        if all_runs:
+            all_runs[-1].append(row)
+        last = row[2]
+    for k, run in enumerate(r for r in all_runs if any(x[2].startswith(transport) for x in r)):
+        tr = [x for x in run if x[2].startswith(transport)]
+        ms = lambda *names: sum(e - b for b, e, n in run if n.startswith(names)) / 1e6
+        tile = [(e - b) / 1e3 for b, e, n in run if n.startswith("k_transport_tile")]
+        busy = sum(1 for t in tile if t > 6.0)
+        out.append(f"| {k} | {(tr[-1][1] - run[0][0]) / 1e6:.1f} | {sum(tile) / 1e3:.1f} | {busy} / {len(tile)} | "
+                   f"{ms('k_gen_'):.1f} | {ms('k_walk'):.1f} | {ms('k_tally'):.1f} | {ms('k_run_'):.1f} | "
+                   f"{ms('k_finish'):.1f} |")
     return "\n".join(out)
 
 
@@ -170,7 +172,7 @@ def tail(root: str, n: int, kernels: list, launches: int = 0) -> str:
         with open(f, newline="") as fh:
             for r in csv.DictReader(fh):
                 k = _short(r["Kernel_Name"])
-                if k in kernels:
+                if _named(k, kernels):
                     rows.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), k))
     rows.sort()
     last = rows[-n:]
