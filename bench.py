@@ -52,19 +52,20 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 
 # HBM traffic of the transport launches from two rocprofv3 counter passes
-# (FETCH_SIZE, then WRITE_SIZE, KiB summed over all 1116 transport dispatches
-# of one benchmark step and divided by the 1114 launches the timer brackets:
-# the two untimed finisher passes for unlaunched packets find none), each
+# (FETCH_SIZE, then WRITE_SIZE, KiB summed over all 1272 transport dispatches
+# of one benchmark step and divided by the 1218 launches the timer brackets:
+# it takes a round's two walk kernels as one launch, and the two finisher
+# passes for unlaunched packets, which find none, are not timed), each
 # scaled by what the same counter reads for a plain 1 GiB device copy.  Valid
 # only for the kernel source it was measured on: reported as null once that
 # source changes.
 TRAFFIC = {
-    "source_sha256": "8bb39fd3887b04371c6d942347b4d62e84295b83b6cd1f108f5dbfd0a7129089",
-    "fetch_kib_per_launch": 253160.5, "fetch_factor": 2.000,
-    "write_kib_per_launch": 364187.4, "write_factor": 1.000,
+    "source_sha256": "1ca7f4269f3cbf0e6064b7e6899ebe4ebb8304db8dd7cdda3fe27e79db476a04",
+    "fetch_kib_per_launch": 243460.3, "fetch_factor": 2.000,
+    "write_kib_per_launch": 321713.7, "write_factor": 1.000,
     # VALU wave-instructions per pixel visit (rocprofv3 SQ_INSTS_VALU over the
     # same dispatches, divided by the step's pixel visits)
-    "valu_per_visit": 13.147,
+    "valu_per_visit": 10.270,
 }
 
 # Algorithmic arithmetic of the method, in lane-operations (one FMA, compare,

@@ -316,7 +316,9 @@ mc_status mc_run_noalloc(const mc_medium *medium, const mc_source *src, int n_sr
 /* Residual (Sec. 2 eq. error_function3, Sec. 6): H = mua a0 (Grueneisen 1),
  * r = hmeas - H, q* = mua r (per unit angle), eps = (dx^2 / 2) sum r^2.
  * coeffs_d: forward FP64 [>=1][nz][nx] (only a0 is read); hmeas_d FP64
- * [nz][nx]; q_star_d FP64 [nz][nx] out (may be NULL); eps_d device double out. */
+ * [nz][nx]; q_star_d FP64 [nz][nx] out (may be NULL, hmeas_d or the a0 plane);
+ * eps_d device double out (inside one of the maps it is written last, by one
+ * workgroup). */
 mc_status mc_residual(const mc_medium *medium, const double *coeffs_d, const double *hmeas_d,
                       double *q_star_d, double *eps_d, void *stream);
 
@@ -354,7 +356,8 @@ mc_status mc_gradient_h(const mc_medium *medium, int n_harm, const double *fwd_d
  * the domain and angle of a radiance times a detector weight function b, both
  * given by harmonic maps with the same convention:
  *   sum_i dx^2 [a0 d0/2pi + (1/pi) sum_n (a_n dc_n + b_n ds_n)].
- * det_d: FP64 [2N+1][nz][nx].  out_d: device double. */
+ * det_d: FP64 [2N+1][nz][nx].  out_d: device double (as eps_d of
+ * mc_residual). */
 mc_status mc_detect(const mc_medium *medium, int n_harm, const double *coeffs_d, const double *det_d,
                     double *out_d, void *stream);
 

@@ -1401,7 +1401,8 @@ __global__ void __launch_bounds__(256) k_gen_scatter(Gen G, int g) {
 }
 
 // ---- generation step 3: move the packets tile by tile
-// Bound by vector issue (95% busy at 4 waves per SIMD): a pass of the inner
+// Bound by vector issue (90% busy at 4 waves per SIMD, the LDS index unit 78%, half
+// of that bank conflicts; 10.2 vector instructions a visit): a pass of the inner
 // loop, one segment of every lane, is ~295 vector instructions at N = 16, of
 // which 64 add the segment to the visit's sums, 70 add a finished visit to the
 // tally and 98 deflect, though about half the lanes do either.  So what counts
@@ -1706,7 +1707,8 @@ k_transport_tile(Gen G, int g) {
 // disc 45.6 -> 19.0 ms, 5e5 adjoint packets at N = 32 on 149 x 101 34.1 -> 13.1
 // ms, against generations and a finisher that added each visit to HBM.  What
 // bounds it now: for few packets the ~170 instructions of a segment in a lone
-// wave (0.45 us); for many, issue in k_walk, the LDS atomics (75% active) in
+// wave (0.45 us); for many, vector issue (62% busy) and the loads of the medium in
+// k_walk, the LDS atomics (index unit 65% active, half of it bank conflicts) in
 // k_tally.
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 constexpr uint32_t kRunSlice = 256;         // run slots a wave reserves at a time
@@ -1862,7 +1864,8 @@ __device__ __forceinline__ void ledger_flush_lane(const ProbDev &O, const Ledger
 // refills and the space left are looked after every fourth.  ONE: a single
 // problem, whose parameters are the same in every lane.  The passes' random
 // numbers come in one of three ways:
-//  * kWalkAll: a wave works out its own.  Bound by issue, with 16 waves a CU
+//  * kWalkAll: a wave works out its own, with 16 waves a CU: vector issue 62%
+//    busy, 59% of its lanes moving, the rest waits for the medium
 //    (1.34e8 events of 1e6 packets on a 256^2 disc: 1.1 - 1.3 ms, against 1.6
 //    with rings, whose LDS leaves room for 7 workgroups a CU).
 //  * kWalkRing: a workgroup is two waves; the first moves the packets, the
@@ -2920,7 +2923,8 @@ __global__ void k_normalise(const ProbDev *pd, int N, const GenCtl *ctl, const W
 // hands its number on through the result's own eight bytes, and given back by
 // the workgroup that writes the result.  With every slot taken, the first
 // workgroup computes all parts itself.  256^2, N = 16: mc_detect 509 -> 16 us,
-// mc_residual 29 -> 12 us against one workgroup (with 2 us of k_red_begin).
+// mc_residual 29 -> 12 us against one workgroup (with 2 us of k_red_begin; kernels
+// alone 13.1 and 10.2).
 //
 // A slot's number is handed on as a signalling NaN that no sum can be
 // (red_store): a workgroup that starts after the first one has written the
